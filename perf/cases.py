@@ -1,0 +1,306 @@
+"""The workloads this library's speed is measured on: the calls a program
+makes through the Python binding, over the range of sizes, element types and
+data it meets.
+
+Operations
+  compress / decompress   one array on the device, blocking (Codec.compress,
+                          Codec.decompress), into buffers the program keeps
+  roundtrip               several arrays compressed and decompressed with the
+                          asynchronous calls and one sync
+  batch_compress / batch_decompress
+                          many ragged series in one one-shot batch call
+  plan_compress / plan_decompress
+                          the same through a tuned plan replayed as a graph
+  host_compress / host_decompress
+                          pinned host memory to pinned host memory through
+                          the transfer pipeline
+
+Data (all drawn on the GPU from the seed)
+  walk     a random walk kept at a fixed number of decimal places
+  sensor   segments of 65,536 values at 1-6 places with 1 % full-precision
+           outliers and a few NaN, infinities, -0.0 and subnormals
+  mixed    first half a noisy sinusoid at 0-4 places per segment, second half
+           a smooth field at full precision (no decimal structure)
+Batches hold ragged series of 1,024 to 369,000 values, 60 % of them float64,
+at 0-6 decimal places.
+"""
+import math
+
+import numpy as np
+import torch
+
+from paper_2511_04140_amd import codec as C
+
+CHUNK = 1025          # values per chunk of the stream format
+SEGMENT = 65536       # values that share a number of decimal places
+SERIES_LO, SERIES_HI = 1024, 369_000
+# stream bytes per input byte of each data kind (by dtype), as measured
+RATIO = {("walk", "f64"): 0.13, ("walk", "f32"): 0.27, ("sensor", "f64"): 0.643, ("sensor", "f32"): 0.80,
+         ("mixed", "f64"): 0.48, ("mixed", "f32"): 0.434}
+RATIO_SERIES = 0.175
+
+
+def listed():
+    return [
+        # the smallest calls: one message or one small column, where launches
+        # and host work are everything
+        dict(name="compress_tiny_f64", op="compress", dtype="f64", data="walk", n=1500, count=1),
+        dict(name="decompress_tiny_f32", op="decompress", dtype="f32", data="walk", n=3001, count=1),
+        # an ordinary array, a few MB: one column of a table, resident in cache
+        dict(name="compress_8mb_f64", op="compress", dtype="f64", data="walk", n=1 << 20, count=1),
+        dict(name="decompress_8mb_f64", op="decompress", dtype="f64", data="walk", n=1_000_003, count=1),
+        # the large array of the benchmark: 2 GiB of sensor readings
+        dict(name="compress_2gib_sensor_f64", op="compress", dtype="f64", data="sensor", n=1 << 28, count=1),
+        dict(name="decompress_2gib_sensor_f64", op="decompress", dtype="f64", data="sensor", n=1 << 28, count=1),
+        # float32 simulation output, half decimal and half full precision
+        dict(name="compress_mixed_f32", op="compress", dtype="f32", data="mixed", n=(1 << 27) + 12_345, count=1),
+        dict(name="decompress_mixed_f32", op="decompress", dtype="f32", data="mixed", n=(1 << 27) + 12_345, count=1),
+        # a program that enqueues many mid-sized arrays and waits once
+        dict(name="roundtrip_async_f64", op="roundtrip", dtype="f64", data="sensor", n=100_003, count=16),
+        # many ragged series at once: a kept plan, and the one-shot call
+        dict(name="plan_compress_2000", op="plan_compress", dtype="both", data="series", n=0, count=2000),
+        dict(name="batch_decompress_200", op="batch_decompress", dtype="both", data="series", n=0, count=200),
+        # data that lives on the host and streams through the GPU
+        dict(name="host_compress_f64", op="host_compress", dtype="f64", data="sensor", n=(1 << 24) + 4_099, count=1),
+    ]
+
+
+def draw(rng):
+    op = rng.choice(["compress", "decompress", "compress", "decompress", "roundtrip", "batch_compress",
+                     "batch_decompress", "plan_compress", "plan_decompress", "host_compress", "host_decompress"])
+    if op.startswith(("batch", "plan")):
+        hi = 2000 if op.startswith("plan") else 400
+        return dict(op=op, dtype="both", data="series", n=0, count=int(round(_log_uniform(rng, 2, hi))))
+    dtype = rng.choice(["f64", "f32"])
+    data = rng.choice(["walk", "sensor", "mixed"])
+    if op == "roundtrip":
+        return dict(op=op, dtype=dtype, data=data, n=int(_log_uniform(rng, 1000, 1 << 20)), count=rng.randint(2, 24))
+    hi = 1 << 25 if op.startswith("host") else 1 << 27
+    return dict(op=op, dtype=dtype, data=data, n=int(_log_uniform(rng, 1, hi)), count=1)
+
+
+def _log_uniform(rng, lo, hi):
+    return math.exp(rng.uniform(math.log(lo), math.log(hi)))
+
+
+# ---- inputs -----------------------------------------------------------------
+
+def _torch_dtype(name):
+    return torch.float64 if name == "f64" else torch.float32
+
+
+def _round_places(x, places, dtype):
+    """x (float64) to `places` decimals, as the nearest float of the dtype
+    (places: a number, or an integer tensor of one per value)."""
+    if torch.is_tensor(places):  # exact powers, which pow() on the GPU does not promise
+        scale = torch.tensor([10.0 ** k for k in range(7)], dtype=torch.float64, device="cuda")[places]
+    else:
+        scale = 10.0 ** places
+    if dtype == torch.float64:
+        return torch.round(x * scale) / scale + 0.0
+    scale32 = scale.to(torch.float32) if torch.is_tensor(scale) else scale
+    return torch.round(x * scale).to(torch.float32) / scale32 + 0.0
+
+
+def _segment_places(gen, n, lo, hi):
+    """One number of places from lo..hi per SEGMENT values, one per value."""
+    d = torch.randint(lo, hi + 1, ((n + SEGMENT - 1) // SEGMENT,), generator=gen, device="cuda")
+    return torch.repeat_interleave(d, SEGMENT)[:n]
+
+
+def _normal(gen, n):
+    return torch.randn(n, generator=gen, device="cuda", dtype=torch.float32).to(torch.float64)
+
+
+def _walk(gen, n, sigma):
+    """A Gaussian random walk, summed in integers so that the same seed gives
+    the same values in every process."""
+    steps = torch.round(_normal(gen, n) * (sigma * 2.0 ** 32)).to(torch.int64)
+    return torch.cumsum(steps, 0).to(torch.float64) * 2.0 ** -32
+
+
+def _values(gen, n, data, dtype):
+    t = torch.arange(n, device="cuda", dtype=torch.float64)
+    if data == "walk":
+        sigma = 0.5 if dtype == torch.float64 else 0.02  # a float32 keeps six digits
+        return _round_places(100.0 + _walk(gen, n, sigma), 2, dtype)
+    if data == "sensor":
+        x = 100.0 * torch.sin(t * (2 * math.pi / 1e4)) + _walk(gen, n, 0.05)
+        v = _round_places(x, _segment_places(gen, n, 1, 6), dtype)
+        wild = torch.rand(n, generator=gen, device="cuda") < 0.01
+        jitter = (torch.rand(n, generator=gen, device="cuda") - 0.5).to(torch.float64) * 2e-3
+        v = torch.where(wild, (x * (1.0 + jitter)).to(dtype), v)
+        odd = torch.tensor([math.nan, math.inf, -math.inf, -0.0, 1e-310 if dtype == torch.float64 else 1e-40],
+                           dtype=dtype, device="cuda")
+        k = n // 100_000
+        if k:
+            at = torch.randint(0, n, (k,), generator=gen, device="cuda")
+            v[at] = odd[at % 5]
+        return v
+    half = n // 2
+    smooth = torch.sin(t[:half] * (2 * math.pi / 4096)) + _normal(gen, half) * 0.01
+    a = _round_places(smooth, _segment_places(gen, half, 0, 4), dtype)
+    noise = (torch.rand(n - half, generator=gen, device="cuda", dtype=torch.float64) - 0.5) * 2e-3
+    b = (torch.sin(t[half:] * (2 * math.pi / 32_768)) * torch.cos(t[half:] * 1e-6) + noise).to(dtype)
+    return torch.cat([a, b])
+
+
+def _arrays(case, seed):
+    """The input arrays of a case, on the GPU."""
+    gen = torch.Generator(device="cuda")
+    gen.manual_seed(seed)
+    if case["data"] != "series":
+        dt = _torch_dtype(case["dtype"])
+        return [_values(gen, case["n"], case["data"], dt) for _ in range(case["count"])]
+    count = case["count"]
+    rng = np.random.default_rng(count)  # the shape of a batch is its own, the seed draws its values
+    lens = np.exp(rng.uniform(np.log(SERIES_LO), np.log(SERIES_HI), count)).astype(np.int64)
+    # lengths scaled to their mean, so that the work goes with the count
+    lens = np.maximum(1, lens * (_mean_series() * count / lens.sum())).astype(np.int64)
+    is64 = rng.permutation(count) < round(0.6 * count)
+    room = (lens + 63) // 64 * 64  # each series starts at a 256-byte boundary, as an allocation does
+    places = torch.repeat_interleave(torch.from_numpy(rng.integers(0, 7, count)).cuda(),
+                                     torch.from_numpy(room).cuda())
+    total = int(room.sum())
+    t = torch.arange(total, device="cuda", dtype=torch.float64)
+    x = 100.0 * torch.sin(t * (2 * math.pi / 1e4)) + _walk(gen, total, 0.05)
+    v = _round_places(x, places, torch.float64)
+    v32 = v.to(torch.float32)
+    at = np.concatenate([[0], np.cumsum(room)[:-1]])
+    return [(v if is64[i] else v32)[at[i]:at[i] + lens[i]] for i in range(count)]
+
+
+def _mean_series():
+    return (SERIES_HI - SERIES_LO) / math.log(SERIES_HI / SERIES_LO)
+
+
+# ---- states and passes ------------------------------------------------------
+
+_codecs = {}
+
+
+def _codec(blocking=True):
+    """The codecs a program keeps: one for blocking calls, one for queues of
+    asynchronous ones."""
+    if blocking not in _codecs:
+        _codecs[blocking] = C.Codec(0, blocking=blocking)
+    return _codecs[blocking]
+
+
+def _pool(sizes):
+    """One zeroed device buffer with room for each output, and its parts."""
+    room = [(s + 255) // 256 * 256 for s in sizes]
+    pool = torch.zeros(sum(room), dtype=torch.uint8, device="cuda")
+    at = np.concatenate([[0], np.cumsum(room)[:-1]]).astype(np.int64)
+    return pool, [pool[a:a + s] for a, s in zip(at.tolist(), sizes)]
+
+
+def _value_pools(xs):
+    """Like _pool, for decompressed values."""
+    pool, parts = _pool([x.numel() * x.element_size() for x in xs])
+    return pool, [p.view(x.dtype) for p, x in zip(parts, xs)]
+
+
+def _bounds(xs):
+    return [C.compress_bound(x.numel(), x.dtype) for x in xs]
+
+
+def prepare(case, seed):
+    op = case["op"]
+    xs = _arrays(case, seed)
+    torch.cuda.synchronize()
+    st = {"op": op}
+    if op.startswith("host"):
+        c = st["codec"] = _codec()
+        x = xs[0].cpu().pin_memory()
+        st["x"] = x
+        st["out"] = torch.zeros(C.compress_bound(x.numel(), x.dtype), dtype=torch.uint8, pin_memory=True)
+        if op == "host_decompress":
+            st["stream"] = c.compress_host(x).clone().pin_memory()
+            st["out"] = torch.zeros(x.numel(), dtype=x.dtype, pin_memory=True)
+        return st
+    if op == "roundtrip":
+        st["codec"] = _codec(False)
+        st["xs"] = xs
+        st["bufs"] = [torch.zeros(b, dtype=torch.uint8, device="cuda") for b in _bounds(xs)]
+        st["ys"] = [torch.zeros_like(x) for x in xs]
+        torch.cuda.synchronize()
+        return st
+    c = st["codec"] = _codec()
+    if op in ("compress", "decompress"):
+        out = torch.zeros(_bounds(xs)[0], dtype=torch.uint8, device="cuda")
+        torch.cuda.synchronize()
+        if op == "compress":
+            st["x"], st["out"] = xs[0], out
+        else:
+            st["stream"] = c.compress(xs[0], out=out).clone()
+            st["out"] = torch.zeros_like(xs[0])
+            torch.cuda.synchronize()
+        return st
+    pool, outs = _pool(_bounds(xs))
+    torch.cuda.synchronize()
+    if op.endswith("decompress"):
+        st["streams"] = c.compress_batch(xs, outs)
+        st["spool"] = pool
+        st["counts"], st["dtypes"] = [x.numel() for x in xs], [x.dtype for x in xs]
+        st["pool"], st["outs"] = _value_pools(xs)
+        torch.cuda.synchronize()
+        if op == "plan_decompress":
+            st["plan"] = c.plan_decompress(st["streams"], st["counts"], st["dtypes"], st["outs"])
+    else:
+        st["xs"], st["pool"], st["outs"] = xs, pool, outs
+        if op == "plan_compress":
+            st["plan"] = c.plan_compress(xs, outs)
+    return st
+
+
+def run(st):
+    """One pass.  A compression's output is its whole buffer (zeros past the
+    stream) and the stream's length."""
+    op, c = st["op"], st["codec"]
+    if op == "compress":
+        return st["out"], c.compress(st["x"], out=st["out"]).numel()
+    if op == "decompress":
+        return c.decompress(st["stream"], out=st["out"])
+    if op == "roundtrip":
+        lens = []
+        for x, b, y in zip(st["xs"], st["bufs"], st["ys"]):
+            lens.append(c.compress_async(x, b))
+            c.decompress_n_async(b, x.numel(), x.dtype, y)
+        c.sync()
+        return st["bufs"], st["ys"], np.array([n.value for n in lens])
+    if op == "batch_compress":
+        got = c.compress_batch(st["xs"], st["outs"])
+        return st["pool"], np.array([g.numel() for g in got])
+    if op == "batch_decompress":
+        c.decompress_batch(st["streams"], st["counts"], st["dtypes"], st["outs"])
+        return st["pool"]
+    if op.startswith("plan"):
+        st["plan"].run(fetch=False)
+        return st["pool"]
+    if op == "host_compress":
+        return st["out"], c.compress_host(st["x"], out=st["out"]).numel()
+    return c.decompress_host(st["stream"], out=st["out"])
+
+
+def work(case):
+    if case["data"] == "series":
+        values = case["count"] * _mean_series() * (0.6 * 8 + 0.4 * 4)
+        return {"bytes": values * (1 + RATIO_SERIES), "flops": 0}
+    size = 8 if case["dtype"] == "f64" else 4
+    raw = case["n"] * case["count"] * size
+    stream = 32 + raw * RATIO[case["data"], case["dtype"]]
+    # a round trip reads and writes the values and the stream once each
+    return {"bytes": (raw + stream) * (2 if case["op"] == "roundtrip" else 1), "flops": 0}
+
+
+def exact(case, seed):
+    """The values a decompression gives back (the codec is lossless); a
+    compressed stream is bytes and has no 64-bit counterpart."""
+    op = case["op"]
+    if op == "roundtrip":
+        xs = _arrays(case, seed)
+        return [None] * len(xs), [x.to(torch.float64) for x in xs], None
+    if op in ("decompress", "host_decompress"):
+        return _arrays(case, seed)[0].to(torch.float64)
+    return None
