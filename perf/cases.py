@@ -35,9 +35,9 @@ CHUNK = 1025          # values per chunk of the stream format
 SEGMENT = 65536       # values that share a number of decimal places
 SERIES_LO, SERIES_HI = 1024, 369_000
 # stream bytes per input byte of each data kind (by dtype), as measured
-RATIO = {("walk", "f64"): 0.13, ("walk", "f32"): 0.27, ("sensor", "f64"): 0.643, ("sensor", "f32"): 0.80,
-         ("mixed", "f64"): 0.48, ("mixed", "f32"): 0.434}
-RATIO_SERIES = 0.175
+RATIO = {("walk", "f64"): 0.129, ("walk", "f32"): 0.112, ("sensor", "f64"): 0.644, ("sensor", "f32"): 0.50,
+         ("mixed", "f64"): 0.41, ("mixed", "f32"): 0.361}
+RATIO_SERIES = 0.18
 
 
 def listed():
@@ -91,15 +91,13 @@ def _torch_dtype(name):
 
 def _round_places(x, places, dtype):
     """x (float64) to `places` decimals, as the nearest float of the dtype
-    (places: a number, or an integer tensor of one per value)."""
-    if torch.is_tensor(places):  # exact powers, which pow() on the GPU does not promise
-        scale = torch.tensor([10.0 ** k for k in range(7)], dtype=torch.float64, device="cuda")[places]
-    else:
-        scale = 10.0 ** places
+    (places: an integer tensor, one per value or one for all)."""
+    # exact powers from a table on the GPU: pow() there does not promise them,
+    # and a division by a Python number becomes a product with its reciprocal
+    scale = torch.tensor([10.0 ** k for k in range(7)], dtype=torch.float64, device="cuda")[places]
     if dtype == torch.float64:
         return torch.round(x * scale) / scale + 0.0
-    scale32 = scale.to(torch.float32) if torch.is_tensor(scale) else scale
-    return torch.round(x * scale).to(torch.float32) / scale32 + 0.0
+    return torch.round(x * scale).to(torch.float32) / scale.to(torch.float32) + 0.0
 
 
 def _segment_places(gen, n, lo, hi):
@@ -123,7 +121,8 @@ def _values(gen, n, data, dtype):
     t = torch.arange(n, device="cuda", dtype=torch.float64)
     if data == "walk":
         sigma = 0.5 if dtype == torch.float64 else 0.02  # a float32 keeps six digits
-        return _round_places(100.0 + _walk(gen, n, sigma), 2, dtype)
+        two = torch.full((n,), 2, device="cuda")
+        return _round_places(100.0 + _walk(gen, n, sigma), two, dtype)
     if data == "sensor":
         x = 100.0 * torch.sin(t * (2 * math.pi / 1e4)) + _walk(gen, n, 0.05)
         v = _round_places(x, _segment_places(gen, n, 1, 6), dtype)
