@@ -72,23 +72,20 @@ typedef enum {
 
 typedef struct falcon_ctx falcon_ctx;
 
-/* How falcon_compress runs on the device (both give the same stream).
- *  TWO_PASS     a size pass computes every chunk's size (Sec. 3.3), a prefix
- *               scan turns the sizes into offsets (Sec. 3.4), and a write
- *               pass recomputes each chunk and writes it at its offset; no
- *               chunk waits for another.  The default.
- *  SINGLE_PASS  one launch: waves take chunks from a work queue (atomic
- *               ticket counters) and each chunk finds its offset with a
- *               decoupled look-back over the sizes published by the chunks
- *               before it (the synchronisation of Sec. 3.4), so the input
- *               is read once. */
+/* How falcon_compress runs on the device.  Both values run the same launch
+ * and give the same stream; they are kept for programs that set one.
+ * Waves take chunks from a work queue (ticket counters), publish each
+ * chunk's size (Sec. 3.3), and write its payload when its offset has
+ * arrived from the workgroup that does the launch's prefix sum (Sec. 3.4);
+ * the input is read once.  The launch makes progress with any number of its
+ * workgroups resident. */
 typedef enum falcon_compress_form {
   FALCON_FORM_TWO_PASS = 0,
   FALCON_FORM_SINGLE_PASS = 1
 } falcon_compress_form;
 
 /* Context options.  A zero-initialised struct, or opts = NULL, gives the
- * defaults: asynchronous device calls, host length pointers, two passes. */
+ * defaults: asynchronous device calls, host length pointers. */
 typedef struct falcon_opts {
   unsigned flags;     /* FALCON_OPT_* */
   int compress_form;  /* falcon_compress_form of falcon_compress */
@@ -115,7 +112,7 @@ falcon_status falcon_create(int device, const falcon_opts* opts, falcon_ctx** ou
  * falcon_sync, writes the host lengths those calls left pending, and
  * returns the first error the device found among them: FALCON_ERR_CORRUPT_STREAM
  * when a decompressed chunk failed a check, FALCON_ERR_DEVICE when a HIP call
- * failed or a single-pass look-back gave up (which a correct run never
+ * failed or a wait for a chunk's offset gave up (which a correct run never
  * does).  FALCON_OK otherwise, also when there was nothing to wait for. */
 falcon_status falcon_sync(falcon_ctx* ctx);
 
@@ -131,7 +128,7 @@ size_t falcon_compress_bound(size_t n, falcon_dtype dt);
 /* Compresses n values at d_in (device) into d_out (device, out_cap bytes).
  * Sec. 3.2-3.5 and Alg. 3: per-chunk integer conversion and adaptive
  * bit-plane encoding, the chunks packed by a prefix sum of their sizes
- * (Sec. 3.4), in the context's falcon_compress_form.  Asynchronous: *out_len
+ * (Sec. 3.4), in one launch.  Asynchronous: *out_len
  * receives the stream length at falcon_sync (a host size_t), or in stream
  * order with FALCON_OPT_DEVICE_LENGTHS (a device size_t); the stream header
  * at d_out + 24 also holds the payload byte count once the work is done.
@@ -142,7 +139,7 @@ falcon_status falcon_compress(falcon_ctx* ctx, const void* d_in, size_t n, falco
 
 /* For callers that cannot allocate memory (code under HIP graph capture,
  * tight serving loops, harnesses that forbid hipMalloc): falcon_compress
- * (two passes, FALCON_OPT_DEVICE_LENGTHS semantics) without a context and
+ * (FALCON_OPT_DEVICE_LENGTHS semantics; two passes over the input) without a context and
  * without any allocation.  Its scratch is a fixed array of about 14 MiB in
  * the library's device code; every GPU the library runs on holds its own
  * copy until the process ends.  The device is the current HIP device, and
@@ -305,16 +302,13 @@ typedef enum { FALCON_OP_COMPRESS = 0, FALCON_OP_DECOMPRESS = 1 } falcon_op;
 
 /* Plan flags: FALCON_PLAN_TUNE times every launch geometry candidate on the
  * plan's own series and keeps the fastest (compression: launch form split /
- * mixed x 8 or 16 waves per workgroup x full or half grid x two passes with
- * static striding or the single pass with its work queue; decompression:
+ * mixed x 4 or 8 waves per workgroup x full or half grid; decompression:
  * form x grid), and records the choice in the context by shape class
  * (operation, dtypes present, log2 of the chunk count, log2 of the series
  * count): a later tuned plan of the same class takes the recorded geometry
  * without timing.  FALCON_PLAN_GRAPH records the plan's launches as one HIP
- * graph replayed by falcon_plan_run.  FALCON_PLAN_SINGLE_PASS makes an
- * untuned compression plan run the single-pass form (the tuner decides by
- * itself).  The one-shot batch calls compress in the context's
- * falcon_compress_form. */
+ * graph replayed by falcon_plan_run.  FALCON_PLAN_SINGLE_PASS is accepted and
+ * changes nothing: every compression plan runs in one pass. */
 enum { FALCON_PLAN_TUNE = 1, FALCON_PLAN_GRAPH = 2, FALCON_PLAN_SINGLE_PASS = 4 };
 
 typedef struct falcon_plan falcon_plan;
@@ -328,7 +322,7 @@ typedef struct falcon_plan_info {
   float default_ms;     /* autotuner: time of the default geometry */
   int graph;            /* 1 if runs replay a HIP graph */
   uint64_t total_chunks;
-  int form;             /* compression: 0 two passes, 1 single pass (work queue; falcon_compress_form) */
+  int form;             /* compression: 1 (one pass, work queue); decompression: 0 */
   int from_cache;       /* 1 if the geometry came from the context's record of an earlier plan of the
                            same shape class instead of timing */
 } falcon_plan_info;
@@ -345,9 +339,8 @@ falcon_status falcon_compress_each(falcon_ctx* ctx, falcon_series* s, size_t cou
 falcon_status falcon_decompress_each(falcon_ctx* ctx, falcon_series* s, size_t count, void* stream);
 
 /* Compresses count series in one launch sequence (no tuning, no graph):
- * every chunk of every series is a work item of the same size pass, one
- * scan turns the sizes of all series into offsets (Sec. 3.4, each series
- * relative to its first chunk), and the write pass places every chunk.
+ * every chunk of every series of a dtype is a work item of one launch, whose
+ * prefix sum starts each series' offsets at 0 (Sec. 3.4).
  * Sets each s[i].out_len.  Series are checked on the host first: a bad descriptor
  * returns FALCON_ERR_INVALID_ARG / FALCON_ERR_BUFFER_TOO_SMALL before any
  * launch.  Synchronous. */
@@ -453,20 +446,20 @@ void falcon_server_destroy(falcon_server* s);
 falcon_status falcon_stream_info(const void* h_hdr, size_t len, size_t* n, falcon_dtype* dt);
 
 /* Device time in milliseconds of the last falcon_compress /
- * falcon_compress_variant (all its launches: size pass, scan, write pass; or
- * the single-pass launch and the clearing of its counters) or
- * falcon_decompress / falcon_decompress_n (the scan of the size array and
- * the decoding kernel), measured with HIP events recorded on the launch
- * stream; waits for that call's work.  Intended for roofline accounting;
+ * falcon_compress_variant or falcon_decompress / falcon_decompress_n, all its
+ * launches together; waits for that call's work.  falcon_compress is timed by
+ * stamps of the device's clock that its launch leaves, the others by HIP
+ * events recorded on the launch stream.  Intended for roofline accounting;
  * FALCON_ERR_INVALID_ARG if no call has run yet. */
 falcon_status falcon_last_kernel_ms(falcon_ctx* ctx, float* ms);
 
-/* The stages of that call separately, ms[0..2]: two-pass compression: size
- * pass, scan, write pass; single-pass compression: the whole launch, 0, 0;
- * decompression: 0, scan, decoding kernel. */
+/* The stages of that call separately, ms[0..2].  falcon_compress: until the
+ * last chunk's size was known, until the last offset was, until the launch's
+ * end (most payloads are written during the first); falcon_compress_variant:
+ * size pass, scan, write pass; decompression: 0, scan, decoding kernel. */
 falcon_status falcon_last_stage_ms(falcon_ctx* ctx, float* ms);
 
-/* The context keeps the events of its last FALCON_TIMED_CALLS timed calls
+/* The context keeps the times of its last FALCON_TIMED_CALLS timed calls
  * (falcon_compress, falcon_compress_variant, falcon_decompress,
  * falcon_decompress_n), so that a caller who enqueues many asynchronous
  * calls and synchronises once can still read each call's stages. */

@@ -192,7 +192,8 @@ class Codec:
     blocking=True (the default here) makes every device call wait for its
     work and report its own errors, as the methods below expect; with
     blocking=False the *_async methods enqueue and sync() completes them.
-    form selects how compression runs ("two_pass" or "single_pass")."""
+    form ("two_pass" or "single_pass") is kept for programs that set it; both
+    run the same launch."""
 
     def __init__(self, device: int | torch.device = 0, blocking: bool = True, form: str = "two_pass",
                  device_lengths: bool = False):
@@ -219,7 +220,7 @@ class Codec:
             pass
 
     def last_kernel_ms(self) -> float:
-        """Duration of the last kernel this codec launched (HIP events)."""
+        """Device time of the last timed call (falcon_last_kernel_ms)."""
         ms = ctypes.c_float()
         st = lib().falcon_last_kernel_ms(self._ctx, ctypes.byref(ms))
         if st != 0:
@@ -227,8 +228,9 @@ class Codec:
         return ms.value
 
     def last_stage_ms(self) -> list:
-        """Stages of the last call: [size pass, scan, write pass] for
-        compression, [0, scan, decoding kernel] for decompression."""
+        """Stages of the last call (falcon_last_stage_ms): [to the last size,
+        to the last offset, to the end] for compression, [0, scan, decoding
+        kernel] for decompression."""
         ms = (ctypes.c_float * 3)()
         st = lib().falcon_last_stage_ms(self._ctx, ms)
         if st != 0:

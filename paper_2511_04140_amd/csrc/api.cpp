@@ -30,13 +30,13 @@ void write_header(uint8_t* h, falcon_dtype dt, uint64_t n, uint64_t payload) {
 
 falcon_status lane_init(Lane& l) {
   if (hipStreamCreateWithFlags(&l.stream, hipStreamNonBlocking) != hipSuccess ||
-      hipMalloc(&l.ctl, 64) != hipSuccess || hipMemset(l.ctl, 0, 64) != hipSuccess ||
-      hipMalloc(&l.qctr, 8 * kQueueGroups * kQueueStride) != hipSuccess ||
+      hipHostMalloc(&l.ctl, 64, hipHostMallocDefault) != hipSuccess ||
       hipHostMalloc(&l.stage, kStageBytes, hipHostMallocDefault) != hipSuccess) {
     lane_free(l);
     return FALCON_ERR_DEVICE;
   }
   memset(l.stage, 0, kStageBytes);
+  memset(l.ctl, 0, 64);
   return FALCON_OK;
 }
 
@@ -46,9 +46,8 @@ void lane_free(Lane& l) {
   if (l.tiles) (void)hipFree(l.tiles);
   if (l.meta) (void)hipFree(l.meta);
   if (l.gsizes) (void)hipFree(l.gsizes);
-  if (l.status) (void)hipFree(l.status);
-  if (l.qctr) (void)hipFree(l.qctr);
-  if (l.ctl) (void)hipFree(l.ctl);
+  queue_free(l.q);
+  if (l.ctl) (void)hipHostFree(l.ctl);
   if (l.stage) (void)hipHostFree(l.stage);
   if (l.stream) (void)hipStreamDestroy(l.stream);
   l = Lane();
@@ -93,40 +92,54 @@ int grid_for(int max_grid, uint64_t nchunks, int waves_per_block) {
 
 }  // namespace
 
-// Makes the lane's status array hold nchunks words, picks the tag of the
-// next single-pass launch and clears the ticket counters.  The status array
-// is cleared when it is (re)allocated and whenever the 16-bit tag wraps, so
-// a word left by an earlier launch never carries the current tag.
-falcon_status prepare_queue(Lane& l, uint64_t nchunks, hipStream_t s) {
-  const size_t old_cap = l.status_cap;
-  const uint64_t* old = l.status;
-  falcon_status st = grow_raw(&l.status, &l.status_cap, nchunks, s);
+falcon_status queue_prepare(Queue& q, uint64_t nchunks, hipStream_t s) {
+  if (q.ctr && nchunks + kQueueSlack <= q.cap && !q.dirty) return FALCON_OK;
+  q.dirty = true;  // until everything below has worked
+  if (!q.ctr && hipMalloc(&q.ctr, 8 * kQueueWords) != hipSuccess) return FALCON_ERR_OUT_OF_MEMORY;
+  const size_t had = q.cap;
+  size_t cap = had;
+  q.cap = 0;
+  falcon_status st = grow_raw(&q.size, &cap, nchunks + kQueueSlack, s);
   if (st != FALCON_OK) return st;
-  l.qtag = (l.qtag + 1) & 0xFFFFu;
-  if (l.status != old || l.status_cap != old_cap || l.qtag == 0) {
-    if (l.qtag == 0) l.qtag = 1;
-    if ((st = dev_err(launch_fill_u64(l.status, l.status_cap, 0, s))) != FALCON_OK) return st;
-  }
-  return dev_err(launch_fill_u64(l.qctr, (size_t)kQueueGroups * kQueueStride, 0, s));
+  cap = had;
+  if ((st = grow_raw(&q.off, &cap, nchunks + kQueueSlack, s)) != FALCON_OK) return st;
+  if ((st = dev_err(launch_fill_u64(q.ctr, kQueueWords, 0, s))) != FALCON_OK ||
+      (st = dev_err(launch_fill_u64(reinterpret_cast<uint64_t*>(q.size), cap / 2, 0, s))) != FALCON_OK ||
+      (st = dev_err(launch_fill_u64(q.off, cap, 0, s))) != FALCON_OK)
+    return st;
+  q.cap = cap;
+  q.dirty = false;
+  return FALCON_OK;
 }
 
-// Moves the timing ring to a fresh slot for a timed call and returns its
-// four events; the slot counts as complete once the call has recorded all
-// of them.
-static hipEvent_t* begin_timed(falcon_ctx* ctx) {
+void queue_free(Queue& q) {
+  if (q.ctr) (void)hipFree(q.ctr);
+  if (q.size) (void)hipFree(q.size);
+  if (q.off) (void)hipFree(q.off);
+  q = Queue();
+}
+
+// Up to one 4-wave workgroup per CU (1,024 chunks), small workgroups spread
+// the chunks over more CUs; beyond that, 8-wave ones draw from 8 ticket
+// counters and scan twice as many sizes a round.  Decimal float64 data, 4
+// against 8 waves: 98 chunks 15.7 / 17.3 us, 1,024 chunks 20.2 / 20.6, 2,047
+// chunks 26.5 / 25.0, 16,369 chunks 87 / 70.
+int queue_waves(uint64_t nchunks) { return nchunks <= 1024 ? 4 : 8; }
+
+// Moves the timing ring to a fresh slot for a timed call; the slot counts
+// once the call sets its kind, when everything is enqueued.
+static void begin_timed(falcon_ctx* ctx) {
   ctx->ev_slot = (ctx->ev_slot + 1) % FALCON_TIMED_CALLS;
-  ctx->ev_ok[ctx->ev_slot] = false;
-  return ctx->ev[ctx->ev_slot];
+  ctx->ev_kind[ctx->ev_slot] = falcon_ctx::kNotTimed;
 }
 
-// Compression, in one of two forms.  Two passes (the default, and the
-// only form of the ablation variants): a size pass, a scan of the chunk
-// sizes into offsets, a write pass that redoes a4-a7 and writes each chunk
-// at its offset.  Single pass: one launch in which waves take chunks from
-// a work queue and find their offsets with a decoupled look-back (see
-// codec_kernels.hpp).  Both give the same stream.
+// Compression: one launch in which waves take chunks from a work queue and
+// one workgroup turns their sizes into offsets (k_compress_queue).  The ablation
+// variants run in two passes: a size pass, a scan of the chunk sizes into
+// offsets, a write pass that redoes a4-a7 and writes each chunk at its
+// offset.
 falcon_status enqueue_compress(falcon_ctx* ctx, Lane& l, const void* d_in, uint64_t n, falcon_dtype dt, void* d_out,
-                               hipStream_t s, bool timed, int variant, int form, uint64_t* d_len) {
+                               hipStream_t s, bool timed, int variant, uint64_t* d_len) {
   const uint64_t nc = chunks_of(n);
   falcon_status st = FALCON_OK;
   CompressArgs a{};
@@ -140,54 +153,52 @@ falcon_status enqueue_compress(falcon_ctx* ctx, Lane& l, const void* d_in, uint6
   a.nseries = 1;
   a.total_chunks = nc;
   a.lens = d_len;
-  a.relative = 0;
-  hipEvent_t* ev = timed ? begin_timed(ctx) : nullptr;
-  auto mark = [&](int i) { return timed ? dev_err(hipEventRecord(ev[i], s)) : FALCON_OK; };
-  if (variant == 0 && form == FALCON_FORM_SINGLE_PASS) {
-    if ((st = mark(0)) != FALCON_OK || (st = prepare_queue(l, nc ? nc : 1, s)) != FALCON_OK) return st;
-    const int nw = kCompressWaves;
-    const int grid = grid_for(max_grid_q(ctx, dt, nw), nc, nw);
-    a.total_waves = (uint32_t)(grid * nw);
-    a.status = l.status;
-    a.qctr = l.qctr;
-    a.qgroups = (uint32_t)(grid < kQueueGroups ? grid : kQueueGroups);
+  if (timed) begin_timed(ctx);
+  if (variant == 0) {
+    if ((st = queue_prepare(l.q, nc ? nc : 1, s)) != FALCON_OK) return st;
+    const int nw = queue_waves(nc);
+    a.qctr = l.q.ctr;
+    a.qsize = l.q.size;
+    a.qoff = l.q.off;
     a.ctl = l.ctl;
-    a.qtag = l.qtag;
-    if ((st = dev_err(launch_compress_queue(a, (int)dt, nw, grid, s))) != FALCON_OK) return st;
-    if ((st = mark(1)) != FALCON_OK || (st = mark(2)) != FALCON_OK || (st = mark(3)) != FALCON_OK) return st;
-  } else {
-    st = prepare_launch(l, nc ? nc : 1, scan_tiles(nc) + 1, s);
-    if (st == FALCON_OK) st = grow_raw(&l.meta, &l.meta_cap, nc ? nc : 1, s);
-    if (st == FALCON_OK) st = grow_raw(&l.gsizes, &l.gsizes_cap, nc ? nc : 1, s);
-    if (st != FALCON_OK) return st;
-    a.meta = l.meta;
-    a.gsizes = l.gsizes;
-    a.offsets = l.offsets;
-    const int nw = variant ? kVariantWaves : compress_waves((int)dt);
-    const int g1 = grid_for(variant ? ctx->grid_v[dt][variant][1] : max_grid_c(ctx, dt, 1, nw), nc, nw);
-    const int g2 = grid_for(variant ? ctx->grid_v[dt][variant][2] : max_grid_c(ctx, dt, 2, nw), nc, nw);
-    auto launch = [&](int pass, int grid) {
-      a.total_waves = (uint32_t)(grid * nw);
-      return dev_err(variant ? launch_compress_variant(a, (int)dt, variant, pass, grid, s)
-                             : launch_compress(a, (int)dt, pass, nw, grid, s));
-    };
-    if ((st = mark(0)) != FALCON_OK) return st;
-    if (nc && (st = launch(1, g1)) != FALCON_OK) return st;
-    if ((st = mark(1)) != FALCON_OK) return st;
-    if (nc && (st = dev_err(launch_scan_sizes(l.gsizes, nc, 0, ~0u, ~0ull, l.tiles, l.offsets, l.ctl, l.epoch,
-                                              s))) != FALCON_OK)
+    a.times = timed ? ctx->times + (size_t)ctx->ev_slot * kTimeWords : nullptr;
+    // one workgroup scans
+    if ((st = dev_err(launch_compress_queue(a, (int)dt, nw, grid_for(max_grid_q(ctx, dt, nw), nc + nw, nw), s))) !=
+        FALCON_OK)
       return st;
-    if ((st = mark(2)) != FALCON_OK) return st;
-    if ((st = launch(2, g2)) != FALCON_OK) return st;
-    if ((st = mark(3)) != FALCON_OK) return st;
+    if (timed) ctx->ev_kind[ctx->ev_slot] = falcon_ctx::kStamps;
+    return FALCON_OK;
   }
-  if (timed) ctx->ev_ok[ctx->ev_slot] = true;
+  hipEvent_t* ev = ctx->ev[ctx->ev_slot];
+  auto mark = [&](int i) { return timed ? dev_err(hipEventRecord(ev[i], s)) : FALCON_OK; };
+  st = prepare_launch(l, nc ? nc : 1, scan_tiles(nc) + 1, s);
+  if (st == FALCON_OK) st = grow_raw(&l.meta, &l.meta_cap, nc ? nc : 1, s);
+  if (st == FALCON_OK) st = grow_raw(&l.gsizes, &l.gsizes_cap, nc ? nc : 1, s);
+  if (st != FALCON_OK) return st;
+  a.meta = l.meta;
+  a.gsizes = l.gsizes;
+  a.offsets = l.offsets;
+  const int nw = kVariantWaves;
+  auto launch = [&](int pass) {
+    const int grid = grid_for(ctx->grid_v[dt][variant][pass], nc, nw);
+    a.total_waves = (uint32_t)(grid * nw);
+    return dev_err(launch_compress_variant(a, (int)dt, variant, pass, grid, s));
+  };
+  if ((st = mark(0)) != FALCON_OK) return st;
+  if (nc && (st = launch(1)) != FALCON_OK) return st;
+  if ((st = mark(1)) != FALCON_OK) return st;
+  if (nc && (st = dev_err(launch_scan_sizes(l.gsizes, nc, 0, ~0u, ~0ull, l.tiles, l.offsets, l.ctl, l.epoch, s))) !=
+                FALCON_OK)
+    return st;
+  if ((st = mark(2)) != FALCON_OK) return st;
+  if ((st = launch(2)) != FALCON_OK) return st;
+  if ((st = mark(3)) != FALCON_OK) return st;
+  if (timed) ctx->ev_kind[ctx->ev_slot] = falcon_ctx::kEvents;
   return FALCON_OK;
 }
 
 falcon_status enqueue_decompress(falcon_ctx* ctx, Lane& l, const uint8_t* d_in, uint64_t in_len, uint64_t n,
-                                 falcon_dtype dt, uint64_t payload, void* d_out, hipStream_t s, bool timed,
-                                 bool copy_error) {
+                                 falcon_dtype dt, uint64_t payload, void* d_out, hipStream_t s, bool timed) {
   const uint64_t nc = chunks_of(n);
   falcon_status st = prepare_launch(l, nc, scan_tiles(nc) + 1, s);
   if (st != FALCON_OK) return st;
@@ -196,7 +207,8 @@ falcon_status enqueue_decompress(falcon_ctx* ctx, Lane& l, const uint8_t* d_in, 
   // count when the host knows it; otherwise the last chunk's check does that)
   const uint32_t lo = dt == FALCON_FLOAT64 ? 11u : 7u;
   const uint32_t hi = (uint32_t)max_chunk_bytes(dt);
-  hipEvent_t* ev = timed ? begin_timed(ctx) : nullptr;
+  if (timed) begin_timed(ctx);
+  hipEvent_t* ev = ctx->ev[ctx->ev_slot];
   auto mark = [&](int i) { return timed ? dev_err(hipEventRecord(ev[i], s)) : FALCON_OK; };
   if ((st = mark(0)) != FALCON_OK || (st = mark(1)) != FALCON_OK) return st;
   if ((st = dev_err(launch_scan_sizes(reinterpret_cast<const uint32_t*>(d_in + 32), nc, lo, hi,
@@ -223,9 +235,8 @@ falcon_status enqueue_decompress(falcon_ctx* ctx, Lane& l, const uint8_t* d_in, 
   if ((st = mark(2)) != FALCON_OK) return st;
   if ((st = dev_err(launch_decompress(a, (int)dt, grid, s))) != FALCON_OK) return st;
   if ((st = mark(3)) != FALCON_OK) return st;
-  if (timed) ctx->ev_ok[ctx->ev_slot] = true;
-  if (!copy_error) return FALCON_OK;
-  return dev_err(hipMemcpyAsync(l.stage + 32, &l.ctl->error, 4, hipMemcpyDeviceToHost, s));
+  if (timed) ctx->ev_kind[ctx->ev_slot] = falcon_ctx::kEvents;
+  return FALCON_OK;
 }
 
 namespace {
@@ -319,23 +330,24 @@ falcon_status falcon_create(int device, const falcon_opts* opts, falcon_ctx** ou
   if (!ctx) return FALCON_ERR_OUT_OF_MEMORY;
   ctx->device = device;
   ctx->opt_flags = flags;
-  ctx->compress_form = form;
   bool ok = lane_init(ctx->main) == FALCON_OK &&
             hipEventCreateWithFlags(&ctx->ev_done, hipEventDisableTiming) == hipSuccess;
   for (int c = 0; ok && c < FALCON_TIMED_CALLS; ++c)
     for (int i = 0; ok && i < 4; ++i) ok = hipEventCreate(&ctx->ev[c][i]) == hipSuccess;
+  constexpr size_t kTimeBytes = (size_t)kTimeWords * 8;
+  ok = ok && hipMalloc(&ctx->times, FALCON_TIMED_CALLS * kTimeBytes) == hipSuccess &&
+       launch_fill_u64(ctx->times, (size_t)FALCON_TIMED_CALLS * kTimeWords, 0, ctx->main.stream) == hipSuccess &&
+       hipStreamSynchronize(ctx->main.stream) == hipSuccess &&
+       hipHostMalloc(&ctx->times_host, kTimeBytes, hipHostMallocDefault) == hipSuccess &&
+       hipDeviceGetAttribute(&ctx->tick_khz, hipDeviceAttributeWallClockRate, device) == hipSuccess;
   if (!ok) {
     falcon_destroy(ctx);
     return FALCON_ERR_DEVICE;
   }
   for (int form_ = 1; form_ <= 3; ++form_) {
-    for (int pass = 1; pass <= 2; ++pass) {
-      ctx->grid_c[form_][pass][0] = max_grid_compress(device, form_, pass, 8);
-      ctx->grid_c[form_][pass][1] = max_grid_compress(device, form_, pass, 16);
-    }
     ctx->grid_d[form_] = max_grid_decompress(device, form_);
-    ctx->grid_q[form_][0] = max_grid_compress_queue(device, form_, 8);
-    ctx->grid_q[form_][1] = max_grid_compress_queue(device, form_, 16);
+    ctx->grid_q[form_][0] = max_grid_compress_queue(device, form_, 4);
+    ctx->grid_q[form_][1] = max_grid_compress_queue(device, form_, 8);
   }
   for (int f = 1; f <= 2; ++f)
     for (int v = 1; v <= 3; ++v)
@@ -376,20 +388,15 @@ falcon_status falcon_sync(falcon_ctx* ctx) {
     const size_t k = np - b * kLenBlock < kLenBlock ? np - b * kLenBlock : kLenBlock;
     st = dev_err(hipMemcpyAsync(ctx->len_host + b * kLenBlock, ctx->len_blocks[b], k * 8, hipMemcpyDeviceToHost, s));
   }
-  if (st == FALCON_OK) st = dev_err(hipMemcpyAsync(l.stage + 32, l.ctl, 8, hipMemcpyDeviceToHost, s));
   const falcon_status sy = dev_err(hipStreamSynchronize(s));
   if (st == FALCON_OK) st = sy;
   if (st == FALCON_OK) {
     for (const auto& p : ctx->pending) *p.dst = (size_t)ctx->len_host[p.slot];
     // the decompression error word holds the epoch of the last launch whose
     // chunk failed: a launch since the last sync has a larger one
-    const uint32_t err = rd32(l.stage + 32);
+    const uint32_t err = l.ctl->error;
     if (err != 0 && err > ctx->sync_epoch && err <= l.epoch) st = FALCON_ERR_CORRUPT_STREAM;
-    if (rd32(l.stage + 36) != 0) {
-      (void)launch_fill_u64(reinterpret_cast<uint64_t*>(l.ctl), 1, 0, s);
-      (void)hipStreamSynchronize(s);
-      st = FALCON_ERR_DEVICE;
-    }
+    if (compress_failed(l)) st = FALCON_ERR_DEVICE;
   }
   ctx->pending.clear();
   ctx->sync_epoch = l.epoch;
@@ -411,6 +418,8 @@ void falcon_destroy(falcon_ctx* ctx) {
   if (ctx->ev_done) (void)hipEventDestroy(ctx->ev_done);
   for (uint64_t* b : ctx->len_blocks) (void)hipFree(b);
   if (ctx->len_host) (void)hipHostFree(ctx->len_host);
+  if (ctx->times) (void)hipFree(ctx->times);
+  if (ctx->times_host) (void)hipHostFree(ctx->times_host);
   delete ctx;
 }
 
@@ -458,7 +467,7 @@ falcon_status falcon_compress_variant(falcon_ctx* ctx, const void* d_in, size_t 
   else if (n) st = pending_length(ctx, out_len, &d_len);
   else *out_len = 32;
   if (st == FALCON_OK)
-    st = enqueue_compress(ctx, ctx->main, d_in, n, dt, d_out, s, true, (int)v, ctx->compress_form, d_len);
+    st = enqueue_compress(ctx, ctx->main, d_in, n, dt, d_out, s, true, (int)v, d_len);
   if (st == FALCON_OK && dev_len && n == 0) st = empty_length(d_len, s);
   return end_call(ctx, s, st);
 }
@@ -477,7 +486,7 @@ falcon_status falcon_decompress_n(falcon_ctx* ctx, const void* d_in, size_t in_l
   if (st != FALCON_OK) return st;
   // an empty stream has no chunk to check its header: nothing to launch
   if (n) st = enqueue_decompress(ctx, ctx->main, static_cast<const uint8_t*>(d_in), in_len, n, dt,
-                                 kPayloadFromHeader, d_out, s, true, false);
+                                 kPayloadFromHeader, d_out, s, true);
   return end_call(ctx, s, st);
 }
 
@@ -506,7 +515,7 @@ falcon_status falcon_decompress(falcon_ctx* ctx, const void* d_in, size_t in_len
   if (out_cap_bytes / es < n) return end_call(ctx, s, FALCON_ERR_BUFFER_TOO_SMALL);
   if (n && (!d_out || ((uintptr_t)d_out % es))) return end_call(ctx, s, FALCON_ERR_INVALID_ARG);
   if (n)
-    st = enqueue_decompress(ctx, l, static_cast<const uint8_t*>(d_in), in_len, n, dt, payload, d_out, s, true, false);
+    st = enqueue_decompress(ctx, l, static_cast<const uint8_t*>(d_in), in_len, n, dt, payload, d_out, s, true);
   return end_call(ctx, s, st);
 }
 
@@ -527,7 +536,7 @@ falcon_status falcon_compress_each(falcon_ctx* ctx, falcon_series* ss, size_t co
     st = pending_length(ctx, &ss[i].out_len, &dl[i]);
     if (st == FALCON_OK)
       st = enqueue_compress(ctx, ctx->main, ss[i].d_in, ss[i].n, ss[i].dtype, ss[i].d_out, s, false, 0,
-                            ctx->compress_form, dl[i]);
+                            dl[i]);
     if (st == FALCON_OK && ss[i].n == 0) st = empty_length(dl[i], s);
   }
   st = end_call(ctx, s, st);
@@ -548,7 +557,7 @@ falcon_status falcon_decompress_each(falcon_ctx* ctx, falcon_series* ss, size_t 
   for (size_t i = 0; i < count && st == FALCON_OK; ++i) {
     if (ss[i].n)
       st = enqueue_decompress(ctx, ctx->main, static_cast<const uint8_t*>(ss[i].d_in), ss[i].in_len, ss[i].n,
-                              ss[i].dtype, kPayloadFromHeader, ss[i].d_out, s, false, false);
+                              ss[i].dtype, kPayloadFromHeader, ss[i].d_out, s, false);
     ss[i].out_len = ss[i].n;
   }
   st = end_call(ctx, s, st);
@@ -559,11 +568,28 @@ falcon_status falcon_decompress_each(falcon_ctx* ctx, falcon_series* ss, size_t 
 falcon_status falcon_call_stage_ms(falcon_ctx* ctx, unsigned back, float* ms) {
   if (!ctx || !ms || back >= FALCON_TIMED_CALLS) return FALCON_ERR_INVALID_ARG;
   const int slot = (ctx->ev_slot + FALCON_TIMED_CALLS - (int)back) % FALCON_TIMED_CALLS;
-  if (!ctx->ev_ok[slot]) return FALCON_ERR_INVALID_ARG;
-  hipEvent_t* ev = ctx->ev[slot];
-  if (hipEventSynchronize(ev[3]) != hipSuccess) return FALCON_ERR_DEVICE;
-  for (int i = 0; i < 3; ++i)
-    if (hipEventElapsedTime(ms + i, ev[i], ev[i + 1]) != hipSuccess) return FALCON_ERR_DEVICE;
+  if (ctx->ev_kind[slot] == falcon_ctx::kNotTimed) return FALCON_ERR_INVALID_ARG;
+  if (ctx->ev_kind[slot] == falcon_ctx::kEvents) {
+    hipEvent_t* ev = ctx->ev[slot];
+    if (hipEventSynchronize(ev[3]) != hipSuccess) return FALCON_ERR_DEVICE;
+    for (int i = 0; i < 3; ++i)
+      if (hipEventElapsedTime(ms + i, ev[i], ev[i + 1]) != hipSuccess) return FALCON_ERR_DEVICE;
+    return FALCON_OK;
+  }
+  // the call's stream, unless a falcon_sync has waited for it already
+  if (hipSetDevice(ctx->device) != hipSuccess ||
+      (ctx->unsynced && hipStreamSynchronize(ctx->last_stream) != hipSuccess) ||
+      hipMemcpyAsync(ctx->times_host, ctx->times + (size_t)slot * kTimeWords, (size_t)kTimeWords * 8,
+                     hipMemcpyDeviceToHost, ctx->main.stream) != hipSuccess ||
+      hipStreamSynchronize(ctx->main.stream) != hipSuccess)
+    return FALCON_ERR_DEVICE;
+  const uint64_t* w = ctx->times_host;
+  uint64_t end = w[2];
+  for (int i = 1; i <= kTimeEnds; ++i) end = w[kTimeStride * i] > end ? w[kTimeStride * i] : end;
+  const double per_ms = (double)ctx->tick_khz;
+  ms[0] = (float)((double)(w[1] - w[0]) / per_ms);
+  ms[1] = (float)((double)(w[2] - w[1]) / per_ms);
+  ms[2] = (float)((double)(end - w[2]) / per_ms);
   return FALCON_OK;
 }
 

@@ -3,20 +3,18 @@
 //
 // Every chunk of every series gets a launch chunk index t: the float64
 // series come first, then the float32 ones, each series' chunks
-// consecutive.  Waves take chunks by static striding over t; each series'
-// offsets are the scan of all chunk sizes minus the offset of its own first
-// chunk, so series are independent and each output is byte-identical to a
-// one-series call.  Two launch forms exist: split (one launch per dtype,
+// consecutive.  Each series' offsets are counted from its own first chunk, so
+// series are independent and each output is byte-identical to a one-series
+// call.  Two launch forms exist: split (one launch per dtype,
 // each over its own contiguous range of t) and mixed (one launch over all
 // of t, the wave branching on the dtype of the chunk's series).
 //
-// Compression runs in two passes over all series (size pass, one scan of
-// all chunk sizes, write pass; see codec_kernels.hpp), so no chunk waits on
-// another, or, when the autotuner finds it faster, in the single pass with a
-// work queue over all chunks and a look-back that stops at each series'
-// first chunk.  A run never depends on host state beyond its descriptors: the
-// control block is cleared by a fill kernel at the start of a decompression
-// run (no memset nodes in a recorded graph) and the launch epoch is fixed.
+// Compression takes the chunks of all series from one work queue per launch,
+// and its scanning workgroup starts every series' offsets at 0 (see
+// codec_kernels.hpp).  A run never depends on host state beyond its
+// descriptors: the queue's words are clear before and after every launch,
+// the error words are cleared on the host after each run, and the launch
+// epoch is fixed, so a recorded graph can be replayed (no memset nodes).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <string.h>
@@ -57,12 +55,10 @@ falcon_status grow(P** p, size_t* cap, size_t need, size_t elem, bool pinned, hi
   return FALCON_OK;
 }
 
-int grid_of(const falcon_ctx* ctx, const BatchGeom& g, int form, int pass, uint64_t chunks, bool compress) {
-  const int maxg = !compress ? max_grid_d(ctx, form) : g.form ? max_grid_q(ctx, form, g.nw) : max_grid_c(ctx, form, pass, g.nw);
+int grid_of(int maxg, const BatchGeom& g, uint64_t waves, int per) {
   int grid = (int)((int64_t)maxg * g.grid_pct / 100);
   if (grid < 1) grid = 1;
-  const int per = compress ? g.nw : kDecompressWaves;
-  const uint64_t want = (chunks + per - 1) / per;
+  const uint64_t want = (waves + per - 1) / per;
   if (want < (uint64_t)grid) grid = (int)(want ? want : 1);
   return grid;
 }
@@ -142,19 +138,14 @@ falcon_status batch_layout(BatchScratch& b, int op, const falcon_series* s, size
       (r = grow(&b.offsets, &b.offsets_cap, t ? t : 1, 8, false, st)) != FALCON_OK ||
       (r = grow(&b.tiles, &b.tiles_cap, gwords, 8, false, st)) != FALCON_OK ||
       (r = grow(&b.lens, &b.lens_cap, count, 8, false, st)) != FALCON_OK ||
-      (r = grow(&b.h_lens, &b.h_lens_cap, count + 1, 8, true, st)) != FALCON_OK)
+      (r = grow(&b.h_lens, &b.h_lens_cap, count, 8, true, st)) != FALCON_OK)
     return r;
-  if ((r = grow(&b.sizes, &b.sizes_cap, t ? t : 1, 4, false, st)) != FALCON_OK) return r;
-  if (op == FALCON_OP_COMPRESS && (r = grow(&b.meta, &b.meta_cap, t ? t : 1, sizeof(ChunkMeta), false, st)) !=
-                                      FALCON_OK)
+  if (op == FALCON_OP_DECOMPRESS && (r = grow(&b.sizes, &b.sizes_cap, t ? t : 1, 4, false, st)) != FALCON_OK)
     return r;
-  if (op == FALCON_OP_COMPRESS &&
-      (r = grow(&b.status, &b.status_cap, (size_t)kQueueGroups * kQueueStride + (t ? t : 1), 8, false, st)) !=
-          FALCON_OK)
-    return r;
+  if (op == FALCON_OP_COMPRESS && (r = queue_prepare(b.q, t ? t : 1, st)) != FALCON_OK) return r;
   if (!b.ctl) {
-    if (hipMalloc(&b.ctl, 64) != hipSuccess) return FALCON_ERR_OUT_OF_MEMORY;
-    if (launch_fill_u64(reinterpret_cast<uint64_t*>(b.ctl), 8, 0, st) != hipSuccess) return FALCON_ERR_DEVICE;
+    if (hipHostMalloc(&b.ctl, 64, hipHostMallocDefault) != hipSuccess) return FALCON_ERR_OUT_OF_MEMORY;
+    memset(b.ctl, 0, 64);
   }
   return FALCON_OK;
 }
@@ -175,63 +166,27 @@ falcon_status batch_enqueue(const falcon_ctx* ctx, BatchScratch& b, const BatchL
     if (L.has32) parts[np++] = {1, L.t64, L.total - L.t64};
   }
   if (L.op == FALCON_OP_COMPRESS) {
-    if (np == 0) parts[np++] = {2, 0, 0};  // only empty series: the last launch writes their headers
+    if (np == 0) parts[np++] = {2, 0, 0};  // only empty series: the launch writes their headers
     CompressArgs a{};
     a.one = L.one_c;
     a.many = static_cast<const CompressSeries*>(b.many);
     a.nseries = (uint32_t)L.count;
     a.lens = b.lens;
-    a.meta = b.meta;
-    a.gsizes = b.sizes;
-    a.offsets = b.offsets;
-    a.relative = 1;
-    if (g.form == 1) {
-      // single pass: a work queue and a per-series look-back; counters,
-      // status words and the error word cleared by fill kernels (a recorded
-      // graph replays them), so every run uses the same tag
-      const size_t nq = (size_t)kQueueGroups * kQueueStride;
-      if ((st = dev_err(launch_fill_u64(b.status, nq + (L.total ? L.total : 1), 0, s))) != FALCON_OK ||
-          (st = dev_err(launch_fill_u64(reinterpret_cast<uint64_t*>(b.ctl), 1, 0, s))) != FALCON_OK)
-        return st;
-      a.qctr = b.status;
-      a.status = b.status + nq;
-      a.ctl = b.ctl;
-      a.qtag = kBatchEpoch;
-      for (int i = 0; i < np; ++i) {
-        // launches run one after the other on s: each starts with cleared counters
-        if (i > 0 && (st = dev_err(launch_fill_u64(b.status, nq, 0, s))) != FALCON_OK) return st;
-        a.total_chunks = parts[i].chunks;
-        a.t0 = parts[i].t0;
-        const int grid = grid_of(ctx, g, parts[i].form, 0, parts[i].chunks, true);
-        a.total_waves = (uint32_t)(grid * g.nw);
-        a.qgroups = (uint32_t)(grid < kQueueGroups ? grid : kQueueGroups);
-        if ((st = dev_err(launch_compress_queue(a, parts[i].form, g.nw, grid, s))) != FALCON_OK) return st;
-      }
-      if ((st = dev_err(hipMemcpyAsync(b.h_lens, b.lens, L.count * 8, hipMemcpyDeviceToHost, s))) != FALCON_OK)
-        return st;
-      return dev_err(hipMemcpyAsync(b.h_lens + L.count, b.ctl, 8, hipMemcpyDeviceToHost, s));
+    a.qctr = b.q.ctr;
+    a.qsize = b.q.size;
+    a.qoff = b.q.off;
+    a.ctl = b.ctl;
+    // launches run one after the other on s, each leaving the queue's words
+    // clear for the next
+    for (int i = 0; i < np; ++i) {
+      a.total_chunks = parts[i].chunks;
+      a.t0 = parts[i].t0;
+      const int nw = g.nw ? g.nw : queue_waves(parts[i].chunks);
+      const int grid = grid_of(max_grid_q(ctx, parts[i].form, nw), g, parts[i].chunks + nw, nw);
+      if ((st = dev_err(launch_compress_queue(a, parts[i].form, nw, grid, s))) != FALCON_OK) return st;
     }
-    // two passes over all series: sizes, one scan over all chunks, writes
-    for (int pass = 1; pass <= 2; ++pass) {
-      for (int i = 0; i < np; ++i) {
-        if (pass == 1 && parts[i].chunks == 0) continue;
-        a.total_chunks = parts[i].chunks;
-        a.t0 = parts[i].t0;
-        const int grid = grid_of(ctx, g, parts[i].form, pass, parts[i].chunks, true);
-        a.total_waves = (uint32_t)(grid * g.nw);
-        if ((st = dev_err(launch_compress(a, parts[i].form, pass, g.nw, grid, s))) != FALCON_OK) return st;
-      }
-      if (pass == 1 && L.total &&
-          (st = dev_err(launch_scan_sizes(b.sizes, L.total, 0, ~0u, ~0ull, b.tiles, b.offsets, b.ctl, kBatchEpoch,
-                                          s))) != FALCON_OK)
-        return st;
-    }
-    if ((st = dev_err(hipMemcpyAsync(b.h_lens, b.lens, L.count * 8, hipMemcpyDeviceToHost, s))) != FALCON_OK)
-      return st;
-    return dev_err(hipMemcpyAsync(b.h_lens + L.count, b.ctl, 8, hipMemcpyDeviceToHost, s));
+    return dev_err(hipMemcpyAsync(b.h_lens, b.lens, L.count * 8, hipMemcpyDeviceToHost, s));
   }
-  // clear the control block (error word) of decompression
-  if ((st = dev_err(launch_fill_u64(reinterpret_cast<uint64_t*>(b.ctl), 2, 0, s))) != FALCON_OK) return st;
   // decompression: headers and sizes, one scan over all chunks, kernels
   DecompressSeries* many = static_cast<DecompressSeries*>(b.many);
   if ((st = dev_err(launch_batch_dprep(many, (uint32_t)L.count, L.total, b.sizes, b.ctl, kBatchEpoch, s))) !=
@@ -250,20 +205,19 @@ falcon_status batch_enqueue(const falcon_ctx* ctx, BatchScratch& b, const BatchL
     a.ctl = b.ctl;
     a.epoch = kBatchEpoch;
     a.relative = 1;
-    const int grid = grid_of(ctx, g, parts[i].form, 0, parts[i].chunks, false);
+    const int grid = grid_of(max_grid_d(ctx, parts[i].form), g, parts[i].chunks, kDecompressWaves);
     a.total_waves = (uint32_t)(grid * kDecompressWaves);
     if ((st = dev_err(launch_decompress(a, parts[i].form, grid, s))) != FALCON_OK) return st;
   }
-  return dev_err(hipMemcpyAsync(b.h_lens + L.count, &b.ctl->error, 4, hipMemcpyDeviceToHost, s));
+  return FALCON_OK;
 }
 
-falcon_status batch_result(const BatchScratch& b, const BatchLayout& L, const falcon_series* src,
+falcon_status batch_result(BatchScratch& b, const BatchLayout& L, const falcon_series* src,
                            falcon_series* dst) {
-  uint32_t err[2];
-  memcpy(err, b.h_lens + L.count, 8);
-  if (L.op == FALCON_OP_DECOMPRESS && err[0] == kBatchEpoch) return FALCON_ERR_CORRUPT_STREAM;
-  // a single-pass look-back that gave up (never in a correct run)
-  if (L.op == FALCON_OP_COMPRESS && err[1] != 0) return FALCON_ERR_DEVICE;
+  const uint32_t err = b.ctl->error;
+  b.ctl->error = 0;  // for the next run
+  if (L.op == FALCON_OP_DECOMPRESS && err == kBatchEpoch) return FALCON_ERR_CORRUPT_STREAM;
+  if (queue_failed(b.ctl, b.q)) return FALCON_ERR_DEVICE;
   if (dst)
     for (size_t i = 0; i < L.count; ++i) dst[i].out_len = L.op == FALCON_OP_COMPRESS ? b.h_lens[i] : src[i].n;
   return FALCON_OK;
@@ -275,11 +229,10 @@ void batch_free(BatchScratch& b) {
   if (b.offsets) (void)hipFree(b.offsets);
   if (b.tiles) (void)hipFree(b.tiles);
   if (b.sizes) (void)hipFree(b.sizes);
-  if (b.meta) (void)hipFree(b.meta);
-  if (b.ctl) (void)hipFree(b.ctl);
+  if (b.ctl) (void)hipHostFree(b.ctl);
   if (b.lens) (void)hipFree(b.lens);
   if (b.h_lens) (void)hipHostFree(b.h_lens);
-  if (b.status) (void)hipFree(b.status);
+  queue_free(b.q);
   b = BatchScratch();
 }
 
@@ -353,9 +306,9 @@ uint64_t shape_class(const BatchLayout& L) {
 }
 
 // Autotuner: times every candidate geometry on the plan's own series and
-// keeps the fastest.  Compression: launch form (split / mixed) x 16 or 8
-// waves per workgroup x full or half grid x two passes (static striding) or
-// single pass (work queue); decompression: launch form x grid.  All
+// keeps the fastest.  Compression: launch form (split / mixed) x 8 or 4
+// waves per workgroup x full or half grid; decompression: launch form x
+// grid.  All
 // candidates produce the same bytes (the launch geometry never changes a
 // stream).  The choice is recorded in the context by shape class, and a
 // later plan of the same class takes it without timing.
@@ -370,18 +323,16 @@ falcon_status autotune(falcon_plan* p) {
   std::vector<BatchGeom> cands;
   const bool both = p->layout.has64 && p->layout.has32;
   const bool comp = p->layout.op == FALCON_OP_COMPRESS;
-  for (int form = 0; form <= (comp ? 1 : 0); ++form)
-    for (int split = 1; split >= (both ? 0 : 1); --split)
-      for (int nw : {16, 8})
-        for (int pct : {100, 50}) {
-          if (!comp && nw != 16) continue;  // no workgroup size choice there
-          BatchGeom g;
-          g.split = split;
-          g.nw = nw;
-          g.grid_pct = pct;
-          g.form = form;
-          cands.push_back(g);
-        }
+  for (int split = 1; split >= (both ? 0 : 1); --split)
+    for (int nw : {8, 4})
+      for (int pct : {100, 50}) {
+        if (!comp && nw != 8) continue;  // no workgroup size choice there
+        BatchGeom g;
+        g.split = split;
+        g.nw = nw;
+        g.grid_pct = pct;
+        cands.push_back(g);
+      }
   float best = 1e30f;
   BatchGeom pick = cands[0];
   for (size_t i = 0; i < cands.size(); ++i) {
@@ -416,7 +367,6 @@ falcon_status batch_call(falcon_ctx* ctx, int op, falcon_series* s, size_t count
   hipStream_t hs = stream ? static_cast<hipStream_t>(stream) : ctx->main.stream;
   BatchLayout L;
   BatchGeom g;
-  g.form = op == FALCON_OP_COMPRESS ? ctx->compress_form : 0;
   falcon_status st = batch_layout(ctx->batch, op, s, count, L, hs);
   if (st == FALCON_OK) st = batch_enqueue(ctx, ctx->batch, L, g, hs, true);
   if (st == FALCON_OK) st = dev_err(hipStreamSynchronize(hs));
@@ -451,7 +401,6 @@ falcon_status falcon_plan_create(falcon_ctx* ctx, falcon_op op, const falcon_ser
     st = dev_err(hipMemcpyAsync(p->scratch.many, p->scratch.h_desc, p->layout.desc_bytes, hipMemcpyHostToDevice,
                                 p->stream));
   if (st == FALCON_OK) st = dev_err(hipStreamSynchronize(p->stream));
-  if (op == FALCON_OP_COMPRESS && (flags & FALCON_PLAN_SINGLE_PASS)) p->geom.form = 1;
   if (st == FALCON_OK && (flags & FALCON_PLAN_TUNE)) st = autotune(p);
   if (st == FALCON_OK && (flags & FALCON_PLAN_GRAPH)) {
     if (hipStreamBeginCapture(p->stream, hipStreamCaptureModeThreadLocal) != hipSuccess) {
@@ -476,7 +425,12 @@ falcon_status falcon_plan_run(falcon_plan* p, falcon_series* s, void* stream) {
   if (!p) return FALCON_ERR_INVALID_ARG;
   if (hipSetDevice(p->ctx->device) != hipSuccess) return FALCON_ERR_DEVICE;
   hipStream_t hs = stream ? static_cast<hipStream_t>(stream) : p->stream;
-  falcon_status st = p->exec ? dev_err(hipGraphLaunch(p->exec, hs))
+  // clears the queue's words again if the last run gave up (never grows them)
+  falcon_status st = p->layout.op == FALCON_OP_COMPRESS
+                         ? queue_prepare(p->scratch.q, p->layout.total ? p->layout.total : 1, hs)
+                         : FALCON_OK;
+  if (st != FALCON_OK) return st;
+  st = p->exec ? dev_err(hipGraphLaunch(p->exec, hs))
                              : batch_enqueue(p->ctx, p->scratch, p->layout, p->geom, hs, false);
   if (st != FALCON_OK) return st;
   if ((st = dev_err(hipStreamSynchronize(hs))) != FALCON_OK) return st;
@@ -486,14 +440,15 @@ falcon_status falcon_plan_run(falcon_plan* p, falcon_series* s, void* stream) {
 falcon_status falcon_plan_describe(const falcon_plan* p, falcon_plan_info* info) {
   if (!p || !info) return FALCON_ERR_INVALID_ARG;
   info->split = p->geom.split;
-  info->waves_per_group = p->layout.op == FALCON_OP_COMPRESS ? p->geom.nw : kDecompressWaves;
+  const bool comp = p->layout.op == FALCON_OP_COMPRESS;
+  info->waves_per_group = !comp ? kDecompressWaves : p->geom.nw ? p->geom.nw : queue_waves(p->layout.total);
   info->grid_percent = p->geom.grid_pct;
   info->candidates = p->candidates;
   info->best_ms = p->best_ms;
   info->default_ms = p->default_ms;
   info->graph = p->exec != nullptr;
   info->total_chunks = p->layout.total;
-  info->form = p->layout.op == FALCON_OP_COMPRESS ? p->geom.form : 0;
+  info->form = comp ? 1 : 0;
   info->from_cache = p->from_cache ? 1 : 0;
   return FALCON_OK;
 }

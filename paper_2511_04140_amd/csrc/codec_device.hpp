@@ -101,6 +101,10 @@ __device__ __forceinline__ const_ptr<T> cst(const T* p) {
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t store_window(void* base, uint32_t bytes) {
   return __builtin_amdgcn_make_buffer_rsrc(base, 0, (int)bytes, 0x00020000);
 }
+// The same for loads: lanes out of range read 0 without an access.
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t load_window(const void* base, uint32_t bytes) {
+  return store_window(const_cast<void*>(base), bytes);
+}
 constexpr uint32_t kDropOffset = 0x80000000u;  // beyond any window: the store is dropped
 constexpr int kNonTemporal = 2;                 // aux bit: no temporal reuse expected
 
@@ -222,6 +226,9 @@ __device__ __forceinline__ U unzigzag(U z) {
 // Wave helpers
 // ---------------------------------------------------------------------------
 __device__ __forceinline__ int lane_id() { return (int)__lane_id(); }
+
+// The device's constant-rate clock (the same on every XCD), in ticks.
+__device__ __forceinline__ uint64_t now_ticks() { return __builtin_amdgcn_s_memrealtime(); }
 
 __device__ __forceinline__ uint64_t ballot(bool p) { return __ballot(p); }
 
@@ -396,6 +403,18 @@ __device__ __forceinline__ uint64_t wave_incl_scan64(uint64_t v, int lane) {
   const int row = lane >> 4;
   const uint64_t below = row == 0 ? 0 : row == 1 ? t0 : row == 2 ? t0 + t1 : t0 + t1 + t2;
   return v + below;
+}
+// The same for 32-bit values, modulo 2^32, in six DPP steps: the rows' scans,
+// then row_bcast:15 hands rows 1 and 3 the total of the row before and
+// row_bcast:31 rows 2 and 3 that of the lower half.
+__device__ __forceinline__ uint32_t wave_incl_scan32(uint32_t v) {
+  v += dpp_shr0<1>(v);
+  v += dpp_shr0<2>(v);
+  v += dpp_shr0<4>(v);
+  v += dpp_shr0<8>(v);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);
+  v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);
+  return v;
 }
 // Number of set bits of mask in lanes below this one.
 __device__ __forceinline__ uint32_t mbcnt(uint64_t m) {

@@ -1,9 +1,10 @@
 // codec_kernels.hpp -- Falcon compression and decompression kernels for
 // gfx950 (device code; each kernels_*.hip instantiates one form).
 //
-// Compression runs in two passes (size pass, scan of the sizes, write
-// pass) and decompression after a scan of the size array, so no chunk ever
-// waits for another: waves take chunks by static striding.
+// Compression runs in one launch with a work queue (k_compress_queue); where
+// nothing may be kept between calls, and for the ablation variants, in two
+// passes (k_compress_pass) around a scan of the sizes.  Decompression follows
+// a scan of the size array.
 #pragma once
 
 #include <type_traits>
@@ -478,22 +479,37 @@ __device__ __forceinline__ void write_stream_header(uint8_t* out, uint32_t dtype
 // Split in two halves: transform (front) and encode + write (back).
 // ---------------------------------------------------------------------------
 // a1: coalesced load in the slot layout; positions past the end repeat the
-// last value (padding of a partial last chunk).
+// last value (padding of a partial last chunk).  The loads go through a
+// window over the chunk at one lane offset plus constants: no address
+// arithmetic, and no 16 per-lane indices kept in registers across the chunk
+// loop.
 template <class T>
-__device__ __forceinline__ void load_chunk(const CompressSeries& sd, uint64_t c, int lane,
+__device__ __forceinline__ void load_chunk(const CompressSeries& sd, uint64_t c, int lane_in,
                                            typename T::U (&vb)[17]) {
   using U = typename T::U;
-  const global_ptr<const U> in = gbl(reinterpret_cast<const U*>(sd.in));
+  int lane = lane_in;  // opaque, see transform_front
+  asm volatile("" : "+v"(lane));
   const uint64_t base = c * kChunk;
   const uint64_t rem = sd.n - base;
-  const uint32_t nv = rem < (uint64_t)kChunk ? (uint32_t)rem : (uint32_t)kChunk;
+  const uint32_t nv = uniform(rem < (uint64_t)kChunk ? (uint32_t)rem : (uint32_t)kChunk);
+  const U* const in = reinterpret_cast<const U*>(sd.in) + base;
+  const __amdgpu_buffer_rsrc_t win = load_window(in, nv * (uint32_t)sizeof(U));
+  const int l1 = (lane + 1) * (int)sizeof(U);
 #pragma unroll
   for (int k = 0; k < 16; ++k) {
-    uint32_t idx = 1 + 64 * k + lane;
-    idx = idx < nv ? idx : nv - 1;
-    vb[k] = __builtin_nontemporal_load(in + base + idx);
+    const int o = l1 + 64 * k * (int)sizeof(U);
+    if constexpr (sizeof(U) == 8)
+      vb[k] = __builtin_bit_cast(U, __builtin_amdgcn_raw_buffer_load_b64(win, o, 0, kNonTemporal));
+    else
+      vb[k] = __builtin_amdgcn_raw_buffer_load_b32(win, o, 0, kNonTemporal);
   }
-  vb[16] = in[base];
+  vb[16] = cst(in)[0];
+  if (nv < (uint32_t)kChunk) {
+    const U last = cst(in)[nv - 1];
+#pragma unroll
+    for (int k = 0; k < 16; ++k)
+      if (1u + 64u * k + (uint32_t)lane >= nv) vb[k] = last;
+  }
 }
 
 struct ChunkPlanes {
@@ -526,22 +542,18 @@ __device__ __forceinline__ void transform_front(const LdsTables& sm, uint8_t* bu
   U* g = reinterpret_cast<U*>(buf);
   {
     const uint32_t s0 = 1u + (uint32_t)lane + ((1u + (uint32_t)lane) >> 4);
-    const F P = T::pow10(sm, case1 ? cp.A : 0);
+    auto put = [&](int k, U gk) {
+      if (k < 16) g[s0 + 68u * k] = gk;
+      else if (lane == 0) g[0] = gk;
+    };
+    // one branch for the chunk: the compiler would leave one per value
+    if (case1) {
+      const F P = T::pow10(sm, cp.A);
 #pragma unroll
-    for (int k = 0; k < 17; ++k) {
-      U gk;
-      if (case1) {
-        F r;
-        eps_test<T>(vb[k], P, r);
-        gk = (U)T::to_int(r);
-      } else {
-        gk = zigzag<U>(vb[k]);
-      }
-      if (k < 16) {
-        g[s0 + 68u * k] = gk;
-      } else if (lane == 0) {
-        g[0] = gk;
-      }
+      for (int k = 0; k < 17; ++k) put(k, (U)T::to_int(T::rnd(T::f(vb[k]) * P)));
+    } else {
+#pragma unroll
+      for (int k = 0; k < 17; ++k) put(k, zigzag<U>(vb[k]));
     }
   }
   wave_lds_sync();
@@ -856,6 +868,11 @@ __device__ __forceinline__ void stage_store(uint8_t* buf, const Staged& st, int 
   }
 }
 
+// Reports a failed check: the launch epoch to the error word (host memory).
+__device__ __forceinline__ void chunk_error(Ctl* ctl, uint32_t epoch) {
+  __hip_atomic_store(&ctl->error, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // d2-d5 of one chunk whose payload is in LDS (stage_store done).
 template <class T>
 __device__ __forceinline__ void decompress_chunk(const LdsTables& sm, uint8_t* buf, const DecompressSeries& sd,
@@ -1037,15 +1054,28 @@ __device__ __forceinline__ void decompress_chunk(const LdsTables& sm, uint8_t* b
     else
       __builtin_amdgcn_raw_buffer_store_b32(v, win, (int)voff, 0, kNonTemporal);
   }
-  if (err && lane == 0) __hip_atomic_store(&ctl->error, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (err && lane == 0) chunk_error(ctl, epoch);
   wave_lds_sync();
 }
 
 // ---------------------------------------------------------------------------
 // Kernels
 // ---------------------------------------------------------------------------
+// The series of launch chunk t: the last one of the sorted descriptors with
+// chunk0 <= t.
 template <class Series>
-__device__ __forceinline__ Series find_series(const Series& one, const Series* many, uint32_t ns, uint64_t t) {
+__device__ __forceinline__ uint32_t find_index(const Series* many, uint32_t ns, uint64_t t) {
+  if (!many) return 0;
+  uint32_t lo = 0, hi = ns - 1;
+  while (lo < hi) {
+    const uint32_t mid = (lo + hi + 1) >> 1;
+    if (cst(many)[mid].chunk0 <= t) lo = mid;
+    else hi = mid - 1;
+  }
+  return lo;
+}
+template <class Series>
+__device__ __forceinline__ Series get_series(const Series& one, const Series* many, uint32_t i) {
   if (!many) {  // one-series launch: the descriptor travels in the arguments
     Series s = one;
     // keeps the compiler from merging this copy with the global load below
@@ -1053,30 +1083,28 @@ __device__ __forceinline__ Series find_series(const Series& one, const Series* m
     asm volatile("" ::: "memory");
     return s;
   }
-  uint32_t lo = 0, hi = ns - 1;  // last series with chunk0 <= t
-  while (lo < hi) {
-    const uint32_t mid = (lo + hi + 1) >> 1;
-    if (cst(many)[mid].chunk0 <= t) lo = mid;
-    else hi = mid - 1;
-  }
   // the descriptor as 8-byte scalar loads (a struct copy through an
   // address-space-qualified pointer is not available in C++)
   static_assert(sizeof(Series) % 8 == 0, "descriptor made of 8-byte words");
   uint64_t w[sizeof(Series) / 8];
-  const const_ptr<uint64_t> q = cst(reinterpret_cast<const uint64_t*>(many + lo));
+  const const_ptr<uint64_t> q = cst(reinterpret_cast<const uint64_t*>(many + i));
 #pragma unroll
-  for (uint32_t i = 0; i < sizeof(Series) / 8; ++i) w[i] = q[i];
+  for (uint32_t k = 0; k < sizeof(Series) / 8; ++k) w[k] = q[k];
   Series s;
   __builtin_memcpy(&s, w, sizeof(Series));
   return s;
 }
+template <class Series>
+__device__ __forceinline__ Series find_series(const Series& one, const Series* many, uint32_t ns, uint64_t t) {
+  return get_series(one, many, find_index(many, ns, t));
+}
 
 // Writes the 32-byte header of every empty series of a batch launch and its
 // stream length (no chunk of the launch belongs to them).  Run by the first
-// workgroup of a batch launch (one with a descriptor array and a length
-// array), one thread per series.
+// workgroup of a batch launch (one with a descriptor array), one thread per
+// series.
 __device__ __forceinline__ void empty_series_headers(const CompressArgs& a) {
-  if (!a.lens || !a.many || blockIdx.x != 0) return;
+  if (!a.many || blockIdx.x != 0) return;
   for (uint32_t i = threadIdx.x; i < a.nseries; i += blockDim.x) {
     const CompressSeries& sd = a.many[i];
     if (sd.n != 0) continue;
@@ -1085,28 +1113,25 @@ __device__ __forceinline__ void empty_series_headers(const CompressArgs& a) {
     o[1] = 1u | (sd.dtype << 8);
     o[2] = (uint32_t)kChunk;
     o[3] = o[4] = o[5] = o[6] = o[7] = 0;
-    if (a.lens) a.lens[sd.idx] = kHdrBytes;
+    a.lens[sd.idx] = kHdrBytes;
   }
 }
 
 // ---------------------------------------------------------------------------
-// Two-pass compression.  The size pass runs a1-a9 for every chunk and keeps
+// Two-pass compression of one series (falcon_compress_noalloc and the
+// ablation variants).  The size pass runs a1-a9 for every chunk and keeps
 // what the write pass needs (ChunkMeta); the chunk sizes are then scanned
 // into offsets (k_scan_*), and the write pass reloads each chunk, redoes
 // a4-a7 with the case already decided, assembles the payload and writes it
 // at its offset.  No chunk ever waits for another, so waves take chunks by
 // static striding.
 // ---------------------------------------------------------------------------
-// vb holds the chunk's values when loaded is set (else they are loaded
-// here); prefetch() runs as soon as vb is free, so that the next chunk's
-// loads overlap the rest of this one.
+// vb holds the chunk's values; prefetch() runs as soon as vb is free, so that
+// the next chunk's loads overlap the rest of this one.
 template <class T, int V, class Prefetch>
 __device__ __forceinline__ void size_chunk(const LdsTables& tab, uint8_t* buf, const CompressArgs& a,
-                                           const CompressSeries& sd, uint64_t t, int lane,
-                                           typename T::U (&vb)[17], bool loaded, bool& hint,
-                                           Prefetch&& prefetch) {
-  const uint64_t c = t - sd.chunk0;
-  if (!loaded) load_chunk<T>(sd, c, lane, vb);
+                                           const CompressSeries& sd, uint64_t c, int lane,
+                                           typename T::U (&vb)[17], bool& hint, Prefetch&& prefetch) {
   ChunkPlanes cp;
   compress_front<T, false, V>(tab, buf, vb, lane, cp, hint);
   prefetch();
@@ -1119,8 +1144,8 @@ __device__ __forceinline__ void size_chunk(const LdsTables& tab, uint8_t* buf, c
     m.B = (uint8_t)cp.B;
     m.w = (uint8_t)cp.w;
     m.pad = 0;
-    a.meta[t] = m;
-    a.gsizes[t] = st.S;
+    a.meta[c] = m;
+    a.gsizes[c] = st.S;
     gbl(reinterpret_cast<uint32_t*>(sd.out + kHdrBytes))[c] = st.S;
   }
   wave_lds_sync();
@@ -1128,21 +1153,18 @@ __device__ __forceinline__ void size_chunk(const LdsTables& tab, uint8_t* buf, c
 
 template <class T, class Prefetch>
 __device__ __forceinline__ void write_chunk(const LdsTables& tab, uint8_t* buf, const CompressArgs& a,
-                                            const CompressSeries& sd, uint64_t t, int lane,
-                                            typename T::U (&vb)[17], bool loaded, Prefetch&& prefetch) {
-  const uint64_t c = t - sd.chunk0;
+                                            const CompressSeries& sd, uint64_t c, int lane,
+                                            typename T::U (&vb)[17], Prefetch&& prefetch) {
   const uint64_t nc = (sd.n + kChunk - 1) / kChunk;
-  if (!loaded) load_chunk<T>(sd, c, lane, vb);
   // The chunk's metadata and offset come through scalar loads at a
   // wave-uniform index (readfirstlane): a vector load would count against
   // the vector-memory counter, and waiting for it would also wait for the
   // next chunk's prefetch and this wave's outstanding stores.
-  const uint64_t tu = uniform64(t);
+  const uint64_t tu = uniform64(c);
   const const_ptr<uint64_t> mp = cst(reinterpret_cast<const uint64_t*>(a.meta + tu));
   const uint64_t flags = uniform64(mp[0]);
   const uint64_t m1 = uniform64(mp[1]);
-  const uint64_t base = a.relative ? uniform64(cst(a.offsets)[uniform64(sd.chunk0)]) : 0;
-  const uint64_t off = uniform64(cst(a.offsets)[tu]) - base;
+  const uint64_t off = uniform64(cst(a.offsets)[tu]);
   const uint32_t S = (uint32_t)m1;
   ChunkPlanes cp;
   cp.A = (int)((m1 >> 32) & 0xFF);
@@ -1168,13 +1190,6 @@ __device__ __forceinline__ void write_chunk(const LdsTables& tab, uint8_t* buf, 
   wave_lds_sync();
 }
 
-template <int NW, int WB>
-__device__ __forceinline__ void pass_prologue(BlockLdsT<NW, WB>& sm, const CompressArgs& a, bool headers) {
-  load_tables(sm.tab);
-  if (headers) empty_series_headers(a);
-  __syncthreads();
-}
-
 // PASS 1 = size pass, 2 = write pass; one dtype per launch.  V selects an
 // ablation variant (size pass only: the write pass follows the flags the
 // size pass stored); WB is the per-wave LDS buffer in 16-byte blocks, which
@@ -1186,279 +1201,433 @@ __global__ __launch_bounds__(64 * NW)
 __attribute__((amdgpu_waves_per_eu((T::W == 32 && WB == wave_blocks<T>()) ? 6 : 4))) void k_compress_pass(
     CompressArgs a) {
   __shared__ BlockLdsT<NW, WB> sm;
-  pass_prologue(sm, a, PASS == 2);
+  load_tables(sm.tab);
+  __syncthreads();
   const int lane = lane_id();
   const int wid = (int)uniform(threadIdx.x >> 6);  // wave-uniform: keeps the chunk loop scalar
   uint8_t* buf = wave_bytes(sm, wid);
   typename T::U vb[17];
-  if (PASS == 2 && a.total_chunks == 0 && !a.many && blockIdx.x == 0 && wid == 0)
-    write_stream_header(a.one.out, a.one.dtype, 0, 0, lane);
+  const CompressSeries sd = a.one;
+  if (PASS == 2 && a.total_chunks == 0 && blockIdx.x == 0 && wid == 0)
+    write_stream_header(sd.out, sd.dtype, 0, 0, lane);
   uint64_t t = (uint64_t)blockIdx.x * NW + wid;
   if (t >= a.total_chunks) return;
-  CompressSeries sd = find_series(a.one, a.many, a.nseries, t + a.t0);
-  load_chunk<T>(sd, t + a.t0 - sd.chunk0, lane, vb);
+  load_chunk<T>(sd, t, lane, vb);
   bool hint = false;  // case-decision order (decide_case), carried across the wave's chunks
   for (;;) {
-    const uint64_t tg = t + a.t0;
-    const CompressSeries cur = sd;
     const uint64_t tn = t + a.total_waves;
     const bool more = tn < a.total_chunks;
     auto prefetch = [&]() {
-      if (more) {
-        sd = find_series(a.one, a.many, a.nseries, tn + a.t0);
-        load_chunk<T>(sd, tn + a.t0 - sd.chunk0, lane, vb);
-      }
+      if (more) load_chunk<T>(sd, tn, lane, vb);
     };
-    if (PASS == 1) size_chunk<T, V>(sm.tab, buf, a, cur, tg, lane, vb, true, hint, prefetch);
-    else write_chunk<T>(sm.tab, buf, a, cur, tg, lane, vb, true, prefetch);
+    if (PASS == 1) size_chunk<T, V>(sm.tab, buf, a, sd, t, lane, vb, hint, prefetch);
+    else write_chunk<T>(sm.tab, buf, a, sd, t, lane, vb, prefetch);
     if (!more) break;
     t = tn;
   }
 }
 
-template <int NW, int PASS>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) void k_compress_pass_mixed(
-    CompressArgs a) {
-  __shared__ BlockLdsT<NW> sm;
-  pass_prologue(sm, a, PASS == 2);
-  const int lane = lane_id();
-  const int wid = (int)uniform(threadIdx.x >> 6);  // wave-uniform: keeps the chunk loop scalar
-  uint8_t* buf = wave_bytes(sm, wid);
-  bool hint = false;
-  for (uint64_t t = (uint64_t)blockIdx.x * NW + wid; t < a.total_chunks; t += a.total_waves) {
-    const uint64_t tg = t + a.t0;
-    const CompressSeries sd = find_series(a.one, a.many, a.nseries, tg);
-    auto none = []() {};
-    if (uniform(sd.dtype) == 2) {
-      uint64_t vb[17];
-      if (PASS == 1) size_chunk<TF64, kVarFalcon>(sm.tab, buf, a, sd, tg, lane, vb, false, hint, none);
-      else write_chunk<TF64>(sm.tab, buf, a, sd, tg, lane, vb, false, none);
-    } else {
-      uint32_t vb[17];
-      if (PASS == 1) size_chunk<TF32, kVarFalcon>(sm.tab, buf, a, sd, tg, lane, vb, false, hint, none);
-      else write_chunk<TF32>(sm.tab, buf, a, sd, tg, lane, vb, false, none);
+// ---------------------------------------------------------------------------
+// One-launch compression (Sec. 3.4).  The input is read once: a wave takes
+// chunks from a work queue (ticket counters), publishes each chunk's size as
+// soon as it is known, and writes the payload once the chunk's offset has
+// arrived.  One workgroup of the launch does nothing but turn sizes into
+// offsets (scan_group), so an offset costs a wave one load and no look-back of
+// its own.  Per chunk (queue_chunk):
+//   1. the loads and the case decision (a1-a3);
+//   2. the payload of the chunk before, which waits in the wave's LDS buffer,
+//      moves to registers;
+//   3. the transform and the row statistics (a4-a9) through the buffer; the
+//      size is published;
+//   4. the offset of the chunk before, and its payload's stores;
+//   5. the transpose and this chunk's payload, assembled in the buffer (a7,
+//      a11).
+// A chunk's offset is used one whole chunk after its size went out, and no
+// wave waits between taking a chunk and publishing its size.  Both matter: an
+// offset needs the size of every earlier chunk, of which some 4,000 are under
+// way, so the slowest of them sets the wait.  Waiting right after the
+// assembly cost 500 us of 1,350 on 2 GiB of float64 readings; here it costs
+// nothing measurable.
+// Bound by instruction issue on decimal data and float32 (VALU at 60-70 % of
+// its rate), by memory on float64 readings.  Against a size pass, three scan
+// launches and a write pass, which read the input twice: 2 GiB of float64
+// readings 1,200 -> 840 us, of two-place decimals 1,075 -> 690 us, 1 GiB of
+// float32 645 -> 543 us, 8 MiB of decimals 47 -> 20 us, 16 KB 40 -> 15 us.
+// Sizes and offsets travel through device-scope words that are zero between
+// launches: the scanning workgroup clears a size when it has read it, a wave
+// an offset, and the last to draw from a counter that counter, so a launch
+// needs no clearing launch before it and can be replayed from a graph.
+//
+// Progress.  The first workgroup to come scans; every other one has a wave on
+// each of the NW ticket counters.  Working waves wait for offsets, so for
+// sizes of smaller chunks.  Take the smallest chunk whose size is not
+// published: if a wave holds it, that wave at most loads and computes before
+// it publishes; if not, every chunk its counter has handed out is smaller, so
+// the wave of that counter in any resident working workgroup comes to it (the
+// offset it may wait for first is smaller still, and delivered).  So the queue
+// drains with the scanning workgroup and any one other resident, whatever
+// else runs on the device.  The waits are bounded all the same: past their
+// limits (or once another wave has given up) a wave sets ctl->qerror and
+// leaves; no payload is written without its offset, and none past the nc
+// chunk bounds that the caller's buffer holds.
+// ---------------------------------------------------------------------------
+constexpr uint64_t kOffReady = 1ull << 63;   // offset word: delivered (0: not yet)
+// a size word is not 0 once known
+constexpr uint32_t kSizeHead = 1u << 31;     // the first chunk of its series
+constexpr uint32_t kSizeMask = kSizeHead - 1;
+constexpr uint32_t kWaitLimit = 1u << 20;    // rereads of an offset, a microsecond or so each
+constexpr uint32_t kScanLimit = 1u << 22;    // rounds of the scanning wave without a new size
+
+template <class W>
+__device__ __forceinline__ W qload(const W* p) {
+  return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+template <class W>
+__device__ __forceinline__ void qstore(W* p, W v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// The control block is host memory.
+__device__ __forceinline__ bool queue_failed(const Ctl* ctl) {
+  return __hip_atomic_load(&ctl->qerror, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM) != 0;
+}
+__device__ __forceinline__ void queue_fail(Ctl* ctl) {
+  __hip_atomic_store(&ctl->qerror, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// The wave's next chunk; total_chunks and above: none left.  Counter g hands
+// out the chunks g, g + NW, g + 2 NW, ... in increasing order, one wave of
+// every workgroup drawing from it: one counter would serialise all chunks of
+// the launch on one memory location (12 ns a draw).  Every working wave draws
+// exactly one ticket past its counter's chunks, so the wave that draws the
+// last of them clears the counter.
+template <int NW>
+__device__ __forceinline__ uint64_t take_chunk(const CompressArgs& a, uint32_t g, int lane) {
+  uint64_t* const ctr = a.qctr + (size_t)kQueueStride * g;
+  uint64_t k = 0;
+  if (lane == 0) k = __hip_atomic_fetch_add(ctr, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  k = uniform64(k);
+  const uint64_t t = k * NW + g;
+  if (t >= a.total_chunks) {
+    const uint64_t valid = (a.total_chunks + NW - 1 - g) / NW;  // chunks on this counter
+    if (k == valid + (gridDim.x - 1) - 1 && lane == 0) qstore(ctr, (uint64_t)0);
+  }
+  return t;
+}
+
+// Whether this workgroup is the launch's scanning one: the first to come
+// (called by one thread).  The workgroups meet in kRoleLines lines first, so
+// that a full chip of them does not queue at one word; the last to come
+// clears each word.
+__device__ __forceinline__ bool take_scan_role(const CompressArgs& a) {
+  uint64_t* const role = a.qctr + (size_t)kQueueStride * kQueueGroups;
+  const uint32_t line = blockIdx.x % kRoleLines, lines = min(gridDim.x, (uint32_t)kRoleLines);
+  uint64_t* const mine = role + (size_t)kQueueStride * (1 + line);
+  const uint64_t k = __hip_atomic_fetch_add(mine, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (k == (gridDim.x + kRoleLines - 1 - line) / kRoleLines - 1) qstore(mine, (uint64_t)0);
+  if (k != 0) return false;
+  const uint64_t first = __hip_atomic_fetch_add(role, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (first == lines - 1) qstore(role, (uint64_t)0);
+  return first == 0;
+}
+
+// a10 by one workgroup: sizes to offsets in chunk order, each series' offsets
+// starting at 0 (a size word carries its series' first-chunk mark).  It has
+// to keep up with the whole chip, some 500 chunks a microsecond, and nothing
+// else hides its latencies; a round reads 64 * kScanBlocks sizes per wave, and
+// each wave scans its own part up to the first size still missing.  (One
+// wave alone moved 250 chunks a microsecond; with 1, 2, 4 and 8 blocks of 64 a
+// wave, 1 GiB of float32 took 1,134, 711, 544 and 560 us.)
+constexpr int kScanBlocks = 4;
+struct ScanPart {   // one wave's part of a round
+  uint32_t known;   // sizes up to the first gap
+  uint32_t sum;     // their sum from the part's last first-chunk mark on
+  uint32_t mark;    // the part holds such a mark
+  uint32_t failed;
+};
+template <int NW>
+__device__ __forceinline__ void scan_group(const CompressArgs& a, ScanPart* parts, int lane, int wid,
+                                           uint64_t t_start) {
+  constexpr uint32_t kPart = 64 * kScanBlocks;
+  uint64_t t = 0, carry = 0, seen = 0;
+  uint32_t idle = 0;
+  __builtin_amdgcn_s_setprio(3);
+  for (uint32_t round = 0; t < a.total_chunks; ++round) {
+    const uint64_t at = t + kPart * (uint32_t)wid + (uint32_t)lane;
+    uint32_t w[kScanBlocks];
+#pragma unroll
+    for (int r = 0; r < kScanBlocks; ++r) w[r] = qload(a.qsize + at + 64 * r);
+    // this wave's part: offsets from its start (or its marks) on
+    uint32_t rel[kScanBlocks], m[kScanBlocks];
+    uint64_t marked[kScanBlocks];  // lanes at or past a mark of the part
+    ScanPart p{0, 0, 0, 0};
+    bool open = true;
+#pragma unroll
+    for (int r = 0; r < kScanBlocks; ++r) {
+      const uint64_t missing = ~ballot(w[r] != 0);
+      const uint32_t known = missing ? (uint32_t)__builtin_ctzll(missing) : 64u;
+      m[r] = open ? known : 0;
+      open = open && known == 64;
+      const bool mine = (uint32_t)lane < m[r];
+      const uint32_t v = mine ? w[r] & kSizeMask : 0u;
+      const uint32_t incl = wave_incl_scan32(v), excl = incl - v;
+      const uint32_t all = rl(incl, 63);
+      const uint64_t heads = a.many ? ballot(mine && (w[r] & kSizeHead) != 0) : 0;
+      rel[r] = p.sum + excl;
+      marked[r] = p.mark ? ~0ull : 0;
+      p.sum += all;
+      if (heads) {
+        const uint64_t below = heads & (~0ull >> (63 - lane));  // marks up to this lane
+        const int head = below ? 63 - (int)__builtin_clzll(below) : 0;
+        const uint32_t from = (uint32_t)__builtin_amdgcn_ds_bpermute(head << 2, (int)excl);
+        if (below) rel[r] = excl - from;
+        marked[r] |= ~0ull << __builtin_ctzll(heads);
+        p.sum = all - rl(excl, 63 - (int)__builtin_clzll(heads));
+        p.mark = 1;
+      }
+      p.known += m[r];
     }
+    if (wid == 0 && (idle > kScanLimit || ((idle & 255u) == 255u && queue_failed(a.ctl)))) p.failed = 1;
+    ScanPart* const now = parts + NW * (round & 1u);  // two sets: one barrier a round
+    if (lane == 0) now[wid] = p;
+    __syncthreads();
+    seen = now_ticks();
+    // the parts before this one, up to the first gap of the round
+    uint64_t base = carry;
+    bool mine_open = true, all_open = true, failed = false;
+    uint64_t t_next = t;
+#pragma unroll
+    for (int i = 0; i < NW; ++i) {
+      if (i == wid) {
+        base = carry;
+        mine_open = all_open;
+      }
+      const ScanPart q = now[i];
+      if (all_open) {
+        carry = q.mark ? (uint64_t)uniform(q.sum) : carry + uniform(q.sum);
+        t_next += uniform(q.known);
+      }
+      all_open = all_open && uniform(q.known) == kPart;
+      failed = failed || uniform(q.failed) != 0;
+    }
+    if (failed) {
+      if (wid == 0 && lane == 0) queue_fail(a.ctl);
+      break;
+    }
+    if (mine_open) {
+#pragma unroll
+      for (int r = 0; r < kScanBlocks; ++r) {
+        if ((uint32_t)lane < m[r]) {
+          qstore(a.qoff + at + 64 * r, (((marked[r] >> lane) & 1u ? 0 : base) + rel[r]) | kOffReady);
+          qstore(a.qsize + at + 64 * r, 0u);
+        }
+      }
+    }
+    idle = t_next == t ? idle + 1 : 0;
+    t = t_next;
+  }
+  __builtin_amdgcn_s_setprio(0);
+  if (a.times && wid == 0 && lane == 0) {
+    a.times[0] = t_start;
+    a.times[1] = seen;
+    a.times[2] = now_ticks();
   }
 }
 
-// ---------------------------------------------------------------------------
-// Single-pass compression (Sec. 3.4): one launch computes every chunk and
-// writes it at its offset.  Waves take chunks from a work queue (atomic
-// ticket counters, see take_ticket), so chunks start close to launch order,
-// and each chunk finds its offset with a decoupled look-back over per-chunk
-// status words:
-//   1. a1-a6 and the row statistics give the chunk's size S, published at
-//      once as an aggregate (A, S); a series' first chunk publishes its
-//      inclusive prefix (P, S) instead;
-//   2. the transpose and the payload assembly (at byte phase 0 in LDS) run
-//      while the chunks before it publish their sizes;
-//   3. the look-back reads the 64 status words before the chunk, adds the
-//      aggregates up to the nearest inclusive prefix and publishes (P, O + S);
-//   4. the payload goes to its offset O, shifted to the destination's byte
-//      phase on the way out of LDS.
-// A chunk waits only for smaller chunks.  The smallest unfinished chunk
-// never waits: if a wave holds it, every chunk before it is done; if not,
-// every chunk its counter has handed out is smaller and done, so the waves
-// of that counter are free to take it.  So the queue always drains, with
-// or without other kernels on the device.  The look-back's wait is nevertheless
-// bounded: past kSpinLimit rereads (or once another wave has given up) it
-// gives up, sets ctl->qerror and the chunk writes nothing; its successors
-// then compute offsets that are too small, never too large, and every
-// payload write is also checked against the nc chunk bounds the caller's
-// buffer holds, so nothing is written out of bounds.
-// ---------------------------------------------------------------------------
-// Status word: bits 63..62 kind (1 = aggregate, 2 = inclusive prefix),
-// bits 61..46 the launch's tag, bits 45..0 the byte count.
-constexpr uint64_t kStAgg = 1ull << 62, kStPre = 2ull << 62;
-constexpr uint64_t kStValMask = (1ull << 46) - 1;
-constexpr uint64_t kStTagMask = 0xFFFFull << 46;
-constexpr uint32_t kSpinLimit = 1u << 20;
-
-__device__ __forceinline__ uint64_t status_word(uint64_t kind, uint32_t tag, uint64_t v) {
-  return kind | ((uint64_t)(tag & 0xFFFFu) << 46) | (v & kStValMask);
-}
-
-// The next chunk of the calling wave (lane 0 takes the ticket; every lane
-// gets the chunk).  Counter g hands out chunks g, g + G, g + 2G, ... in
-// increasing order to the waves with (workgroup + wave index) mod G = g;
-// one counter would serialise every chunk on one memory location.  Mixing
-// the wave index in spreads each counter's waves over all XCDs (workgroups
-// are dealt to XCDs round-robin), so that no counter falls behind with a
-// slower XCD.
-__device__ __forceinline__ uint64_t take_ticket(const CompressArgs& a, int lane) {
-  const uint32_t g = (blockIdx.x + uniform(threadIdx.x >> 6)) % a.qgroups;
-  uint64_t k = 0;
-  if (lane == 0)
-    k = __hip_atomic_fetch_add(a.qctr + (size_t)kQueueStride * g, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return uniform64(k) * a.qgroups + g;
-}
-
-// Exclusive prefix of the sizes of the chunks tf .. tg - 1 (tf = launch
-// index of the series' first chunk, tg > tf): the aggregates of the chunks
-// before tg back to the nearest inclusive prefix, plus that prefix.  Lane L
-// reads the status word of chunk j - 1 - L; positions before tf act as an
-// inclusive prefix of 0.  Sets failed (uniform) after kSpinLimit rereads of
-// a window with a word still unpublished.
-__device__ __forceinline__ uint64_t look_back(const CompressArgs& a, uint64_t tg, uint64_t tf, int lane,
-                                              bool& failed) {
-  const uint64_t tag = (uint64_t)(a.qtag & 0xFFFFu) << 46;
-  uint64_t acc = 0;
-  uint64_t j = tg;
-  uint32_t spins = 0;
-  for (;;) {
-    const bool edge = j < tf + 1 + (uint64_t)lane;  // j - 1 - lane < tf
-    uint64_t w = 0;
-    if (!edge) w = __hip_atomic_load(a.status + (j - 1 - lane), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    const bool mine = (w & kStTagMask) == tag;
-    const bool pre = edge || (mine && (w >> 62) == 2);
-    const bool ready = pre || (mine && (w >> 62) == 1);
-    const uint64_t pm = ballot(pre);
-    const uint32_t s = pm ? (uint32_t)__builtin_ctzll(pm) : 64u;
-    // lanes 0 .. s must all hold a published word
-    const uint64_t upto = s >= 63 ? ~0ull : ((2ull << s) - 1);
-    if ((ballot(!ready) & upto) == 0) {
-      acc += wave_sum64(((uint32_t)lane <= s && !edge) ? (w & kStValMask) : 0ull);
-      if (s < 64) return acc;
-      j -= 64;
-      continue;
-    }
-    // give up past the limit, or at once when another wave has given up
-    // (every 256 rereads the shared error word is checked)
+// The delivered offset of launch chunk t (word: an earlier read of it);
+// failed is set when none arrives.
+__device__ __forceinline__ uint64_t wait_offset(const CompressArgs& a, uint64_t t, uint64_t word, int lane,
+                                                bool& failed) {
+  uint64_t w = uniform64(word);
+  for (uint32_t spins = 0; !(w & kOffReady);) {
     ++spins;
-    if (spins > kSpinLimit ||
-        ((spins & 255u) == 0 &&
-         __hip_atomic_load(&a.ctl->qerror, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0)) {
+    if (spins > kWaitLimit || ((spins & 255u) == 0 && queue_failed(a.ctl))) {
       failed = true;
       return 0;
     }
-    __builtin_amdgcn_s_sleep(1);
+    __builtin_amdgcn_s_sleep(8);
+    w = uniform64(qload(a.qoff + t));
   }
+  if (lane == 0) qstore(a.qoff + t, (uint64_t)0);
+  return w & ~kOffReady;
 }
 
-// a11 for the single pass: copies a payload assembled at phase 0 (buf holds
-// its S bytes) to dst, which may have any byte phase ph = dst & 15.  Whole
-// 16-byte destination blocks are built from five aligned LDS dwords shifted
-// by the phase (v_alignbyte) and stored with one non-temporal 16-byte store
-// each (as in copy_payload); the partial first and last blocks are written
-// byte by byte, one byte per lane (lanes 0-15 the first block, 16-31 the
-// last).
-__device__ __forceinline__ void copy_payload_shifted(const uint8_t* buf, uint8_t* dst, uint32_t S, int lane) {
-  const uint32_t ph = uniform((uint32_t)((uintptr_t)dst & 15u));
-  uint8_t* const dal = dst - ph;
-  const uint32_t end = ph + S;
-  const uint32_t nblk = (end + 15) >> 4;
-  const uint32_t r = (16u - ph) & 3u;  // byte shift inside a dword (uniform)
-  const uint32_t* bw = reinterpret_cast<const uint32_t*>(buf);
-  // whole blocks: 16k >= ph and 16k + 16 <= end
-  const uint32_t k0 = ph ? 1u : 0u;
-  const uint32_t k1 = end >> 4;  // blocks below k1 end at or before `end`
-  for (uint32_t k = k0 + (uint32_t)lane; k < k1; k += 64) {
-    const uint32_t x = 16u * k - ph;  // first payload byte of the block
-    const uint32_t d0 = x >> 2;
-    const uint32_t w0 = bw[d0], w1 = bw[d0 + 1], w2 = bw[d0 + 2], w3 = bw[d0 + 3], w4 = bw[d0 + 4];
-    uint4 v;
-    v.x = __builtin_amdgcn_alignbyte(w1, w0, r);
-    v.y = __builtin_amdgcn_alignbyte(w2, w1, r);
-    v.z = __builtin_amdgcn_alignbyte(w3, w2, r);
-    v.w = __builtin_amdgcn_alignbyte(w4, w3, r);
-    gstore16_nt(dal + 16u * k, v);
-  }
-  // partial blocks: the first if ph > 0 (or the payload ends inside it), the
-  // last if end is not block aligned and it is not the first
-  const uint32_t j = (uint32_t)lane & 15u;
-  if (lane < 16) {
-    const bool partial = ph != 0 || end < 16;
-    if (partial && j >= ph && j < end) gbl(dal)[j] = buf[j - ph];
-  } else if (lane < 32) {
-    const uint32_t kl = nblk - 1;
-    const uint32_t p = 16u * kl + j;
-    if (kl > 0 && (end & 15u) != 0 && p < end) gbl(dal)[p] = buf[p - ph];
-  }
+// A chunk whose payload waits in the wave's LDS buffer for its offset.
+struct Waiting {
+  uint64_t t;       // launch chunk
+  uint32_t series;  // its series' descriptor
+  uint32_t S;
+};
+
+// A payload held in registers: lane L the 16-byte blocks L, L + 64, ... and
+// one of the bytes past them (a payload of a whole number of kHeldBlocks * 64
+// blocks and more has up to 19 of those).
+template <class T>
+struct Held {
+  static constexpr int kBlocks = T::BOUND / 1024;
+  uint4 blk[kBlocks];
+  uint32_t byte, nblk, rest;
+};
+template <class T>
+__device__ __forceinline__ void hold_payload(const uint8_t* buf, uint32_t S, int lane_in, Held<T>& h) {
+  int lane = lane_in;  // opaque, see transform_front
+  asm volatile("" : "+v"(lane));
+  static_assert(T::BOUND - Held<T>::kBlocks * 1024 < 64, "one byte per lane holds the rest");
+  h.nblk = min(S >> 4, (uint32_t)Held<T>::kBlocks * 64u);
+  h.rest = S - 16u * h.nblk;
+#pragma unroll
+  for (int k = 0; k < Held<T>::kBlocks; ++k)
+    if (64u * k < h.nblk) h.blk[k] = *reinterpret_cast<const uint4*>(buf + 16u * ((uint32_t)lane + 64u * k));
+  h.byte = buf[16u * h.nblk + min((uint32_t)lane, h.rest)];
+  wave_lds_sync();
+}
+// a11: the payload to dst, which may have any alignment: unaligned 16-byte
+// stores, whose 64 lanes cover 1024 bytes back to back, ran within 2-8 % of
+// aligned ones (4,197 against 4,283 GB/s writing 5,264-byte payloads), so the
+// payload needs no shift to its destination's phase.
+template <class T>
+__device__ __forceinline__ void store_payload(uint8_t* dst, const Held<T>& h, int lane_in) {
+  int lane = lane_in;  // opaque, see transform_front
+  asm volatile("" : "+v"(lane));
+  const __amdgpu_buffer_rsrc_t blocks = store_window(dst, 16u * h.nblk);
+#pragma unroll
+  for (int k = 0; k < Held<T>::kBlocks; ++k)
+    if (64u * k < h.nblk)
+      __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, h.blk[k]), blocks, 16 * lane + 1024 * k, 0,
+                                             kNonTemporal);
+  const __amdgpu_buffer_rsrc_t tail = store_window(dst + 16u * h.nblk, h.rest);
+  __builtin_amdgcn_raw_buffer_store_b8((uint8_t)h.byte, tail, lane, 0, 0);
 }
 
-// One chunk of the single pass, executed by one wave.  vb holds its values;
-// next() runs once the chunk's offset is known: it takes the wave's next
-// ticket and loads that chunk into vb (so the ticket is drawn when the wave
-// is about to start it, and chunks publish their sizes close to ticket
-// order), and the loads overlap this chunk's payload copy.
-template <class T, class Next>
-__device__ __forceinline__ void queue_chunk(const LdsTables& tab, uint8_t* buf, const CompressArgs& a,
-                                            const CompressSeries& sd, uint64_t tg, int lane,
-                                            typename T::U (&vb)[17], Next&& next) {
-  const uint64_t c = tg - sd.chunk0;
+// Writes a held payload at its offset; false if the offset never came or
+// lies past the nc chunk bounds that the caller's buffer holds.
+template <class T>
+__device__ __forceinline__ bool finish_chunk(const CompressArgs& a, const Waiting& p, const Held<T>& h,
+                                             uint64_t word, int lane) {
+  bool failed = false;
+  const uint64_t off = wait_offset(a, p.t, word, lane, failed);
+  const CompressSeries sd = get_series(a.one, a.many, p.series);
+  const uint64_t c = p.t + a.t0 - sd.chunk0;
   const uint64_t nc = (sd.n + kChunk - 1) / kChunk;
-  // a2-a6 and the row statistics (a8-a9)
+  if (failed || off + p.S > nc * (uint64_t)T::BOUND) {
+    if (lane == 0) queue_fail(a.ctl);
+    return false;
+  }
+  store_payload<T>(sd.out + kHdrBytes + 4 * nc + off, h, lane);
+  if (c == nc - 1) {
+    write_stream_header(sd.out, sd.dtype, sd.n, off + p.S, lane);
+    if (a.lens && lane == 0) a.lens[sd.idx] = kHdrBytes + 4 * nc + off + p.S;
+  }
+  return true;
+}
+
+// One chunk of the queue (values in vb): see the steps above.  p is the chunk
+// before it, if pending, and becomes cur.  False if the chunk before could
+// not be written.
+template <class T>
+__device__ __forceinline__ bool queue_chunk(const LdsTables& tab, uint8_t* buf, const CompressArgs& a,
+                                            const Waiting& cur, const typename T::U (&vb)[17], int lane,
+                                            bool& hint, Waiting& p, bool pending) {
   ChunkPlanes cp;
-  bool case1, no_hint = false;  // the queue's waves take chunks far apart: no order hint
-  decide_case<T, false>(tab, vb, cp.A, cp.B, case1, no_hint);
+  bool case1;
+  decide_case<T>(tab, vb, cp.A, cp.B, case1, hint);
+  // asked for here, the offset has arrived when the size is out
+  const uint64_t word = pending ? qload(a.qoff + p.t) : 0;
+  Held<T> h;
+  if (pending) hold_payload<T>(buf, p.S, lane, h);
   typename T::U e[16];
   transform_front<T, true>(tab, buf, vb, lane, case1, cp, e);
   const ChunkStats st = chunk_stats_or<T>(cp, lane);
   const uint32_t S = uniform(st.S);
   const uint64_t flags = uniform64(st.flags);
-  // step 1: publish the size
+  const CompressSeries sd = get_series(a.one, a.many, cur.series);
+  const uint64_t c = cur.t + a.t0 - sd.chunk0;
   if (lane == 0) {
-    __hip_atomic_store(a.status + tg, status_word(c == 0 ? kStPre : kStAgg, a.qtag, S), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
+    qstore(a.qsize + cur.t, S | (c == 0 ? kSizeHead : 0u));
     gbl(reinterpret_cast<uint32_t*>(sd.out + kHdrBytes))[c] = S;
   }
-  // step 2: a7 and the payload at phase 0
+  if (pending && !finish_chunk<T>(a, p, h, word, lane)) return false;
   transform_planes<T>(cp, e);
+  __builtin_amdgcn_s_setprio(2);
   assemble_payload<T>(buf, cp, flags, S, lane);
-  // step 3: the offset
-  bool failed = false;
-  const uint64_t off = c == 0 ? 0 : look_back(a, tg, sd.chunk0, lane, failed);
-  // a payload always ends within nc chunk bounds of the payload's start
-  // (the caller's buffer holds at least that much): a look-back that gave
-  // up, or any offset past that, writes nothing
-  failed = failed || off + S > nc * (uint64_t)T::BOUND;
-  if (c != 0 && lane == 0)
-    __hip_atomic_store(a.status + tg, status_word(kStPre, a.qtag, off + S), __ATOMIC_RELAXED,
-                       __HIP_MEMORY_SCOPE_AGENT);
-  next();
   wave_lds_sync();
-  // step 4: the payload at its offset
-  if (!failed) copy_payload_shifted(buf, sd.out + kHdrBytes + 4 * nc + off, S, lane);
-  else if (lane == 0) __hip_atomic_store(&a.ctl->qerror, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (c == nc - 1) {
-    write_stream_header(sd.out, sd.dtype, sd.n, off + S, lane);
-    if (a.lens && lane == 0) a.lens[sd.idx] = kHdrBytes + 4 * nc + off + S;
-  }
-  wave_lds_sync();
+  __builtin_amdgcn_s_setprio(0);
+  p = cur;
+  p.S = S;
+  return true;
 }
 
-// One dtype per launch.  Every wave takes chunks until it draws one past
-// the last.
+// The last chunk of a wave.
+template <class T>
+__device__ __forceinline__ void finish_last(uint8_t* buf, const CompressArgs& a, const Waiting& p, int lane) {
+  Held<T> h;
+  hold_payload<T>(buf, p.S, lane, h);
+  (void)finish_chunk<T>(a, p, h, qload(a.qoff + p.t), lane);
+}
+
+// The launch's end as its waves see it: the latest of them, in lines of
+// their own (the clock only grows, so nothing needs clearing).
+__device__ __forceinline__ void stamp_end(uint64_t* times, int lane) {
+  if (!times) return;
+  __builtin_amdgcn_s_waitcnt(0);
+  if (lane == 0)
+    (void)__hip_atomic_fetch_max(times + kTimeStride * (1 + blockIdx.x % kTimeEnds), now_ticks(), __ATOMIC_RELAXED,
+                                 __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// An empty launch (no chunk): the header of an empty one-series stream.
+__device__ __forceinline__ void empty_launch(const CompressArgs& a, int lane, int wid, uint64_t t_start) {
+  if (blockIdx.x != 0 || wid != 0) return;
+  if (!a.many) write_stream_header(a.one.out, a.one.dtype, 0, 0, lane);
+  if (a.times && lane == 0) {
+    a.times[0] = a.times[1] = a.times[2] = t_start;
+  }
+  stamp_end(a.times, lane);
+}
+
+// Tables, the headers of empty series, and the workgroup's role: true if it
+// is the scanning one (or the launch has no chunk).
+template <int NW, int WB>
+__device__ __forceinline__ bool queue_prologue(BlockLdsT<NW, WB>& sm, const CompressArgs& a) {
+  uint32_t* const role = reinterpret_cast<uint32_t*>(&sm.wave[0][0]);
+  if (threadIdx.x == 0) *role = a.total_chunks == 0 || take_scan_role(a) ? 1u : 0u;
+  load_tables(sm.tab);
+  empty_series_headers(a);
+  __syncthreads();
+  const bool scan = uniform(*role) != 0;
+  __syncthreads();  // before the buffer is used
+  return scan;
+}
+
+// One dtype per launch.
 template <class T, int NW>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) void k_compress_queue(CompressArgs a) {
-  __shared__ BlockLdsT<NW> sm;
-  pass_prologue(sm, a, true);
+__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(T::W == 32 ? 6 : 4))) void k_compress_queue(
+    CompressArgs a) {
+  __shared__ BlockLdsT<NW, wave_blocks<T>()> sm;
+  const uint64_t t_start = now_ticks();
   const int lane = lane_id();
   const int wid = (int)uniform(threadIdx.x >> 6);
-  uint8_t* buf = wave_bytes(sm, wid);
-  typename T::U vb[17];
-  if (a.total_chunks == 0 && !a.many && blockIdx.x == 0 && wid == 0)
-    write_stream_header(a.one.out, a.one.dtype, 0, 0, lane);
-  uint64_t t = take_ticket(a, lane);
-  if (t >= a.total_chunks) return;
-  CompressSeries sd = find_series(a.one, a.many, a.nseries, t + a.t0);
-  load_chunk<T>(sd, t + a.t0 - sd.chunk0, lane, vb);
-  for (;;) {
-    const CompressSeries cur = sd;
-    uint64_t tn = 0;
-    bool more = false;
-    auto next = [&]() {
-      tn = take_ticket(a, lane);
-      more = tn < a.total_chunks;
-      if (more) {
-        sd = find_series(a.one, a.many, a.nseries, tn + a.t0);
-        load_chunk<T>(sd, tn + a.t0 - sd.chunk0, lane, vb);
-      }
-    };
-    queue_chunk<T>(sm.tab, buf, a, cur, t + a.t0, lane, vb, next);
-    if (!more) break;
-    t = tn;
+  if (queue_prologue(sm, a)) {
+    if (a.total_chunks == 0) empty_launch(a, lane, wid, t_start);
+    else scan_group<NW>(a, reinterpret_cast<ScanPart*>(&sm.wave[0][1]), lane, wid, t_start);
+    return;
   }
+  uint8_t* buf = wave_bytes(sm, wid);
+  bool hint = false;
+  bool pending = false;
+  Waiting p{0, 0, 0};
+  for (;;) {
+    const uint64_t t = take_chunk<NW>(a, (uint32_t)wid, lane);
+    if (t >= a.total_chunks) break;
+    const Waiting cur{t, find_index(a.many, a.nseries, t + a.t0), 0};
+    const CompressSeries sd = get_series(a.one, a.many, cur.series);
+    typename T::U vb[17];
+    load_chunk<T>(sd, t + a.t0 - sd.chunk0, lane, vb);
+    if (!queue_chunk<T>(sm.tab, buf, a, cur, vb, lane, hint, p, pending)) return;
+    pending = true;
+  }
+  if (pending) finish_last<T>(buf, a, p, lane);
+  stamp_end(a.times, lane);
 }
 
 // Both dtypes in one launch: the wave branches on the dtype of each chunk's
@@ -1467,26 +1636,42 @@ template <int NW>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) void k_compress_queue_mixed(
     CompressArgs a) {
   __shared__ BlockLdsT<NW> sm;
-  pass_prologue(sm, a, true);
+  const uint64_t t_start = now_ticks();
   const int lane = lane_id();
   const int wid = (int)uniform(threadIdx.x >> 6);
-  uint8_t* buf = wave_bytes(sm, wid);
-  auto none = []() {};
-  for (;;) {
-    const uint64_t t = take_ticket(a, lane);
-    if (t >= a.total_chunks) break;
-    const uint64_t tg = t + a.t0;
-    const CompressSeries sd = find_series(a.one, a.many, a.nseries, tg);
-    if (uniform(sd.dtype) == 2) {
-      uint64_t vb[17];
-      load_chunk<TF64>(sd, tg - sd.chunk0, lane, vb);
-      queue_chunk<TF64>(sm.tab, buf, a, sd, tg, lane, vb, none);
-    } else {
-      uint32_t vb[17];
-      load_chunk<TF32>(sd, tg - sd.chunk0, lane, vb);
-      queue_chunk<TF32>(sm.tab, buf, a, sd, tg, lane, vb, none);
-    }
+  if (queue_prologue(sm, a)) {
+    if (a.total_chunks == 0) empty_launch(a, lane, wid, t_start);
+    else scan_group<NW>(a, reinterpret_cast<ScanPart*>(&sm.wave[0][1]), lane, wid, t_start);
+    return;
   }
+  uint8_t* buf = wave_bytes(sm, wid);
+  bool hint = false;
+  bool pending = false, pending64 = false;
+  Waiting p{0, 0, 0};
+  for (;;) {
+    const uint64_t t = take_chunk<NW>(a, (uint32_t)wid, lane);
+    if (t >= a.total_chunks) break;
+    const Waiting cur{t, find_index(a.many, a.nseries, t + a.t0), 0};
+    const CompressSeries sd = get_series(a.one, a.many, cur.series);
+    const bool is64 = uniform(sd.dtype) == 2;
+    // float64 chunks come first, so a wave changes its dtype once at most
+    if (pending && pending64 != is64) {
+      finish_last<TF64>(buf, a, p, lane);
+      pending = false;
+    }
+    auto chunk = [&](auto tag) {
+      using T = decltype(tag);
+      typename T::U vb[17];
+      load_chunk<T>(sd, t + a.t0 - sd.chunk0, lane, vb);
+      return queue_chunk<T>(sm.tab, buf, a, cur, vb, lane, hint, p, pending);
+    };
+    if (!(is64 ? chunk(TF64{}) : chunk(TF32{}))) return;
+    pending = true;
+    pending64 = is64;
+  }
+  if (pending && pending64) finish_last<TF64>(buf, a, p, lane);
+  else if (pending) finish_last<TF32>(buf, a, p, lane);
+  stamp_end(a.times, lane);
 }
 
 // A one-series launch whose header the host has not read
@@ -1510,7 +1695,7 @@ __device__ __forceinline__ DecompressSeries resolve_header(const DecompressArgs&
                   ((uint64_t)w[4] | ((uint64_t)w[5] << 32)) == sd.n && sd.in_len >= kHdrBytes + 4 * nc &&
                   payload <= sd.in_len - kHdrBytes - 4 * nc;
   sd.payload_bytes = ok ? payload : 0;
-  if (!ok && lane == 0) __hip_atomic_store(&a.ctl->error, a.epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (!ok && lane == 0) chunk_error(a.ctl, a.epoch);
   return sd;
 }
 

@@ -30,6 +30,17 @@ inline falcon_status dev_err(hipError_t e) { return e == hipSuccess ? FALCON_OK 
 // Writes the 32-byte stream header (format in falcon.h) to host memory.
 void write_header(uint8_t* h, falcon_dtype dt, uint64_t n, uint64_t payload);
 
+// Words of the one-launch compression: kQueueWords counters, a size and an
+// offset word per chunk.  Every launch leaves them zero, as it needs them;
+// they are cleared when they are allocated, and after a launch that failed.
+struct Queue {
+  uint64_t* ctr = nullptr;
+  uint32_t* size = nullptr;
+  uint64_t* off = nullptr;
+  size_t cap = 0;      // chunks
+  bool dirty = false;  // a launch gave up: clear before the next
+};
+
 // One independent launch queue: a stream and the device scratch that a
 // compression or decompression launch needs for itself (chunk offsets,
 // scan tile sums, size-pass results, control block).  Launches on
@@ -40,22 +51,14 @@ struct Lane {
   size_t offsets_cap = 0;
   uint64_t* tiles = nullptr;    // scan tile sums
   size_t tiles_cap = 0;
-  falcon_dev::Ctl* ctl = nullptr;
-  uint8_t* stage = nullptr;     // pinned host bytes: [0,32) header, [32,40) copy of the control block's
-                                // two error words, [40,48) payload size
+  falcon_dev::Ctl* ctl = nullptr;  // pinned host memory (error words)
+  uint8_t* stage = nullptr;     // pinned host bytes: [0,32) header, [40,48) payload size
   uint32_t epoch = 0;
   falcon_dev::ChunkMeta* meta = nullptr;  // compression size pass results, one per chunk
   size_t meta_cap = 0;
   uint32_t* gsizes = nullptr;             // compression chunk sizes (scan input)
   size_t gsizes_cap = 0;
-  // single-pass compression: one status word per chunk (look-back), the
-  // 16-bit tag of the last launch's words (the array is cleared whenever the
-  // tag wraps or the array is reallocated), and the ticket counters
-  // (kQueueGroups x kQueueStride words, cleared before every launch)
-  uint64_t* status = nullptr;
-  size_t status_cap = 0;
-  uint32_t qtag = 0;
-  uint64_t* qctr = nullptr;
+  Queue q;
 };
 
 falcon_status lane_init(Lane& l);
@@ -79,11 +82,8 @@ struct PipeLane {
 // co-resident workgroups.
 struct BatchGeom {
   int split = 1;
-  // 8-wave workgroups by default: the float32 kernels then run 6 waves per
-  // SIMD (three workgroups per CU), the float64 ones 4, as with 16
-  int nw = falcon_dev::kCompressWaves32;
+  int nw = 0;  // 0: as for one series (queue_waves)
   int grid_pct = 100;
-  int form = 0;  // compression: 0 two passes (static striding), 1 single pass (work queue, look-back)
 };
 
 // Where a batch's series sit in launch-chunk space (float64 series first).
@@ -108,17 +108,14 @@ struct BatchScratch {
   size_t offsets_cap = 0;
   uint64_t* tiles = nullptr;
   size_t tiles_cap = 0;
-  uint32_t* sizes = nullptr;     // decompression: gathered chunk sizes; compression: chunk sizes
+  uint32_t* sizes = nullptr;     // decompression: gathered chunk sizes
   size_t sizes_cap = 0;
-  falcon_dev::ChunkMeta* meta = nullptr;  // compression size pass results
-  size_t meta_cap = 0;
-  falcon_dev::Ctl* ctl = nullptr;
+  falcon_dev::Ctl* ctl = nullptr; // pinned host memory (error words)
   uint64_t* lens = nullptr;      // device stream lengths (compression)
   size_t lens_cap = 0;
   uint64_t* h_lens = nullptr;    // pinned: lengths, then the error word
   size_t h_lens_cap = 0;
-  uint64_t* status = nullptr;    // single-pass compression: ticket counters, then one status word per chunk
-  size_t status_cap = 0;
+  Queue q;
 };
 
 }  // namespace falcon_host
@@ -126,7 +123,6 @@ struct BatchScratch {
 struct falcon_ctx {
   int device = 0;
   unsigned opt_flags = 0;   // FALCON_OPT_* of falcon_create
-  int compress_form = 0;    // falcon_compress_form of falcon_compress
   falcon_host::Lane main;
   // asynchronous device calls: every call waits (on the device) for the
   // previous one when it uses another stream, and records ev_done after its
@@ -146,22 +142,24 @@ struct falcon_ctx {
     size_t slot;
   };
   std::vector<PendingLen> pending;
-  // co-resident workgroups of each kernel: by form (1 = f32, 2 = f64,
-  // 3 = mixed) and, for compression, pass (0 single-pass, 1 size, 2 write)
-  // and workgroup size (8 or 16 waves)
-  int grid_c[4][3][2] = {};
+  // co-resident workgroups of each kernel, by form (1 = f32, 2 = f64,
+  // 3 = mixed): decompression, and compression by workgroup size (4 or 8
+  // waves)
   int grid_d[4] = {};
-  // the same for the single-pass compression kernels: [form][8 or 16 waves]
   int grid_q[4][2] = {};
   // the same for the ablation-variant compression kernels: [form][variant][pass]
   int grid_v[3][4][3] = {};
-  // events of the last FALCON_TIMED_CALLS timed calls, a ring whose slot
-  // ev_slot holds the last call: before the first kernel, after it, after
-  // the scan, after the last kernel (decompression: the first two coincide).
-  // ev_ok marks a slot whose call enqueued all four.
+  // the last FALCON_TIMED_CALLS timed calls, a ring whose slot ev_slot holds
+  // the last call.  A call is timed by events (before the first kernel, after
+  // it, after the scan, after the last kernel; decompression: the first two
+  // coincide), or by the stamps its kernel leaves in its kTimeWords of times.
+  enum Timed : uint8_t { kNotTimed, kEvents, kStamps };
   hipEvent_t ev[FALCON_TIMED_CALLS][4] = {};
-  bool ev_ok[FALCON_TIMED_CALLS] = {};
+  Timed ev_kind[FALCON_TIMED_CALLS] = {};
   int ev_slot = 0;
+  uint64_t* times = nullptr;     // device
+  uint64_t* times_host = nullptr;  // pinned, one slot
+  int tick_khz = 100000;         // rate of the stamps' clock
   // host <-> device pipeline
   // defaults measured on MI355X (4 hardware queues per process): 4 streams
   // of 2048-chunk batches beat the 16 x 4096 setting of Sec. 5.1.4 in both
@@ -186,28 +184,37 @@ namespace falcon_host {
 // on lane l (stream s).  Nothing is waited for; the stream's payload byte
 // count lands in the stream header at d_out + 24.  With timed, events
 // around the kernel feed falcon_last_kernel_ms.  variant != 0 selects an
-// ablation variant's kernels (falcon_variant).
+// ablation variant's kernels (falcon_variant).  compress_failed() afterwards
+// (once the stream has passed the launch) tells whether it gave up.
 falcon_status enqueue_compress(falcon_ctx* ctx, Lane& l, const void* d_in, uint64_t n, falcon_dtype dt, void* d_out,
-                               hipStream_t s, bool timed, int variant = 0, int form = 0, uint64_t* d_len = nullptr);
+                               hipStream_t s, bool timed, int variant = 0, uint64_t* d_len = nullptr);
+inline bool queue_failed(falcon_dev::Ctl* ctl, Queue& q) {
+  if (!ctl->qerror) return false;
+  ctl->qerror = 0;
+  q.dirty = true;
+  return true;
+}
+inline bool compress_failed(Lane& l) { return queue_failed(l.ctl, l.q); }
+// Makes q hold nchunks chunks, all words clear, in the order of stream s.
+falcon_status queue_prepare(Queue& q, uint64_t nchunks, hipStream_t s);
+void queue_free(Queue& q);
+// Wavefronts per workgroup for a compression of nchunks chunks.
+int queue_waves(uint64_t nchunks);
 constexpr size_t kLenBlock = 4096;  // stream-length words per device block of a context
 
 // Enqueues the decompression of a stream at d_in of in_len bytes holding n
 // values of type dt, into d_out.  With payload = kPayloadFromHeader the
 // stream header is read and checked on the device (against n, dt, in_len);
-// otherwise the host has checked it and payload is its byte count.  With
-// copy_error the error word is then copied into l.stage + 32, and
-// decompress_failed() afterwards (once the stream has reached that copy)
+// otherwise the host has checked it and payload is its byte count.
+// decompress_failed() afterwards (once the stream has passed the launch)
 // tells whether a chunk failed.
 constexpr uint64_t kPayloadFromHeader = ~0ull;
 falcon_status enqueue_decompress(falcon_ctx* ctx, Lane& l, const uint8_t* d_in, uint64_t in_len, uint64_t n,
-                                 falcon_dtype dt, uint64_t payload, void* d_out, hipStream_t s, bool timed,
-                                 bool copy_error = true);
-inline bool decompress_failed(const Lane& l) { return rd32(l.stage + 32) == l.epoch; }
+                                 falcon_dtype dt, uint64_t payload, void* d_out, hipStream_t s, bool timed);
+inline bool decompress_failed(const Lane& l) { return l.ctl->error == l.epoch; }
 
-
-inline int max_grid_c(const falcon_ctx* ctx, int form, int pass, int nw);
-inline int max_grid_q(const falcon_ctx* ctx, int form, int nw) { return ctx->grid_q[form][nw == 8 ? 0 : 1]; }
-inline int max_grid_d(const falcon_ctx* ctx, int form);
+inline int max_grid_q(const falcon_ctx* ctx, int form, int nw) { return ctx->grid_q[form][nw == 8 ? 1 : 0]; }
+inline int max_grid_d(const falcon_ctx* ctx, int form) { return ctx->grid_d[form]; }
 
 // Set-up of falcon_compress_noalloc on `device` (noalloc.hip): the device
 // address of its fixed scratch and its launch grids.
@@ -227,13 +234,9 @@ falcon_status batch_enqueue(const falcon_ctx* ctx, BatchScratch& b, const BatchL
                             hipStream_t s, bool upload);
 // After the run has completed: the error status, and each dst[i].out_len
 // (dst may be null; src holds the series the layout was made from).
-falcon_status batch_result(const BatchScratch& b, const BatchLayout& L, const falcon_series* src,
+falcon_status batch_result(BatchScratch& b, const BatchLayout& L, const falcon_series* src,
                            falcon_series* dst);
 void batch_free(BatchScratch& b);
 
 }  // namespace falcon_host
 
-inline int falcon_host::max_grid_c(const falcon_ctx* ctx, int form, int pass, int nw) {
-  return ctx->grid_c[form][pass][nw == 8 ? 0 : 1];
-}
-inline int falcon_host::max_grid_d(const falcon_ctx* ctx, int form) { return ctx->grid_d[form]; }

@@ -7,22 +7,33 @@
 
 namespace falcon_dev {
 
-// Control block of a launch queue: the decompression error word (receives
-// the launch epoch when a chunk fails a check), the single-pass compression
-// error word (set when a look-back gives up, which a correct run never
-// does) and the work-queue ticket counter of single-pass compression.
+// Control block of a launch queue, in pinned host memory so that the host
+// reads it without a copy: the decompression error word (receives the launch
+// epoch when a chunk fails a check) and the compression error word (set when
+// a wait for an offset gives up, which a correct run never does).
 struct Ctl {
   uint32_t error;
   uint32_t qerror;
   uint64_t pad;
 };
 
-// Single-pass compression takes chunks from kQueueGroups ticket counters,
-// each in a 128-byte line of its own (a counter is one word every
-// kQueueStride): workgroup b draws from counter b mod G and its ticket k
-// stands for launch chunk k * G + (b mod G).
-constexpr int kQueueGroups = 16;
+// Compression takes chunks from ticket counters, each in a 128-byte line of
+// its own (a counter is one word every kQueueStride): a launch in workgroups
+// of NW waves uses the first NW of kQueueGroups counters.  The lines after
+// them elect the scanning workgroup.
+constexpr int kQueueGroups = 8;
+constexpr int kRoleLines = 16;
 constexpr int kQueueStride = 16;
+constexpr int kQueueWords = kQueueStride * (kQueueGroups + 1 + kRoleLines);
+constexpr int kQueueSlack = 4096;  // size and offset words past the chunks (the scan reads ahead)
+
+// Time stamps of a timed launch, in ticks of the device's constant-rate
+// clock: words 0-2 the launch's start and, for compression, when the last
+// size and the last offset were known; then kTimeEnds lines of kTimeStride
+// words whose maximum is the launch's end.
+constexpr int kTimeStride = 16;
+constexpr int kTimeEnds = 16;
+constexpr int kTimeWords = kTimeStride * (1 + kTimeEnds);
 
 // One array to compress.  chunk0 is the global index of its first chunk in
 // the launch (prefix of the chunk counts of the series before it).
@@ -66,16 +77,14 @@ struct CompressArgs {
   ChunkMeta* meta;     // one per launch chunk, written by the size pass
   uint32_t* gsizes;    // chunk sizes by launch chunk (scan input), written by the size pass
   const uint64_t* offsets;  // exclusive prefix of gsizes, read by the write pass
-  uint32_t relative;   // 1: offsets run over all series; a series subtracts its first one
-  uint32_t qtag;       // single pass: 16-bit tag of this launch's status words (never 0)
-  // single pass (work queue and look-back): qgroups ticket counters at
-  // qctr[kQueueStride * g], all 0 at the launch's start; status holds one
-  // word per launch chunk
-  uint64_t* status;
+  // one launch (work queue and scanning workgroup): kQueueWords counters, and one
+  // size word and one offset word per chunk of the launch, all 0 at the
+  // launch's start and again at its end
   uint64_t* qctr;
+  uint32_t* qsize;
+  uint64_t* qoff;
   Ctl* ctl;
-  uint32_t qgroups;
-  uint32_t pad2;
+  uint64_t* times;     // kTimeWords, or null
 };
 
 struct DecompressArgs {
@@ -91,25 +100,25 @@ struct DecompressArgs {
   uint32_t relative;       // 1: offsets run over all series; a series subtracts its first one
 };
 
-constexpr int kCompressWaves = 16;    // default wavefronts per compression workgroup
-// The float32 passes run 6 waves per SIMD (their LDS buffer is half the
-// float64 one and their registers are held to 80), which workgroups of 8
-// waves fill (3 per CU); 16-wave workgroups would fit only one.
-constexpr int kCompressWaves32 = 8;
-constexpr int compress_waves(int dtype) { return dtype == 1 ? kCompressWaves32 : kCompressWaves; }
+// Wavefronts per workgroup of the two compression passes.  The float32
+// passes run 6 waves per SIMD (their LDS buffer is half the float64 one and
+// their registers are held to 80), which workgroups of 8 waves fill (3 per
+// CU); 16-wave workgroups would fit only one.
+constexpr int pass_waves(int dtype) { return dtype == 1 ? 8 : 16; }
 constexpr int kDecompressWaves = 4;   // wavefronts per decompression workgroup
 
 // Kernel forms: one instantiation per dtype (1 = f32, 2 = f64) and a mixed
-// one (3) that takes either dtype per series.  nw = wavefronts per
-// compression workgroup, 8 or 16.
+// one (3) that takes either dtype per series.
 constexpr int kFormMixed = 3;
-// pass 1: the size pass of compression (meta, gsizes and the series' size
-// arrays); pass 2: the write pass, after a scan of gsizes into offsets.
-hipError_t launch_compress(const CompressArgs& a, int form, int pass, int nw, int grid, hipStream_t s);
+// The two-pass compression of falcon_compress_noalloc, one dtype per launch
+// (form 1 or 2), pass_waves(form) wavefronts per workgroup.  pass 1: the
+// size pass (meta, gsizes and the stream's size array); pass 2: the write
+// pass, after a scan of gsizes into offsets.
+hipError_t launch_compress(const CompressArgs& a, int form, int pass, int grid, hipStream_t s);
 hipError_t launch_decompress(const DecompressArgs& a, int form, int grid, hipStream_t s);
-// Single-pass compression (work queue over chunks, decoupled look-back for
-// the offsets): a.status / a.qctr / a.qgroups (<= grid) / a.ctl / a.qtag
-// set, the a.qgroups counters cleared beforehand.
+// One-launch compression (work queue over chunks, a scanning workgroup for the
+// offsets, so at least two workgroups), nw = 4 or 8 wavefronts per workgroup: a.qctr, a.qsize, a.qoff,
+// a.ctl set.
 hipError_t launch_compress_queue(const CompressArgs& a, int form, int nw, int grid, hipStream_t s);
 hipError_t launch_compress_queue_f64(const CompressArgs& a, int nw, int grid, hipStream_t s);
 hipError_t launch_compress_queue_f32(const CompressArgs& a, int nw, int grid, hipStream_t s);
@@ -119,15 +128,13 @@ const void* compress_queue_kernel_f32(int nw);
 const void* compress_queue_kernel_mixed(int nw);
 int max_grid_compress_queue(int device, int form, int nw);
 // per-form entry points (one translation unit each)
-hipError_t launch_compress_f64(const CompressArgs& a, int pass, int nw, int grid, hipStream_t s);
-hipError_t launch_compress_f32(const CompressArgs& a, int pass, int nw, int grid, hipStream_t s);
-hipError_t launch_compress_mixed(const CompressArgs& a, int pass, int nw, int grid, hipStream_t s);
+hipError_t launch_compress_f64(const CompressArgs& a, int pass, int grid, hipStream_t s);
+hipError_t launch_compress_f32(const CompressArgs& a, int pass, int grid, hipStream_t s);
 hipError_t launch_decompress_f64(const DecompressArgs& a, int grid, hipStream_t s);
 hipError_t launch_decompress_f32(const DecompressArgs& a, int grid, hipStream_t s);
 hipError_t launch_decompress_mixed(const DecompressArgs& a, int grid, hipStream_t s);
-const void* compress_kernel_f64(int pass, int nw);
-const void* compress_kernel_f32(int pass, int nw);
-const void* compress_kernel_mixed(int pass, int nw);
+const void* compress_kernel_f64(int pass);
+const void* compress_kernel_f32(int pass);
 const void* decompress_kernel_f64();
 const void* decompress_kernel_f32();
 const void* decompress_kernel_mixed();
@@ -153,7 +160,7 @@ hipError_t launch_compress_variant(const CompressArgs& a, int form, int variant,
 const void* compress_variant_kernel_f64(int variant, int pass);
 const void* compress_variant_kernel_f32(int variant, int pass);
 // Largest number of co-resident workgroups of each kernel on the device.
-int max_grid_compress(int device, int form, int pass, int nw);
+int max_grid_compress(int device, int form, int pass);
 int max_grid_compress_variant(int device, int form, int variant, int pass);
 int max_grid_decompress(int device, int form);
 

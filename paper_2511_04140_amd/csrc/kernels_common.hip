@@ -39,7 +39,7 @@ __global__ __launch_bounds__(256) void k_scan_tiles(const uint32_t* sizes, uint6
       sum += v;
     }
   }
-  if (bad) __hip_atomic_store(&ctl->error, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (bad) chunk_error(ctl, epoch);
   uint64_t total;
   block_excl_scan256(sum, tmp, total);
   if (threadIdx.x == 0) tile_sum[blockIdx.x] = total;
@@ -58,7 +58,7 @@ __global__ __launch_bounds__(256) void k_scan_tile_sums(uint64_t* tile_sum, uint
     carry += total;
   }
   if (threadIdx.x == 0 && expect != ~0ull && carry != expect)
-    __hip_atomic_store(&ctl->error, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    chunk_error(ctl, epoch);
 }
 
 __global__ __launch_bounds__(256) void k_scan_apply(const uint32_t* sizes, uint64_t n, const uint64_t* tile_off,
@@ -107,7 +107,7 @@ __global__ __launch_bounds__(256) void k_batch_headers(DecompressSeries* many, u
   }
   if (!ok) {
     payload = 0;
-    __hip_atomic_store(&ctl->error, epoch, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    chunk_error(ctl, epoch);
   }
   sd.payload_bytes = payload;
 }
@@ -143,10 +143,8 @@ hipError_t launch_batch_dprep(DecompressSeries* many, uint32_t ns, uint64_t tota
   return hipGetLastError();
 }
 
-hipError_t launch_compress(const CompressArgs& a, int form, int pass, int nw, int grid, hipStream_t s) {
-  if (form == 2) return launch_compress_f64(a, pass, nw, grid, s);
-  if (form == 1) return launch_compress_f32(a, pass, nw, grid, s);
-  return launch_compress_mixed(a, pass, nw, grid, s);
+hipError_t launch_compress(const CompressArgs& a, int form, int pass, int grid, hipStream_t s) {
+  return form == 2 ? launch_compress_f64(a, pass, grid, s) : launch_compress_f32(a, pass, grid, s);
 }
 
 hipError_t launch_compress_queue(const CompressArgs& a, int form, int nw, int grid, hipStream_t s) {
@@ -198,10 +196,8 @@ static int max_grid_of(const void* fn, int device, int block) {
   return per_cu * prop.multiProcessorCount;
 }
 
-int max_grid_compress(int device, int form, int pass, int nw) {
-  const void* fn = form == 2 ? compress_kernel_f64(pass, nw)
-                             : form == 1 ? compress_kernel_f32(pass, nw) : compress_kernel_mixed(pass, nw);
-  return max_grid_of(fn, device, 64 * nw);
+int max_grid_compress(int device, int form, int pass) {
+  return max_grid_of(form == 2 ? compress_kernel_f64(pass) : compress_kernel_f32(pass), device, 64 * pass_waves(form));
 }
 
 int max_grid_compress_queue(int device, int form, int nw) {

@@ -4,15 +4,12 @@
 
 namespace falcon_dev {
 
-template <int NW>
-static hipError_t launch_nw(const CompressArgs& a, int pass, int grid, hipStream_t s) {
-  if (pass == 1) hipLaunchKernelGGL((k_compress_pass<TF32, NW, 1>), dim3(grid), dim3(64 * NW), 0, s, a);
-  else hipLaunchKernelGGL((k_compress_pass<TF32, NW, 2>), dim3(grid), dim3(64 * NW), 0, s, a);
-  return hipGetLastError();
-}
+constexpr int kPassWaves = pass_waves(1);
 
-hipError_t launch_compress_f32(const CompressArgs& a, int pass, int nw, int grid, hipStream_t s) {
-  return nw == 8 ? launch_nw<8>(a, pass, grid, s) : launch_nw<16>(a, pass, grid, s);
+hipError_t launch_compress_f32(const CompressArgs& a, int pass, int grid, hipStream_t s) {
+  if (pass == 1) hipLaunchKernelGGL((k_compress_pass<TF32, kPassWaves, 1>), dim3(grid), dim3(64 * kPassWaves), 0, s, a);
+  else hipLaunchKernelGGL((k_compress_pass<TF32, kPassWaves, 2>), dim3(grid), dim3(64 * kPassWaves), 0, s, a);
+  return hipGetLastError();
 }
 
 hipError_t launch_decompress_f32(const DecompressArgs& a, int grid, hipStream_t s) {
@@ -20,13 +17,10 @@ hipError_t launch_decompress_f32(const DecompressArgs& a, int grid, hipStream_t 
   return hipGetLastError();
 }
 
-template <int NW>
-static const void* kernel_nw(int pass) {
-  if (pass == 1) return reinterpret_cast<const void*>(&k_compress_pass<TF32, NW, 1>);
-  return reinterpret_cast<const void*>(&k_compress_pass<TF32, NW, 2>);
+const void* compress_kernel_f32(int pass) {
+  if (pass == 1) return reinterpret_cast<const void*>(&k_compress_pass<TF32, kPassWaves, 1>);
+  return reinterpret_cast<const void*>(&k_compress_pass<TF32, kPassWaves, 2>);
 }
-
-const void* compress_kernel_f32(int pass, int nw) { return nw == 8 ? kernel_nw<8>(pass) : kernel_nw<16>(pass); }
 
 template <int V>
 static const void* size_pass_variant_f32() {
@@ -48,13 +42,13 @@ const void* decompress_kernel_f32() { return reinterpret_cast<const void*>(&k_de
 
 hipError_t launch_compress_queue_f32(const CompressArgs& a, int nw, int grid, hipStream_t s) {
   if (nw == 8) hipLaunchKernelGGL((k_compress_queue<TF32, 8>), dim3(grid), dim3(64 * 8), 0, s, a);
-  else hipLaunchKernelGGL((k_compress_queue<TF32, 16>), dim3(grid), dim3(64 * 16), 0, s, a);
+  else hipLaunchKernelGGL((k_compress_queue<TF32, 4>), dim3(grid), dim3(64 * 4), 0, s, a);
   return hipGetLastError();
 }
 
 const void* compress_queue_kernel_f32(int nw) {
   return nw == 8 ? reinterpret_cast<const void*>(&k_compress_queue<TF32, 8>)
-                 : reinterpret_cast<const void*>(&k_compress_queue<TF32, 16>);
+                 : reinterpret_cast<const void*>(&k_compress_queue<TF32, 4>);
 }
 
 }  // namespace falcon_dev

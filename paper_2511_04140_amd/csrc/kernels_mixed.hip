@@ -22,41 +22,22 @@ __global__ __launch_bounds__(64 * kWavesD) __attribute__((amdgpu_waves_per_eu(4)
                   });
 }
 
-template <int NW>
-static hipError_t launch_nw(const CompressArgs& a, int pass, int grid, hipStream_t s) {
-  if (pass == 1) hipLaunchKernelGGL((k_compress_pass_mixed<NW, 1>), dim3(grid), dim3(64 * NW), 0, s, a);
-  else hipLaunchKernelGGL((k_compress_pass_mixed<NW, 2>), dim3(grid), dim3(64 * NW), 0, s, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_compress_mixed(const CompressArgs& a, int pass, int nw, int grid, hipStream_t s) {
-  return nw == 8 ? launch_nw<8>(a, pass, grid, s) : launch_nw<16>(a, pass, grid, s);
-}
-
 hipError_t launch_decompress_mixed(const DecompressArgs& a, int grid, hipStream_t s) {
   hipLaunchKernelGGL(k_decompress_mixed, dim3(grid), dim3(64 * kWavesD), 0, s, a);
   return hipGetLastError();
 }
 
-template <int NW>
-static const void* kernel_nw(int pass) {
-  if (pass == 1) return reinterpret_cast<const void*>(&k_compress_pass_mixed<NW, 1>);
-  return reinterpret_cast<const void*>(&k_compress_pass_mixed<NW, 2>);
-}
-
-const void* compress_kernel_mixed(int pass, int nw) { return nw == 8 ? kernel_nw<8>(pass) : kernel_nw<16>(pass); }
-
 const void* decompress_kernel_mixed() { return reinterpret_cast<const void*>(&k_decompress_mixed); }
 
 hipError_t launch_compress_queue_mixed(const CompressArgs& a, int nw, int grid, hipStream_t s) {
   if (nw == 8) hipLaunchKernelGGL((k_compress_queue_mixed<8>), dim3(grid), dim3(64 * 8), 0, s, a);
-  else hipLaunchKernelGGL((k_compress_queue_mixed<16>), dim3(grid), dim3(64 * 16), 0, s, a);
+  else hipLaunchKernelGGL((k_compress_queue_mixed<4>), dim3(grid), dim3(64 * 4), 0, s, a);
   return hipGetLastError();
 }
 
 const void* compress_queue_kernel_mixed(int nw) {
   return nw == 8 ? reinterpret_cast<const void*>(&k_compress_queue_mixed<8>)
-                 : reinterpret_cast<const void*>(&k_compress_queue_mixed<16>);
+                 : reinterpret_cast<const void*>(&k_compress_queue_mixed<4>);
 }
 
 }  // namespace falcon_dev

@@ -60,7 +60,7 @@ falcon_status setup(int dev, DeviceState** out) {
     d.ptr = static_cast<uint8_t*>(p);
     for (int form = 1; form <= 2; ++form)
       for (int pass = 1; pass <= 2; ++pass)
-        d.grid[form][pass] = max_grid_compress(dev, form, pass, compress_waves(form));
+        d.grid[form][pass] = max_grid_compress(dev, form, pass);
     d.ready = true;
   }
   *out = &d;
@@ -122,21 +122,20 @@ extern "C" falcon_status falcon_compress_noalloc(const void* d_in, size_t n, fal
   a.meta = meta;
   a.gsizes = sizes;
   a.offsets = offsets;
-  a.relative = 0;
   // every scratch word is written before it is read: the size pass writes
   // meta and sizes, the scan the tile sums and offsets; the control block
   // takes an error word only for a chunk size outside [0, 2^32), which never
   // happens, so nothing needs clearing between calls
-  const int nw = compress_waves((int)dt);
+  const int nw = pass_waves((int)dt);
   const int g1 = grid_of(d->grid[dt][1], nc, nw), g2 = grid_of(d->grid[dt][2], nc, nw);
   if (nc) {
     a.total_waves = (uint32_t)(g1 * nw);
-    if ((st = dev_err(launch_compress(a, (int)dt, 1, nw, g1, s))) != FALCON_OK) return st;
+    if ((st = dev_err(launch_compress(a, (int)dt, 1, g1, s))) != FALCON_OK) return st;
     if ((st = dev_err(launch_scan_sizes(sizes, nc, 0, ~0u, ~0ull, tiles, offsets, ctl, 1, s))) != FALCON_OK)
       return st;
   }
   a.total_waves = (uint32_t)(g2 * nw);
-  if ((st = dev_err(launch_compress(a, (int)dt, 2, nw, g2, s))) != FALCON_OK) return st;
+  if ((st = dev_err(launch_compress(a, (int)dt, 2, g2, s))) != FALCON_OK) return st;
   // an empty input has no chunk to write its length
   if (n == 0 && d_out_len)
     return dev_err(launch_fill_u64(reinterpret_cast<uint64_t*>(d_out_len), 1, 32, s));

@@ -186,6 +186,7 @@ void finish_placement(const PipeLane& p, const CompressJob& j) {
 }
 
 falcon_status read_cs(PipeLane& p, const CompressJob& j) {
+  if (compress_failed(p.lane)) return FALCON_ERR_DEVICE;
   p.cs = rd64(p.lane.stage + 40);
   return p.cs > p.nchunks * max_chunk_bytes(j.dt) ? FALCON_ERR_DEVICE : FALCON_OK;
 }
@@ -315,6 +316,7 @@ falcon_status compress_pre_allocation(falcon_ctx* ctx, const CompressJob& j, uin
         const int r = poll(p);
         if (r < 0) return FALCON_ERR_DEVICE;
         if (r == 0) continue;
+        if (compress_failed(p.lane)) return FALCON_ERR_DEVICE;
         ++done;
         p.state = kIdle;
         moved = true;
