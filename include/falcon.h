@@ -347,8 +347,8 @@ falcon_status falcon_decompress_each(falcon_ctx* ctx, falcon_series* s, size_t c
 falcon_status falcon_compress_batch(falcon_ctx* ctx, falcon_series* s, size_t count, void* stream);
 
 /* Decompresses count streams in one launch sequence (Sec. 4 per series):
- * headers checked on the device against the descriptors, one scan over the
- * sizes of all series, one decoding launch.  Errors as falcon_decompress;
+ * headers checked on the device against the descriptors, payload offsets from
+ * the streams' sizes, one decoding launch a dtype.  Errors as falcon_decompress;
  * FALCON_ERR_CORRUPT_STREAM if any series fails. */
 falcon_status falcon_decompress_batch(falcon_ctx* ctx, falcon_series* s, size_t count, void* stream);
 
@@ -447,16 +447,18 @@ falcon_status falcon_stream_info(const void* h_hdr, size_t len, size_t* n, falco
 
 /* Device time in milliseconds of the last falcon_compress /
  * falcon_compress_variant or falcon_decompress / falcon_decompress_n, all its
- * launches together; waits for that call's work.  falcon_compress is timed by
- * stamps of the device's clock that its launch leaves, the others by HIP
- * events recorded on the launch stream.  Intended for roofline accounting;
+ * launches together; waits for that call's work.  Calls are timed by stamps
+ * of the device's clock that their launches leave, the ablation variants by
+ * HIP events recorded on the launch stream.  Intended for roofline accounting;
  * FALCON_ERR_INVALID_ARG if no call has run yet. */
 falcon_status falcon_last_kernel_ms(falcon_ctx* ctx, float* ms);
 
 /* The stages of that call separately, ms[0..2].  falcon_compress: until the
  * last chunk's size was known, until the last offset was, until the launch's
  * end (most payloads are written during the first); falcon_compress_variant:
- * size pass, scan, write pass; decompression: 0, scan, decoding kernel. */
+ * size pass, scan, write pass; decompression: 0, until the first chunk's
+ * offset was known (with the scan launch before it, from 4,097 chunks on),
+ * the decoding from there. */
 falcon_status falcon_last_stage_ms(falcon_ctx* ctx, float* ms);
 
 /* The context keeps the times of its last FALCON_TIMED_CALLS timed calls

@@ -43,6 +43,7 @@ falcon_status lane_init(Lane& l) {
 void lane_free(Lane& l) {
   if (l.stream) (void)hipStreamSynchronize(l.stream);
   if (l.offsets) (void)hipFree(l.offsets);
+  if (l.local) (void)hipFree(l.local);
   if (l.tiles) (void)hipFree(l.tiles);
   if (l.meta) (void)hipFree(l.meta);
   if (l.gsizes) (void)hipFree(l.gsizes);
@@ -69,18 +70,6 @@ falcon_status grow_raw(P** arr, size_t* cap, uint64_t n, hipStream_t s) {
   *cap = 0;
   if (hipMalloc(reinterpret_cast<void**>(arr), c * sizeof(P)) != hipSuccess) return FALCON_ERR_OUT_OF_MEMORY;
   *cap = c;
-  return FALCON_OK;
-}
-
-// Makes the lane's arrays hold nchunks chunk offsets and ntiles scan tile
-// sums, and advances the launch epoch (the value a failing decompression
-// launch leaves in the error word).
-falcon_status prepare_launch(Lane& l, uint64_t nchunks, uint64_t ntiles, hipStream_t s) {
-  falcon_status st = grow_raw(&l.offsets, &l.offsets_cap, nchunks, s);
-  if (st == FALCON_OK) st = grow_raw(&l.tiles, &l.tiles_cap, ntiles, s);
-  if (st != FALCON_OK) return st;
-  l.epoch += 1;
-  if (l.epoch == 0) l.epoch = 1;
   return FALCON_OK;
 }
 
@@ -171,7 +160,8 @@ falcon_status enqueue_compress(falcon_ctx* ctx, Lane& l, const void* d_in, uint6
   }
   hipEvent_t* ev = ctx->ev[ctx->ev_slot];
   auto mark = [&](int i) { return timed ? dev_err(hipEventRecord(ev[i], s)) : FALCON_OK; };
-  st = prepare_launch(l, nc ? nc : 1, scan_tiles(nc) + 1, s);
+  st = grow_raw(&l.offsets, &l.offsets_cap, nc ? nc : 1, s);
+  if (st == FALCON_OK) st = grow_raw(&l.tiles, &l.tiles_cap, scan_tiles(nc) + 1, s);
   if (st == FALCON_OK) st = grow_raw(&l.meta, &l.meta_cap, nc ? nc : 1, s);
   if (st == FALCON_OK) st = grow_raw(&l.gsizes, &l.gsizes_cap, nc ? nc : 1, s);
   if (st != FALCON_OK) return st;
@@ -187,9 +177,7 @@ falcon_status enqueue_compress(falcon_ctx* ctx, Lane& l, const void* d_in, uint6
   if ((st = mark(0)) != FALCON_OK) return st;
   if (nc && (st = launch(1)) != FALCON_OK) return st;
   if ((st = mark(1)) != FALCON_OK) return st;
-  if (nc && (st = dev_err(launch_scan_sizes(l.gsizes, nc, 0, ~0u, ~0ull, l.tiles, l.offsets, l.ctl, l.epoch, s))) !=
-                FALCON_OK)
-    return st;
+  if (nc && (st = dev_err(launch_scan_sizes(l.gsizes, nc, l.tiles, l.offsets, s))) != FALCON_OK) return st;
   if ((st = mark(2)) != FALCON_OK) return st;
   if ((st = launch(2)) != FALCON_OK) return st;
   if ((st = mark(3)) != FALCON_OK) return st;
@@ -200,21 +188,15 @@ falcon_status enqueue_compress(falcon_ctx* ctx, Lane& l, const void* d_in, uint6
 falcon_status enqueue_decompress(falcon_ctx* ctx, Lane& l, const uint8_t* d_in, uint64_t in_len, uint64_t n,
                                  falcon_dtype dt, uint64_t payload, void* d_out, hipStream_t s, bool timed) {
   const uint64_t nc = chunks_of(n);
-  falcon_status st = prepare_launch(l, nc, scan_tiles(nc) + 1, s);
-  if (st != FALCON_OK) return st;
-  // chunk offsets: exclusive prefix of the size array (which the scan also
-  // checks: every size in [lo, hi], and their sum equal to the payload byte
-  // count when the host knows it; otherwise the last chunk's check does that)
-  const uint32_t lo = dt == FALCON_FLOAT64 ? 11u : 7u;
-  const uint32_t hi = (uint32_t)max_chunk_bytes(dt);
-  if (timed) begin_timed(ctx);
-  hipEvent_t* ev = ctx->ev[ctx->ev_slot];
-  auto mark = [&](int i) { return timed ? dev_err(hipEventRecord(ev[i], s)) : FALCON_OK; };
-  if ((st = mark(0)) != FALCON_OK || (st = mark(1)) != FALCON_OK) return st;
-  if ((st = dev_err(launch_scan_sizes(reinterpret_cast<const uint32_t*>(d_in + 32), nc, lo, hi,
-                                      payload == kPayloadFromHeader ? ~0ull : payload, l.tiles, l.offsets, l.ctl,
-                                      l.epoch, s))) != FALCON_OK)
+  falcon_status st = FALCON_OK;
+  const bool direct = nc <= kDirectChunks;
+  if (!direct && ((st = grow_raw(&l.local, &l.local_cap, nc, s)) != FALCON_OK ||
+                  (st = grow_raw(&l.tiles, &l.tiles_cap, scan_tiles(nc), s)) != FALCON_OK))
     return st;
+  // the value a failing launch leaves in the error word
+  l.epoch += 1;
+  if (l.epoch == 0) l.epoch = 1;
+  if (timed) begin_timed(ctx);
   DecompressArgs a{};
   a.one.in = d_in;
   a.one.out = static_cast<uint8_t*>(d_out);
@@ -226,16 +208,14 @@ falcon_status enqueue_decompress(falcon_ctx* ctx, Lane& l, const uint8_t* d_in, 
   a.many = nullptr;
   a.nseries = 1;
   a.total_chunks = nc;
-  a.offsets = l.offsets;
   a.ctl = l.ctl;
   a.epoch = l.epoch;
-  a.relative = 0;
+  a.times = timed ? ctx->times + (size_t)ctx->ev_slot * kTimeWords : nullptr;
+  if (!direct && (st = dev_err(launch_scan_local(&a, nc, l.local, l.tiles, s))) != FALCON_OK) return st;
   const int grid = grid_for(max_grid_d(ctx, dt), nc, kDecompressWaves);
   a.total_waves = (uint32_t)(grid * kDecompressWaves);
-  if ((st = mark(2)) != FALCON_OK) return st;
-  if ((st = dev_err(launch_decompress(a, (int)dt, grid, s))) != FALCON_OK) return st;
-  if ((st = mark(3)) != FALCON_OK) return st;
-  if (timed) ctx->ev_kind[ctx->ev_slot] = falcon_ctx::kEvents;
+  if ((st = dev_err(launch_decompress(a, (int)dt, direct, grid, s))) != FALCON_OK) return st;
+  if (timed) ctx->ev_kind[ctx->ev_slot] = falcon_ctx::kStamps;
   return FALCON_OK;
 }
 

@@ -116,6 +116,7 @@ falcon_status batch_layout(BatchScratch& b, int op, const falcon_series* s, size
         c.out = static_cast<uint8_t*>(d.d_out);
         c.n = d.n;
         c.chunk0 = t;
+        c.payload_bytes = kPayloadFromHeader;
         c.in_len = d.in_len;
         c.dtype = (uint32_t)d.dtype;
         c.idx = (uint32_t)i;
@@ -130,17 +131,17 @@ falcon_status batch_layout(BatchScratch& b, int op, const falcon_series* s, size
         L.has32 |= nc > 0;
       }
       t += nc;
+      L.longest = std::max(L.longest, nc);
     }
   }
   L.total = t;
-  const size_t gwords = scan_tiles(t) + 1;
   if ((r = grow(&b.many, &b.many_cap, L.desc_bytes, 1, false, st)) != FALCON_OK ||
-      (r = grow(&b.offsets, &b.offsets_cap, t ? t : 1, 8, false, st)) != FALCON_OK ||
-      (r = grow(&b.tiles, &b.tiles_cap, gwords, 8, false, st)) != FALCON_OK ||
       (r = grow(&b.lens, &b.lens_cap, count, 8, false, st)) != FALCON_OK ||
       (r = grow(&b.h_lens, &b.h_lens_cap, count, 8, true, st)) != FALCON_OK)
     return r;
-  if (op == FALCON_OP_DECOMPRESS && (r = grow(&b.sizes, &b.sizes_cap, t ? t : 1, 4, false, st)) != FALCON_OK)
+  if (op == FALCON_OP_DECOMPRESS && L.longest > kDirectChunks &&
+      ((r = grow(&b.local, &b.local_cap, t, 4, false, st)) != FALCON_OK ||
+       (r = grow(&b.tiles, &b.tiles_cap, scan_tiles(t), 8, false, st)) != FALCON_OK))
     return r;
   if (op == FALCON_OP_COMPRESS && (r = queue_prepare(b.q, t ? t : 1, st)) != FALCON_OK) return r;
   if (!b.ctl) {
@@ -187,27 +188,21 @@ falcon_status batch_enqueue(const falcon_ctx* ctx, BatchScratch& b, const BatchL
     }
     return dev_err(hipMemcpyAsync(b.h_lens, b.lens, L.count * 8, hipMemcpyDeviceToHost, s));
   }
-  // decompression: headers and sizes, one scan over all chunks, kernels
-  DecompressSeries* many = static_cast<DecompressSeries*>(b.many);
-  if ((st = dev_err(launch_batch_dprep(many, (uint32_t)L.count, L.total, b.sizes, b.ctl, kBatchEpoch, s))) !=
-          FALCON_OK ||
-      (st = dev_err(launch_scan_sizes(b.sizes, L.total, 7, (uint32_t)kF64Chunk, ~0ull, b.tiles, b.offsets, b.ctl,
-                                      kBatchEpoch, s))) != FALCON_OK)
-    return st;
+  if (np == 0) parts[np++] = {2, 0, 0};  // only empty series: the launch checks their headers
+  DecompressArgs a{};
+  a.one = L.one_d;
+  a.many = static_cast<const DecompressSeries*>(b.many);
+  a.nseries = (uint32_t)L.count;
+  a.ctl = b.ctl;
+  a.epoch = kBatchEpoch;
+  const bool direct = L.longest <= kDirectChunks;
+  if (!direct && (st = dev_err(launch_scan_local(&a, L.total, b.local, b.tiles, s))) != FALCON_OK) return st;
   for (int i = 0; i < np; ++i) {
-    DecompressArgs a{};
-    a.one = L.one_d;
-    a.many = many;
-    a.nseries = (uint32_t)L.count;
     a.total_chunks = parts[i].chunks;
     a.t0 = parts[i].t0;
-    a.offsets = b.offsets;
-    a.ctl = b.ctl;
-    a.epoch = kBatchEpoch;
-    a.relative = 1;
     const int grid = grid_of(max_grid_d(ctx, parts[i].form), g, parts[i].chunks, kDecompressWaves);
     a.total_waves = (uint32_t)(grid * kDecompressWaves);
-    if ((st = dev_err(launch_decompress(a, parts[i].form, grid, s))) != FALCON_OK) return st;
+    if ((st = dev_err(launch_decompress(a, parts[i].form, direct, grid, s))) != FALCON_OK) return st;
   }
   return FALCON_OK;
 }
@@ -226,9 +221,8 @@ falcon_status batch_result(BatchScratch& b, const BatchLayout& L, const falcon_s
 void batch_free(BatchScratch& b) {
   if (b.many) (void)hipFree(b.many);
   if (b.h_desc) (void)hipHostFree(b.h_desc);
-  if (b.offsets) (void)hipFree(b.offsets);
   if (b.tiles) (void)hipFree(b.tiles);
-  if (b.sizes) (void)hipFree(b.sizes);
+  if (b.local) (void)hipFree(b.local);
   if (b.ctl) (void)hipHostFree(b.ctl);
   if (b.lens) (void)hipFree(b.lens);
   if (b.h_lens) (void)hipHostFree(b.h_lens);

@@ -47,7 +47,9 @@ struct Queue {
 // different lanes may run concurrently.
 struct Lane {
   hipStream_t stream = nullptr;
-  uint64_t* offsets = nullptr;  // one per chunk: exclusive prefix of the chunk sizes
+  uint32_t* local = nullptr;    // decompression: each chunk's offset inside its scan tile
+  size_t local_cap = 0;
+  uint64_t* offsets = nullptr;  // two-pass compression: exclusive prefix of the chunk sizes
   size_t offsets_cap = 0;
   uint64_t* tiles = nullptr;    // scan tile sums
   size_t tiles_cap = 0;
@@ -90,7 +92,7 @@ struct BatchGeom {
 struct BatchLayout {
   int op = 0;
   size_t count = 0;
-  uint64_t total = 0, t64 = 0;
+  uint64_t total = 0, t64 = 0, longest = 0;
   bool has64 = false, has32 = false;
   falcon_dev::CompressSeries one_c{};
   falcon_dev::DecompressSeries one_d{};
@@ -104,12 +106,11 @@ struct BatchScratch {
   size_t many_cap = 0;
   uint8_t* h_desc = nullptr;     // pinned host copy of the descriptors
   size_t h_desc_cap = 0;
-  uint64_t* offsets = nullptr;   // chunk offsets (scan of all chunk sizes)
-  size_t offsets_cap = 0;
+  // decompression, unless its launches are direct
+  uint32_t* local = nullptr;     // each chunk's offset inside its scan tile
+  size_t local_cap = 0;
   uint64_t* tiles = nullptr;
   size_t tiles_cap = 0;
-  uint32_t* sizes = nullptr;     // decompression: gathered chunk sizes
-  size_t sizes_cap = 0;
   falcon_dev::Ctl* ctl = nullptr; // pinned host memory (error words)
   uint64_t* lens = nullptr;      // device stream lengths (compression)
   size_t lens_cap = 0;
@@ -150,9 +151,9 @@ struct falcon_ctx {
   // the same for the ablation-variant compression kernels: [form][variant][pass]
   int grid_v[3][4][3] = {};
   // the last FALCON_TIMED_CALLS timed calls, a ring whose slot ev_slot holds
-  // the last call.  A call is timed by events (before the first kernel, after
-  // it, after the scan, after the last kernel; decompression: the first two
-  // coincide), or by the stamps its kernel leaves in its kTimeWords of times.
+  // the last call.  A call is timed by the stamps its kernels leave in its
+  // kTimeWords of times, an ablation variant by events (before the first
+  // kernel, after it, after the scan, after the last kernel).
   enum Timed : uint8_t { kNotTimed, kEvents, kStamps };
   hipEvent_t ev[FALCON_TIMED_CALLS][4] = {};
   Timed ev_kind[FALCON_TIMED_CALLS] = {};

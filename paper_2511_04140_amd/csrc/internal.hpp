@@ -51,8 +51,8 @@ struct DecompressSeries {
   uint8_t* out;
   uint64_t n;
   uint64_t chunk0;
-  uint64_t payload_bytes;  // batch launches: filled on the device from the stream header
-  uint64_t in_len;         // stream bytes (batch launches)
+  uint64_t payload_bytes;  // ~0: read from the stream header on the device
+  uint64_t in_len;         // stream bytes
   uint32_t dtype;
   uint32_t idx;
 };
@@ -94,11 +94,26 @@ struct DecompressArgs {
   uint32_t total_waves;
   uint64_t total_chunks;
   uint64_t t0;
-  const uint64_t* offsets;  // chunk offsets (exclusive prefix of the sizes)
-  Ctl* ctl;
+  // offsets of the chunks, unless the launch adds them up itself (direct):
+  // each launch chunk's inside its tile, and the tiles' sums (tiles_scanned:
+  // the sums of the tiles before)
+  const uint32_t* local;
+  const uint64_t* tiles;
+  uint32_t tiles_scanned;
+  uint32_t ntiles;
   uint32_t epoch;
-  uint32_t relative;       // 1: offsets run over all series; a series subtracts its first one
+  uint32_t pad;
+  Ctl* ctl;
+  uint64_t* times;     // kTimeWords, or null
 };
+
+// A decompression launch adds up its chunks' offsets itself (direct) when no
+// series is longer than this many chunks; else k_scan_local runs before it.
+// One float64 series, direct against scanned: 1 chunk 9.6 / 14.3 us, 1,024
+// chunks 12.2 / 16.7, 2,047 chunks 14.9 / 18.8, 4,093 chunks 28.0 / 27.6.
+// Plans of series of 1-360 chunks: 200 of them 57 / 67 us, 2,000 309 / 323.
+constexpr uint64_t kDirectChunks = 4096;
+constexpr int kScanTile = 4096;  // chunk sizes per workgroup of the scans
 
 // Wavefronts per workgroup of the two compression passes.  The float32
 // passes run 6 waves per SIMD (their LDS buffer is half the float64 one and
@@ -115,7 +130,9 @@ constexpr int kFormMixed = 3;
 // size pass (meta, gsizes and the stream's size array); pass 2: the write
 // pass, after a scan of gsizes into offsets.
 hipError_t launch_compress(const CompressArgs& a, int form, int pass, int grid, hipStream_t s);
-hipError_t launch_decompress(const DecompressArgs& a, int form, int grid, hipStream_t s);
+// direct: no series of the launch has more than kDirectChunks chunks, and
+// a.local and a.tiles are not used.
+hipError_t launch_decompress(const DecompressArgs& a, int form, bool direct, int grid, hipStream_t s);
 // One-launch compression (work queue over chunks, a scanning workgroup for the
 // offsets, so at least two workgroups), nw = 4 or 8 wavefronts per workgroup: a.qctr, a.qsize, a.qoff,
 // a.ctl set.
@@ -130,28 +147,24 @@ int max_grid_compress_queue(int device, int form, int nw);
 // per-form entry points (one translation unit each)
 hipError_t launch_compress_f64(const CompressArgs& a, int pass, int grid, hipStream_t s);
 hipError_t launch_compress_f32(const CompressArgs& a, int pass, int grid, hipStream_t s);
-hipError_t launch_decompress_f64(const DecompressArgs& a, int grid, hipStream_t s);
-hipError_t launch_decompress_f32(const DecompressArgs& a, int grid, hipStream_t s);
-hipError_t launch_decompress_mixed(const DecompressArgs& a, int grid, hipStream_t s);
+hipError_t launch_decompress_f64(const DecompressArgs& a, bool direct, int grid, hipStream_t s);
+hipError_t launch_decompress_f32(const DecompressArgs& a, bool direct, int grid, hipStream_t s);
+hipError_t launch_decompress_mixed(const DecompressArgs& a, bool direct, int grid, hipStream_t s);
 const void* compress_kernel_f64(int pass);
 const void* compress_kernel_f32(int pass);
 const void* decompress_kernel_f64();
 const void* decompress_kernel_f32();
 const void* decompress_kernel_mixed();
 hipError_t launch_fill_u64(uint64_t* p, size_t n, uint64_t v, hipStream_t s);
-// Exclusive prefix of n chunk sizes into offsets; sizes outside [lo, hi] or
-// a total other than expect (unless expect is UINT64_MAX) store the epoch in
-// ctl->error.  tile_tmp holds
+// Exclusive prefix of n chunk sizes into offsets; tile_tmp holds
 // scan_tiles(n) words.
-hipError_t launch_scan_sizes(const uint32_t* sizes, uint64_t n, uint32_t lo, uint32_t hi, uint64_t expect,
-                             uint64_t* tile_tmp, uint64_t* offsets, Ctl* ctl, uint32_t epoch, hipStream_t s);
+hipError_t launch_scan_sizes(const uint32_t* sizes, uint64_t n, uint64_t* tile_tmp, uint64_t* offsets, hipStream_t s);
 uint64_t scan_tiles(uint64_t n);
-// Batch decompression, before the scan: reads every series' stream header
-// on the device, checks it against the descriptor (value count, dtype,
-// lengths) and stores its payload byte count in the descriptor; then copies
-// every series' chunk sizes into one array indexed by launch chunk.
-hipError_t launch_batch_dprep(DecompressSeries* many, uint32_t ns, uint64_t total_chunks, uint32_t* sizes_out,
-                              Ctl* ctl, uint32_t epoch, hipStream_t s);
+// Decompression, before launches that are not direct: every launch chunk's
+// offset inside its tile into a->local (total_chunks words) and the tile sums
+// into a->tiles (scan_tiles(total_chunks) words), from the sizes at the
+// streams of a->one or a->many; sets a->ntiles and a->tiles_scanned.
+hipError_t launch_scan_local(DecompressArgs* a, uint64_t total_chunks, uint32_t* local, uint64_t* tiles, hipStream_t s);
 // Compression under an ablation variant of Sec. 5.4.2 (variant 1: Elf's
 // decimal places, 2: every row sparse, 3: every row dense), one dtype per
 // launch (form 1 or 2), kVariantWaves wavefronts per workgroup.

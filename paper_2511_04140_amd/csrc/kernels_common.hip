@@ -5,13 +5,11 @@
 namespace falcon_dev {
 
 // ---------------------------------------------------------------------------
-// Prefix sum of a chunk size array into chunk offsets (decompression, Sec. 4:
-// the size array is scanned into the offset array).  Three small kernels over
-// tiles of kScanTile sizes: tile sums, a scan of the tile sums (which also
-// checks the total against the payload byte count), and the per-tile scan.
-// Sizes outside [lo, hi] set the error word.
+// Prefix sum of a chunk size array into chunk offsets (two-pass compression).
+// Three small kernels over tiles of kScanTile sizes: tile sums, a scan of the
+// tile sums, and the per-tile scan.
 // ---------------------------------------------------------------------------
-constexpr int kScanTile = 4096;  // 256 threads x 16 sizes
+static_assert(kScanTile == 256 * 16, "256 threads x 16 sizes");
 
 __device__ __forceinline__ uint64_t block_excl_scan256(uint64_t v, uint64_t* tmp, uint64_t& total) {
   // tmp: 4 words of LDS (one per wave)
@@ -26,27 +24,18 @@ __device__ __forceinline__ uint64_t block_excl_scan256(uint64_t v, uint64_t* tmp
   return before + incl - v;
 }
 
-__global__ __launch_bounds__(256) void k_scan_tiles(const uint32_t* sizes, uint64_t n, uint32_t lo, uint32_t hi,
-                                                    uint64_t* tile_sum, Ctl* ctl, uint32_t epoch) {
+__global__ __launch_bounds__(256) void k_scan_tiles(const uint32_t* sizes, uint64_t n, uint64_t* tile_sum) {
   __shared__ uint64_t tmp[4];
   const uint64_t base = (uint64_t)blockIdx.x * kScanTile + threadIdx.x * 16;
   uint64_t sum = 0;
-  bool bad = false;
-  for (int k = 0; k < 16; ++k) {
-    if (base + k < n) {
-      const uint32_t v = sizes[base + k];
-      bad |= v < lo || v > hi;
-      sum += v;
-    }
-  }
-  if (bad) chunk_error(ctl, epoch);
+  for (int k = 0; k < 16; ++k)
+    if (base + k < n) sum += sizes[base + k];
   uint64_t total;
   block_excl_scan256(sum, tmp, total);
   if (threadIdx.x == 0) tile_sum[blockIdx.x] = total;
 }
 
-__global__ __launch_bounds__(256) void k_scan_tile_sums(uint64_t* tile_sum, uint64_t ntiles, uint64_t expect,
-                                                        Ctl* ctl, uint32_t epoch) {
+__global__ __launch_bounds__(256) void k_scan_tile_sums(uint64_t* tile_sum, uint64_t ntiles) {
   __shared__ uint64_t tmp[4];
   uint64_t carry = 0;
   for (uint64_t b0 = 0; b0 < ntiles; b0 += 256) {
@@ -57,8 +46,6 @@ __global__ __launch_bounds__(256) void k_scan_tile_sums(uint64_t* tile_sum, uint
     if (i < ntiles) tile_sum[i] = carry + ex;  // becomes the tile's offset
     carry += total;
   }
-  if (threadIdx.x == 0 && expect != ~0ull && carry != expect)
-    chunk_error(ctl, epoch);
 }
 
 __global__ __launch_bounds__(256) void k_scan_apply(const uint32_t* sizes, uint64_t n, const uint64_t* tile_off,
@@ -85,61 +72,65 @@ __global__ void k_fill_u64(uint64_t* p, size_t n, uint64_t v) {
 }
 
 // ---------------------------------------------------------------------------
-// Batch decompression preparation.
+// Decompression's scan (Sec. 4: the size array is scanned into the offset
+// array), as far as one launch gets without waiting: offsets inside each tile
+// and the tile sums.  The decoder's waves add the tile sums themselves, which
+// saves two launches: 43 -> 14 us before the decoder on 261,889 chunks.
 // ---------------------------------------------------------------------------
-// One thread per series: checks the stream header against the descriptor
-// and stores the payload byte count.  A failing series gets payload 0, so
-// that every one of its chunks fails its bounds check without reading.
-__global__ __launch_bounds__(256) void k_batch_headers(DecompressSeries* many, uint32_t ns, Ctl* ctl,
-                                                       uint32_t epoch) {
-  const uint32_t i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= ns) return;
-  DecompressSeries& sd = many[i];
-  const uint64_t nc = (sd.n + kChunk - 1) / kChunk;
-  const uint32_t* h = reinterpret_cast<const uint32_t*>(sd.in);
-  uint64_t payload = 0;
-  bool ok = sd.in_len >= kHdrBytes + 4 * nc;  // also checked on the host
-  if (ok) {
-    ok = h[0] == 0x4E434C46u && h[1] == (1u | (sd.dtype << 8)) && h[2] == (uint32_t)kChunk && h[3] == 0 &&
-         ((uint64_t)h[4] | ((uint64_t)h[5] << 32)) == sd.n;
-    payload = (uint64_t)h[6] | ((uint64_t)h[7] << 32);
-    ok = ok && payload <= sd.in_len - kHdrBytes - 4 * nc && (sd.n != 0 || payload == 0);
+__global__ __launch_bounds__(256) void k_scan_local(DecompressSeries one, const DecompressSeries* many, uint32_t ns,
+                                                    uint64_t n, uint32_t* local, uint64_t* tile_sum,
+                                                    uint64_t* times) {
+  __shared__ uint64_t tmp[4];
+  if (times && blockIdx.x == 0 && threadIdx.x == 0) times[0] = times[1] = now_ticks();
+  const uint64_t base = (uint64_t)blockIdx.x * kScanTile + threadIdx.x * 16;
+  uint32_t v[16];
+  uint64_t sum = 0;
+  if (base < n) {
+    // a thread's chunks lie in one series, or in a few in a row
+    uint32_t i = many ? find_index(many, ns, base) : 0;
+    DecompressSeries sd = one;
+    uint64_t end = n;
+    auto enter = [&]() {
+      sd = many[i];
+      end = i + 1 < ns ? many[i + 1].chunk0 : n;
+    };
+    if (many) enter();
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      const uint64_t t = base + k;
+      v[k] = 0;
+      if (t < n) {
+        while (t >= end) {
+          ++i;
+          enter();
+        }
+        v[k] = reinterpret_cast<const uint32_t*>(sd.in + kHdrBytes)[t - sd.chunk0];
+        sum += v[k];
+      }
+    }
   }
-  if (!ok) {
-    payload = 0;
-    chunk_error(ctl, epoch);
+  uint64_t total;
+  uint32_t run = (uint32_t)block_excl_scan256(sum, tmp, total);
+  if (base < n) {
+#pragma unroll
+    for (int k = 0; k < 16; ++k) {
+      if (base + k < n) local[base + k] = run;
+      run += v[k];
+    }
   }
-  sd.payload_bytes = payload;
+  if (threadIdx.x == 0) tile_sum[blockIdx.x] = total;
 }
 
-// Copies the chunk sizes of all series into one array indexed by launch
-// chunk t; each thread handles 16 consecutive chunks.
-__global__ __launch_bounds__(256) void k_gather_sizes(const DecompressSeries* many, uint32_t ns, uint64_t total,
-                                                      uint32_t* out) {
-  const uint64_t t0 = ((uint64_t)blockIdx.x * blockDim.x + threadIdx.x) * 16;
-  if (t0 >= total) return;
-  uint32_t lo = 0, hi = ns - 1;  // last series with chunk0 <= t0
-  while (lo < hi) {
-    const uint32_t mid = (lo + hi + 1) >> 1;
-    if (many[mid].chunk0 <= t0) lo = mid;
-    else hi = mid - 1;
-  }
-  uint32_t i = lo;
-  for (uint64_t t = t0; t < t0 + 16 && t < total; ++t) {
-    while (i + 1 < ns && many[i + 1].chunk0 <= t) ++i;
-    out[t] = reinterpret_cast<const uint32_t*>(many[i].in + kHdrBytes)[t - many[i].chunk0];
-  }
-}
-
-hipError_t launch_batch_dprep(DecompressSeries* many, uint32_t ns, uint64_t total_chunks, uint32_t* sizes_out,
-                              Ctl* ctl, uint32_t epoch, hipStream_t s) {
-  if (ns == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_batch_headers, dim3((ns + 255) / 256), dim3(256), 0, s, many, ns, ctl, epoch);
-  if (total_chunks) {
-    const uint64_t threads = (total_chunks + 15) / 16;
-    hipLaunchKernelGGL(k_gather_sizes, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s,
-                       (const DecompressSeries*)many, ns, total_chunks, sizes_out);
-  }
+hipError_t launch_scan_local(DecompressArgs* a, uint64_t total_chunks, uint32_t* local, uint64_t* tiles,
+                             hipStream_t s) {
+  const uint64_t ntiles = scan_tiles(total_chunks);
+  a->local = local;
+  a->tiles = tiles;
+  a->ntiles = (uint32_t)ntiles;
+  a->tiles_scanned = ntiles > 64;  // up to 64 (262,144 chunks) the decoder's waves add them
+  hipLaunchKernelGGL(k_scan_local, dim3((unsigned)ntiles), dim3(256), 0, s, a->one, a->many, a->nseries, total_chunks,
+                     local, tiles, a->times);
+  if (a->tiles_scanned) hipLaunchKernelGGL(k_scan_tile_sums, dim3(1), dim3(256), 0, s, tiles, ntiles);
   return hipGetLastError();
 }
 
@@ -162,18 +153,18 @@ hipError_t launch_compress_variant(const CompressArgs& a, int form, int variant,
   return hipLaunchKernel(fn, dim3(grid), dim3(64 * kVariantWaves), args, 0, s);
 }
 
-hipError_t launch_decompress(const DecompressArgs& a, int form, int grid, hipStream_t s) {
-  if (form == 2) return launch_decompress_f64(a, grid, s);
-  if (form == 1) return launch_decompress_f32(a, grid, s);
-  return launch_decompress_mixed(a, grid, s);
+hipError_t launch_decompress(const DecompressArgs& a, int form, bool direct, int grid, hipStream_t s) {
+  if (form == 2) return launch_decompress_f64(a, direct, grid, s);
+  if (form == 1) return launch_decompress_f32(a, direct, grid, s);
+  return launch_decompress_mixed(a, direct, grid, s);
 }
 
-hipError_t launch_scan_sizes(const uint32_t* sizes, uint64_t n, uint32_t lo, uint32_t hi, uint64_t expect,
-                             uint64_t* tile_tmp, uint64_t* offsets, Ctl* ctl, uint32_t epoch, hipStream_t s) {
+hipError_t launch_scan_sizes(const uint32_t* sizes, uint64_t n, uint64_t* tile_tmp, uint64_t* offsets,
+                             hipStream_t s) {
   if (n == 0) return hipSuccess;
   const uint64_t ntiles = (n + kScanTile - 1) / kScanTile;
-  hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)ntiles), dim3(256), 0, s, sizes, n, lo, hi, tile_tmp, ctl, epoch);
-  hipLaunchKernelGGL(k_scan_tile_sums, dim3(1), dim3(256), 0, s, tile_tmp, ntiles, expect, ctl, epoch);
+  hipLaunchKernelGGL(k_scan_tiles, dim3((unsigned)ntiles), dim3(256), 0, s, sizes, n, tile_tmp);
+  hipLaunchKernelGGL(k_scan_tile_sums, dim3(1), dim3(256), 0, s, tile_tmp, ntiles);
   hipLaunchKernelGGL(k_scan_apply, dim3((unsigned)ntiles), dim3(256), 0, s, sizes, n, tile_tmp, offsets);
   return hipGetLastError();
 }

@@ -12,8 +12,15 @@ hipError_t launch_compress_f64(const CompressArgs& a, int pass, int grid, hipStr
   return hipGetLastError();
 }
 
-hipError_t launch_decompress_f64(const DecompressArgs& a, int grid, hipStream_t s) {
-  hipLaunchKernelGGL(k_decompress<TF64>, dim3(grid), dim3(64 * kWavesD), 0, s, a);
+hipError_t launch_decompress_f64(const DecompressArgs& a, bool direct, int grid, hipStream_t s) {
+  const dim3 g(grid), b(64 * kWavesD);
+  if (a.many) {
+    if (direct) hipLaunchKernelGGL((k_decompress<TF64, true, true>), g, b, 0, s, a);
+    else hipLaunchKernelGGL((k_decompress<TF64, false, true>), g, b, 0, s, a);
+  } else {
+    if (direct) hipLaunchKernelGGL((k_decompress<TF64, true, false>), g, b, 0, s, a);
+    else hipLaunchKernelGGL((k_decompress<TF64, false, false>), g, b, 0, s, a);
+  }
   return hipGetLastError();
 }
 
@@ -38,17 +45,25 @@ const void* compress_variant_kernel_f64(int variant, int pass) {
   return nullptr;
 }
 
-const void* decompress_kernel_f64() { return reinterpret_cast<const void*>(&k_decompress<TF64>); }
+// for the occupancy; the form's other kernels fit as often
+const void* decompress_kernel_f64() { return reinterpret_cast<const void*>(&k_decompress<TF64, false, true>); }
+
+template <int NW>
+static void launch_queue(const CompressArgs& a, int grid, hipStream_t s) {
+  if (a.many) hipLaunchKernelGGL((k_compress_queue<TF64, NW, true>), dim3(grid), dim3(64 * NW), 0, s, a);
+  else hipLaunchKernelGGL((k_compress_queue<TF64, NW, false>), dim3(grid), dim3(64 * NW), 0, s, a);
+}
 
 hipError_t launch_compress_queue_f64(const CompressArgs& a, int nw, int grid, hipStream_t s) {
-  if (nw == 8) hipLaunchKernelGGL((k_compress_queue<TF64, 8>), dim3(grid), dim3(64 * 8), 0, s, a);
-  else hipLaunchKernelGGL((k_compress_queue<TF64, 4>), dim3(grid), dim3(64 * 4), 0, s, a);
+  if (nw == 8) launch_queue<8>(a, grid, s);
+  else launch_queue<4>(a, grid, s);
   return hipGetLastError();
 }
 
+// for the occupancy; launches of one series hold as many workgroups per CU
 const void* compress_queue_kernel_f64(int nw) {
-  return nw == 8 ? reinterpret_cast<const void*>(&k_compress_queue<TF64, 8>)
-                 : reinterpret_cast<const void*>(&k_compress_queue<TF64, 4>);
+  return nw == 8 ? reinterpret_cast<const void*>(&k_compress_queue<TF64, 8, true>)
+                 : reinterpret_cast<const void*>(&k_compress_queue<TF64, 4, true>);
 }
 
 }  // namespace falcon_dev

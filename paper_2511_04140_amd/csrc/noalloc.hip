@@ -21,13 +21,12 @@ namespace {
 
 // Largest input, in chunks of 1025 values: 2^19 chunks (537,395,200 values).
 constexpr uint64_t kMaxChunks = 1ull << 19;
-constexpr size_t kCtlBytes = 256;
 constexpr size_t kTileWords = (kMaxChunks + 4095) / 4096 + 1;  // scan tile sums (scan_tiles + 1)
 constexpr size_t kTilesBytes = ((kTileWords * 8 + 255) / 256) * 256;
 constexpr size_t kMetaBytes = kMaxChunks * sizeof(ChunkMeta);
 constexpr size_t kSizesBytes = kMaxChunks * 4;
 constexpr size_t kOffsetsBytes = kMaxChunks * 8;
-constexpr size_t kScratchBytes = kCtlBytes + kTilesBytes + kMetaBytes + kSizesBytes + kOffsetsBytes;
+constexpr size_t kScratchBytes = kTilesBytes + kMetaBytes + kSizesBytes + kOffsetsBytes;
 
 static_assert(sizeof(ChunkMeta) == 16, "metadata words of 16 bytes");
 static_assert(kMetaBytes % 256 == 0 && kSizesBytes % 256 == 0, "sub-arrays stay 256-byte aligned");
@@ -103,11 +102,10 @@ extern "C" falcon_status falcon_compress_noalloc(const void* d_in, size_t n, fal
   if (st != FALCON_OK) return st;
   hipStream_t s = static_cast<hipStream_t>(stream);
   uint8_t* base = d->ptr;
-  Ctl* ctl = reinterpret_cast<Ctl*>(base);
-  uint64_t* tiles = reinterpret_cast<uint64_t*>(base + kCtlBytes);
-  ChunkMeta* meta = reinterpret_cast<ChunkMeta*>(base + kCtlBytes + kTilesBytes);
-  uint32_t* sizes = reinterpret_cast<uint32_t*>(base + kCtlBytes + kTilesBytes + kMetaBytes);
-  uint64_t* offsets = reinterpret_cast<uint64_t*>(base + kCtlBytes + kTilesBytes + kMetaBytes + kSizesBytes);
+  uint64_t* tiles = reinterpret_cast<uint64_t*>(base);
+  ChunkMeta* meta = reinterpret_cast<ChunkMeta*>(base + kTilesBytes);
+  uint32_t* sizes = reinterpret_cast<uint32_t*>(base + kTilesBytes + kMetaBytes);
+  uint64_t* offsets = reinterpret_cast<uint64_t*>(base + kTilesBytes + kMetaBytes + kSizesBytes);
   CompressArgs a{};
   a.one.in = d_in;
   a.one.out = static_cast<uint8_t*>(d_out);
@@ -123,15 +121,13 @@ extern "C" falcon_status falcon_compress_noalloc(const void* d_in, size_t n, fal
   a.gsizes = sizes;
   a.offsets = offsets;
   // every scratch word is written before it is read: the size pass writes
-  // meta and sizes, the scan the tile sums and offsets; the control block
-  // takes an error word only for a chunk size outside [0, 2^32), which never
-  // happens, so nothing needs clearing between calls
+  // meta and sizes, the scan the tile sums and offsets
   const int nw = pass_waves((int)dt);
   const int g1 = grid_of(d->grid[dt][1], nc, nw), g2 = grid_of(d->grid[dt][2], nc, nw);
   if (nc) {
     a.total_waves = (uint32_t)(g1 * nw);
     if ((st = dev_err(launch_compress(a, (int)dt, 1, g1, s))) != FALCON_OK) return st;
-    if ((st = dev_err(launch_scan_sizes(sizes, nc, 0, ~0u, ~0ull, tiles, offsets, ctl, 1, s))) != FALCON_OK)
+    if ((st = dev_err(launch_scan_sizes(sizes, nc, tiles, offsets, s))) != FALCON_OK)
       return st;
   }
   a.total_waves = (uint32_t)(g2 * nw);
