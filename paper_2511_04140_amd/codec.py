@@ -10,6 +10,7 @@ import ctypes
 import os
 import threading
 
+import numpy as np
 import torch
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -35,6 +36,12 @@ class Series(ctypes.Structure):
     _fields_ = [("d_in", ctypes.c_void_p), ("n", ctypes.c_size_t), ("in_len", ctypes.c_size_t),
                 ("d_out", ctypes.c_void_p), ("out_cap", ctypes.c_size_t), ("dtype", ctypes.c_int),
                 ("out_len", ctypes.c_size_t)]
+
+
+_SERIES = np.dtype({"names": [f for f, _ in Series._fields_],
+                    "formats": [np.dtype(t) for _, t in Series._fields_],
+                    "offsets": [getattr(Series, f).offset for f, _ in Series._fields_],
+                    "itemsize": ctypes.sizeof(Series)})
 
 
 class PlanInfo(ctypes.Structure):
@@ -164,6 +171,8 @@ _lock = threading.Lock()
 
 def lib():
     global _lib
+    if _lib is not None:
+        return _lib
     with _lock:
         if _lib is None:
             _lib = _load()
@@ -340,10 +349,8 @@ class Codec:
             self.sync()
         return out[: olen.value]
 
-    def decompress(self, stream: torch.Tensor, out: torch.Tensor | None = None) -> torch.Tensor:
-        """Decompresses a uint8 device tensor holding one stream."""
-        if not stream.is_cuda or stream.dtype != torch.uint8 or not stream.is_contiguous():
-            raise ValueError("decompress needs a contiguous uint8 device tensor")
+    def _header(self, stream: torch.Tensor):
+        """The value count and dtype in a device stream's header."""
         hdr = stream[:32].cpu().numpy() if stream.numel() >= 32 else None
         if hdr is None:
             raise FalconError(ERR_CORRUPT_STREAM, "falcon_decompress")
@@ -352,9 +359,19 @@ class Codec:
         st = lib().falcon_stream_info(ctypes.c_void_p(hdr.ctypes.data), 32, ctypes.byref(n), ctypes.byref(code))
         if st != 0:
             raise FalconError(st, "falcon_stream_info")
-        dt = torch.float64 if code.value == FALCON_FLOAT64 else torch.float32
+        return n.value, torch.float64 if code.value == FALCON_FLOAT64 else torch.float32
+
+    def decompress(self, stream: torch.Tensor, out: torch.Tensor | None = None) -> torch.Tensor:
+        """Decompresses a uint8 device tensor holding one stream."""
+        if not stream.is_cuda or stream.dtype != torch.uint8 or not stream.is_contiguous():
+            raise ValueError("decompress needs a contiguous uint8 device tensor")
+        # a caller's buffer takes whatever the stream holds; without one the
+        # header says what to allocate, and the call need not read it again
+        n, dt = (None, None) if out is not None else self._header(stream)
         if out is None:
-            out = torch.empty(n.value, dtype=dt, device=stream.device)
+            out = torch.empty(n, dtype=dt, device=stream.device)
+            if n:
+                return self.decompress_n(stream, n, dt, out)
         nout = ctypes.c_size_t()
         st = lib().falcon_decompress(self._ctx, ctypes.c_void_p(stream.data_ptr()), stream.numel(),
                                      ctypes.c_void_p(out.data_ptr() if out.numel() else 0),
@@ -422,30 +439,48 @@ class Codec:
         return out[: nout.value]
 
     # -- many series in one launch ------------------------------------------
+    # the descriptors are filled column by column: a ctypes structure per
+    # series costs a one-shot call more than its launches do
     def _compress_descs(self, xs, outs):
         descs = (Series * len(xs))()
-        views = []
-        for i, x in enumerate(xs):
+        for x in xs:
             if not x.is_cuda or not x.is_contiguous():
                 raise ValueError("batch compression needs contiguous device tensors")
-            code = _dtype_code(x.dtype)
-            cap = lib().falcon_compress_bound(x.numel(), code)
-            o = outs[i] if outs is not None else torch.empty(cap, dtype=torch.uint8, device=x.device)
-            descs[i] = Series(x.data_ptr() if x.numel() else None, x.numel(), 0, o.data_ptr(), o.numel(), code, 0)
-            views.append(o)
+        codes = [_dtype_code(x.dtype) for x in xs]
+        ns = [x.numel() for x in xs]
+        if outs is not None:
+            views = [outs[i] for i in range(len(xs))]
+        else:
+            bound = lib().falcon_compress_bound
+            views = [torch.empty(bound(n, c), dtype=torch.uint8, device=x.device) for x, n, c in zip(xs, ns, codes)]
+        if len(xs):
+            col = np.frombuffer(descs, _SERIES)
+            col["d_in"] = [x.data_ptr() for x in xs]
+            col["n"] = ns
+            col["d_out"] = [v.data_ptr() for v in views]
+            col["out_cap"] = [v.numel() for v in views]
+            col["dtype"] = codes
         return descs, views
 
     def _decompress_descs(self, streams, counts, dtypes, outs):
         descs = (Series * len(streams))()
-        views = []
-        for i, s_ in enumerate(streams):
+        for s_ in streams:
             if not s_.is_cuda or s_.dtype != torch.uint8 or not s_.is_contiguous():
                 raise ValueError("batch decompression needs contiguous uint8 device tensors")
-            code = _dtype_code(dtypes[i])
-            o = outs[i] if outs is not None else torch.empty(counts[i], dtype=dtypes[i], device=s_.device)
-            descs[i] = Series(s_.data_ptr(), counts[i], s_.numel(), o.data_ptr() if o.numel() else None,
-                              o.numel() * o.element_size(), code, 0)
-            views.append(o)
+        count = len(streams)
+        codes = [_dtype_code(dtypes[i]) for i in range(count)]
+        if outs is not None:
+            views = [outs[i] for i in range(count)]
+        else:
+            views = [torch.empty(counts[i], dtype=dtypes[i], device=s_.device) for i, s_ in enumerate(streams)]
+        if count:
+            col = np.frombuffer(descs, _SERIES)
+            col["d_in"] = [s_.data_ptr() for s_ in streams]
+            col["n"] = [counts[i] for i in range(count)]
+            col["in_len"] = [s_.numel() for s_ in streams]
+            col["d_out"] = [v.data_ptr() for v in views]  # 0 for an empty tensor
+            col["out_cap"] = [v.numel() * v.element_size() for v in views]
+            col["dtype"] = codes
         return descs, views
 
     def compress_each(self, xs, outs=None):

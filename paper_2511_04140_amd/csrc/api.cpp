@@ -223,8 +223,8 @@ namespace {
 
 // ---- asynchronous device calls --------------------------------------------
 // A device call runs in three steps: begin_call (stream choice, ordering
-// after the previous call), the enqueue, end_call (records the call's end,
-// and with FALCON_OPT_BLOCKING synchronises and reports at once).
+// after the previous call), the enqueue, end_call (with FALCON_OPT_BLOCKING
+// synchronises and reports at once).
 
 hipStream_t call_stream(falcon_ctx* ctx, void* stream) {
   return stream ? static_cast<hipStream_t>(stream) : ctx->main.stream;
@@ -232,15 +232,22 @@ hipStream_t call_stream(falcon_ctx* ctx, void* stream) {
 
 falcon_status begin_call(falcon_ctx* ctx, hipStream_t s) {
   if (hipSetDevice(ctx->device) != hipSuccess) return FALCON_ERR_DEVICE;
-  if (ctx->last_stream && ctx->last_stream != s && hipStreamWaitEvent(s, ctx->ev_done, 0) != hipSuccess)
-    return FALCON_ERR_DEVICE;
+  if (ctx->unsynced && ctx->last_stream != s) {
+    // a stream that its owner has destroyed since takes no event: then
+    // everything on the device is waited for
+    if (hipEventRecord(ctx->ev_last, ctx->last_stream) == hipSuccess) {
+      if (hipStreamWaitEvent(s, ctx->ev_last, 0) != hipSuccess) return FALCON_ERR_DEVICE;
+    } else {
+      (void)hipGetLastError();
+      if (hipDeviceSynchronize() != hipSuccess) return FALCON_ERR_DEVICE;
+    }
+  }
   return FALCON_OK;
 }
 
 falcon_status end_call(falcon_ctx* ctx, hipStream_t s, falcon_status st) {
-  // the work enqueued so far is recorded even after an error, so that a
-  // later call or falcon_sync still orders after it
-  if (hipEventRecord(ctx->ev_done, s) != hipSuccess && st == FALCON_OK) st = FALCON_ERR_DEVICE;
+  // also after an error, so that a later call or falcon_sync still orders
+  // after the work enqueued so far
   ctx->last_stream = s;
   ctx->unsynced = true;
   if (ctx->opt_flags & FALCON_OPT_BLOCKING) {
@@ -250,14 +257,14 @@ falcon_status end_call(falcon_ctx* ctx, hipStream_t s, falcon_status st) {
   return st;
 }
 
-// A device word that the kernels of one compression fill with its stream
+// A pinned word that the kernels of one compression fill with its stream
 // length, reported to *dst at falcon_sync.
 falcon_status pending_length(falcon_ctx* ctx, size_t* dst, uint64_t** d_len) {
   const size_t slot = ctx->pending.size();
   const size_t b = slot / kLenBlock;
   if (b == ctx->len_blocks.size()) {
     void* p = nullptr;
-    if (hipMalloc(&p, kLenBlock * 8) != hipSuccess) return FALCON_ERR_OUT_OF_MEMORY;
+    if (hipHostMalloc(&p, kLenBlock * 8, hipHostMallocDefault) != hipSuccess) return FALCON_ERR_OUT_OF_MEMORY;
     ctx->len_blocks.push_back(static_cast<uint64_t*>(p));
   }
   *d_len = ctx->len_blocks[b] + slot % kLenBlock;
@@ -266,7 +273,7 @@ falcon_status pending_length(falcon_ctx* ctx, size_t* dst, uint64_t** d_len) {
 }
 
 // Writes 32 (the stream length of n = 0, which no kernel writes) to a
-// device length word.
+// length word.
 falcon_status empty_length(uint64_t* d_len, hipStream_t s) { return dev_err(launch_fill_u64(d_len, 1, 32, s)); }
 
 }  // namespace
@@ -311,7 +318,7 @@ falcon_status falcon_create(int device, const falcon_opts* opts, falcon_ctx** ou
   ctx->device = device;
   ctx->opt_flags = flags;
   bool ok = lane_init(ctx->main) == FALCON_OK &&
-            hipEventCreateWithFlags(&ctx->ev_done, hipEventDisableTiming) == hipSuccess;
+            hipEventCreateWithFlags(&ctx->ev_last, hipEventDisableTiming) == hipSuccess;
   for (int c = 0; ok && c < FALCON_TIMED_CALLS; ++c)
     for (int i = 0; ok && i < 4; ++i) ok = hipEventCreate(&ctx->ev[c][i]) == hipSuccess;
   constexpr size_t kTimeBytes = (size_t)kTimeWords * 8;
@@ -345,33 +352,11 @@ falcon_status falcon_sync(falcon_ctx* ctx) {
   if (!ctx->unsynced) return FALCON_OK;
   if (hipSetDevice(ctx->device) != hipSuccess) return FALCON_ERR_DEVICE;
   Lane& l = ctx->main;
-  hipStream_t s = ctx->last_stream;
-  falcon_status st = FALCON_OK;
-  const size_t np = ctx->pending.size();
-  if (np > ctx->len_host_cap) {
-    // grown only here, when no copy into it is in flight
-    if (hipStreamSynchronize(s) != hipSuccess) st = FALCON_ERR_DEVICE;
-    if (ctx->len_host) (void)hipHostFree(ctx->len_host);
-    ctx->len_host = nullptr;
-    ctx->len_host_cap = 0;
-    size_t cap = kLenBlock;
-    while (cap < np) cap *= 2;
-    void* p = nullptr;
-    if (hipHostMalloc(&p, cap * 8, hipHostMallocDefault) != hipSuccess) {
-      st = FALCON_ERR_OUT_OF_MEMORY;
-    } else {
-      ctx->len_host = static_cast<uint64_t*>(p);
-      ctx->len_host_cap = cap;
-    }
-  }
-  for (size_t b = 0; st == FALCON_OK && b * kLenBlock < np; ++b) {
-    const size_t k = np - b * kLenBlock < kLenBlock ? np - b * kLenBlock : kLenBlock;
-    st = dev_err(hipMemcpyAsync(ctx->len_host + b * kLenBlock, ctx->len_blocks[b], k * 8, hipMemcpyDeviceToHost, s));
-  }
-  const falcon_status sy = dev_err(hipStreamSynchronize(s));
-  if (st == FALCON_OK) st = sy;
+  falcon_status st = dev_err(hipStreamSynchronize(ctx->last_stream));
   if (st == FALCON_OK) {
-    for (const auto& p : ctx->pending) *p.dst = (size_t)ctx->len_host[p.slot];
+    // lengths and error words lie in pinned memory: nothing is copied
+    for (const auto& p : ctx->pending)
+      *p.dst = (size_t)ctx->len_blocks[p.slot / kLenBlock][p.slot % kLenBlock];
     // the decompression error word holds the epoch of the last launch whose
     // chunk failed: a launch since the last sync has a larger one
     const uint32_t err = l.ctl->error;
@@ -395,9 +380,8 @@ void falcon_destroy(falcon_ctx* ctx) {
   for (auto& call : ctx->ev)
     for (hipEvent_t e : call)
       if (e) (void)hipEventDestroy(e);
-  if (ctx->ev_done) (void)hipEventDestroy(ctx->ev_done);
-  for (uint64_t* b : ctx->len_blocks) (void)hipFree(b);
-  if (ctx->len_host) (void)hipHostFree(ctx->len_host);
+  if (ctx->ev_last) (void)hipEventDestroy(ctx->ev_last);
+  for (uint64_t* b : ctx->len_blocks) (void)hipHostFree(b);
   if (ctx->times) (void)hipFree(ctx->times);
   if (ctx->times_host) (void)hipHostFree(ctx->times_host);
   delete ctx;

@@ -136,8 +136,7 @@ falcon_status batch_layout(BatchScratch& b, int op, const falcon_series* s, size
   }
   L.total = t;
   if ((r = grow(&b.many, &b.many_cap, L.desc_bytes, 1, false, st)) != FALCON_OK ||
-      (r = grow(&b.lens, &b.lens_cap, count, 8, false, st)) != FALCON_OK ||
-      (r = grow(&b.h_lens, &b.h_lens_cap, count, 8, true, st)) != FALCON_OK)
+      (r = grow(&b.lens, &b.lens_cap, count, 8, true, st)) != FALCON_OK)
     return r;
   if (op == FALCON_OP_DECOMPRESS && L.longest > kDirectChunks &&
       ((r = grow(&b.local, &b.local_cap, t, 4, false, st)) != FALCON_OK ||
@@ -186,7 +185,7 @@ falcon_status batch_enqueue(const falcon_ctx* ctx, BatchScratch& b, const BatchL
       const int grid = grid_of(max_grid_q(ctx, parts[i].form, nw), g, parts[i].chunks + nw, nw);
       if ((st = dev_err(launch_compress_queue(a, parts[i].form, nw, grid, s))) != FALCON_OK) return st;
     }
-    return dev_err(hipMemcpyAsync(b.h_lens, b.lens, L.count * 8, hipMemcpyDeviceToHost, s));
+    return FALCON_OK;
   }
   if (np == 0) parts[np++] = {2, 0, 0};  // only empty series: the launch checks their headers
   DecompressArgs a{};
@@ -214,7 +213,7 @@ falcon_status batch_result(BatchScratch& b, const BatchLayout& L, const falcon_s
   if (L.op == FALCON_OP_DECOMPRESS && err == kBatchEpoch) return FALCON_ERR_CORRUPT_STREAM;
   if (queue_failed(b.ctl, b.q)) return FALCON_ERR_DEVICE;
   if (dst)
-    for (size_t i = 0; i < L.count; ++i) dst[i].out_len = L.op == FALCON_OP_COMPRESS ? b.h_lens[i] : src[i].n;
+    for (size_t i = 0; i < L.count; ++i) dst[i].out_len = L.op == FALCON_OP_COMPRESS ? b.lens[i] : src[i].n;
   return FALCON_OK;
 }
 
@@ -224,8 +223,7 @@ void batch_free(BatchScratch& b) {
   if (b.tiles) (void)hipFree(b.tiles);
   if (b.local) (void)hipFree(b.local);
   if (b.ctl) (void)hipHostFree(b.ctl);
-  if (b.lens) (void)hipFree(b.lens);
-  if (b.h_lens) (void)hipHostFree(b.h_lens);
+  if (b.lens) (void)hipHostFree(b.lens);
   queue_free(b.q);
   b = BatchScratch();
 }

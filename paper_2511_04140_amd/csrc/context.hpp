@@ -112,10 +112,8 @@ struct BatchScratch {
   uint64_t* tiles = nullptr;
   size_t tiles_cap = 0;
   falcon_dev::Ctl* ctl = nullptr; // pinned host memory (error words)
-  uint64_t* lens = nullptr;      // device stream lengths (compression)
+  uint64_t* lens = nullptr;      // pinned: stream lengths, written by the kernels (compression)
   size_t lens_cap = 0;
-  uint64_t* h_lens = nullptr;    // pinned: lengths, then the error word
-  size_t h_lens_cap = 0;
   Queue q;
 };
 
@@ -125,19 +123,18 @@ struct falcon_ctx {
   int device = 0;
   unsigned opt_flags = 0;   // FALCON_OPT_* of falcon_create
   falcon_host::Lane main;
-  // asynchronous device calls: every call waits (on the device) for the
-  // previous one when it uses another stream, and records ev_done after its
-  // work; falcon_sync waits for last_stream
-  hipEvent_t ev_done = nullptr;
+  // asynchronous device calls: a call on another stream than the last one's
+  // waits for it on the device (ev_last, recorded only then: an event record
+  // costs a call about as much as its launch); falcon_sync waits for
+  // last_stream
+  hipEvent_t ev_last = nullptr;
   hipStream_t last_stream = nullptr;
   bool unsynced = false;
   uint32_t sync_epoch = 0;  // main lane's launch epoch at the last falcon_sync
   // stream lengths of compressions that report to host memory: the kernels
-  // write them into device words (blocks of kLenBlock, never moved while in
-  // use), falcon_sync copies them to pinned memory and on to the caller
+  // write them into pinned words (blocks of kLenBlock, never moved while in
+  // use), from which falcon_sync hands them to the caller
   std::vector<uint64_t*> len_blocks;
-  uint64_t* len_host = nullptr;  // pinned, len_host_cap words
-  size_t len_host_cap = 0;
   struct PendingLen {
     size_t* dst;
     size_t slot;
@@ -201,7 +198,7 @@ falcon_status queue_prepare(Queue& q, uint64_t nchunks, hipStream_t s);
 void queue_free(Queue& q);
 // Wavefronts per workgroup for a compression of nchunks chunks.
 int queue_waves(uint64_t nchunks);
-constexpr size_t kLenBlock = 4096;  // stream-length words per device block of a context
+constexpr size_t kLenBlock = 4096;  // stream-length words per pinned block of a context
 
 // Enqueues the decompression of a stream at d_in of in_len bytes holding n
 // values of type dt, into d_out.  With payload = kPayloadFromHeader the

@@ -129,3 +129,31 @@ def test_replays_of_a_captured_launch(orc):
         torch.cuda.synchronize()
         assert buf[:int(ln.item())].cpu().numpy().tobytes() == orc.compress(x), rep
     c.close()
+
+
+def test_streams_in_turn(orc):
+    """Calls of one context on alternating streams, each reading what the one
+    before it wrote: a call on another stream than the last waits for it, and
+    stream lengths and errors arrive with the sync that follows."""
+    from paper_2511_04140_amd import codec as C
+    c = C.Codec(0, blocking=False)
+    st = [torch.cuda.Stream(), torch.cuda.Stream()]
+    x = torch.from_numpy(_data(1025 * 700 + 3, "f64", 9)).cuda()
+    want = np.frombuffer(orc.compress(x.cpu().numpy()), np.uint8)
+    torch.cuda.synchronize()
+    for _ in range(3):
+        src, lens, bufs, keep = x, [], [], []
+        for k in range(6):
+            buf = torch.empty(C.compress_bound(x.numel(), x.dtype), dtype=torch.uint8, device="cuda")
+            y = torch.empty_like(x)
+            lens.append(c.compress_async(src, buf, stream=st[k % 2]))
+            c.decompress_n_async(buf, x.numel(), x.dtype, y, stream=st[(k + 1) % 2])
+            src = y
+            bufs.append(buf)
+            keep.append(y)
+        c.sync()
+        assert torch.equal(src.view(torch.int64), x.view(torch.int64))
+        for ln, buf in zip(lens, bufs):
+            assert np.array_equal(buf[: ln.value].cpu().numpy(), want)
+        torch.cuda.synchronize()
+    c.close()
