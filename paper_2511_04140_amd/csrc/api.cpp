@@ -211,9 +211,13 @@ falcon_status enqueue_decompress(falcon_ctx* ctx, Lane& l, const uint8_t* d_in, 
   a.ctl = l.ctl;
   a.epoch = l.epoch;
   a.times = timed ? ctx->times + (size_t)ctx->ev_slot * kTimeWords : nullptr;
-  if (!direct && (st = dev_err(launch_scan_local(&a, nc, l.local, l.tiles, s))) != FALCON_OK) return st;
   const int grid = grid_for(max_grid_d(ctx, dt), nc, kDecompressWaves);
   a.total_waves = (uint32_t)(grid * kDecompressWaves);
+  if (!direct || nc > kDrawFrom * a.total_waves) {
+    if ((st = queue_prepare(l.q, 0, s)) != FALCON_OK) return st;
+    a.qctr = l.q.ctr;
+  }
+  if (!direct && (st = dev_err(launch_scan_local(&a, nc, l.local, l.tiles, s))) != FALCON_OK) return st;
   if ((st = dev_err(launch_decompress(a, (int)dt, direct, grid, s))) != FALCON_OK) return st;
   if (timed) ctx->ev_kind[ctx->ev_slot] = falcon_ctx::kStamps;
   return FALCON_OK;

@@ -142,7 +142,7 @@ falcon_status batch_layout(BatchScratch& b, int op, const falcon_series* s, size
       ((r = grow(&b.local, &b.local_cap, t, 4, false, st)) != FALCON_OK ||
        (r = grow(&b.tiles, &b.tiles_cap, scan_tiles(t), 8, false, st)) != FALCON_OK))
     return r;
-  if (op == FALCON_OP_COMPRESS && (r = queue_prepare(b.q, t ? t : 1, st)) != FALCON_OK) return r;
+  if ((r = queue_prepare(b.q, op == FALCON_OP_COMPRESS ? t : 0, st)) != FALCON_OK) return r;
   if (!b.ctl) {
     if (hipHostMalloc(&b.ctl, 64, hipHostMallocDefault) != hipSuccess) return FALCON_ERR_OUT_OF_MEMORY;
     memset(b.ctl, 0, 64);
@@ -194,6 +194,7 @@ falcon_status batch_enqueue(const falcon_ctx* ctx, BatchScratch& b, const BatchL
   a.nseries = (uint32_t)L.count;
   a.ctl = b.ctl;
   a.epoch = kBatchEpoch;
+  a.qctr = b.q.ctr;
   const bool direct = L.longest <= kDirectChunks;
   if (!direct && (st = dev_err(launch_scan_local(&a, L.total, b.local, b.tiles, s))) != FALCON_OK) return st;
   for (int i = 0; i < np; ++i) {

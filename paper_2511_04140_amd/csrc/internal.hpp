@@ -24,7 +24,14 @@ struct Ctl {
 constexpr int kQueueGroups = 8;
 constexpr int kRoleLines = 16;
 constexpr int kQueueStride = 16;
-constexpr int kQueueWords = kQueueStride * (kQueueGroups + 1 + kRoleLines);
+// and those of decompression's draws, kDrawGroups lines from kDrawLine on,
+// used by launches of more than kDrawFrom chunks a wave: shorter ones gain
+// nothing (walks of float64, fixed against drawn: 4 chunks a wave 46.3 / 47.6
+// us, 5 54.5 / 53.7, 6 63.0 / 61.1, 8 79.7 / 76.0).
+constexpr int kDrawLine = kQueueGroups + 1 + kRoleLines;
+constexpr int kDrawGroups = 64;
+constexpr uint64_t kDrawFrom = 4;
+constexpr int kQueueWords = kQueueStride * (kDrawLine + kDrawGroups);
 constexpr int kQueueSlack = 4096;  // size and offset words past the chunks (the scan reads ahead)
 
 // Time stamps of a timed launch, in ticks of the device's constant-rate
@@ -103,6 +110,7 @@ struct DecompressArgs {
   uint32_t ntiles;
   uint32_t epoch;
   uint32_t pad;
+  uint64_t* qctr;      // kQueueWords counters as in CompressArgs, where total_chunks > kDrawFrom * total_waves
   Ctl* ctl;
   uint64_t* times;     // kTimeWords, or null
 };

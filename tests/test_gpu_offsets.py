@@ -80,3 +80,54 @@ def test_batches(orc, long_chunks):
         assert np.array_equal(y.cpu().numpy().view(np.uint8), x.view(np.uint8))
     plan.close()
     c.close()
+
+
+@pytest.mark.parametrize("dt,chunks", [("f64", 16384), ("f64", 16385), ("f64", 16449), ("f32", 24576), ("f32", 24577),
+                                       ("f32", 30000)])
+def test_drawn_chunks(dt, chunks):
+    """Up to four chunks a wave (4,096 waves in float64, 6,144 in float32) the
+    chunks are dealt out, beyond that they are drawn from counters that each
+    launch leaves clear: every chunk comes back, three times in a row, and on
+    two contexts at once."""
+    from paper_2511_04140_amd import codec as C
+    cs = [C.Codec(0, blocking=False) for _ in range(2)]
+    dtype = torch.float64 if dt == "f64" else torch.float32
+    n = 1025 * chunks - 3
+    x = (torch.arange(n, device="cuda") * 7919 % 100003).to(dtype)
+    torch.cuda.synchronize()  # the codec has a stream of its own
+    s = cs[0].compress(x)
+    ys = [torch.empty_like(x) for _ in cs]
+    st = [torch.cuda.Stream() for _ in cs]
+    for _ in range(3):
+        for y in ys:
+            y.zero_()
+        torch.cuda.synchronize()
+        for c, y, q in zip(cs, ys, st):
+            c.decompress_n_async(s, n, dtype, y, stream=q)
+        for c in cs:
+            c.sync()
+        for y in ys:
+            assert torch.equal(y, x)
+    for c in cs:
+        c.close()
+
+
+def test_drawn_chunks_of_a_plan():
+    """Replays of a decompression plan whose launches draw their chunks."""
+    from paper_2511_04140_amd import codec as C
+    c = C.Codec(0)
+    xs = [(torch.arange(1025 * 60 + 11 * i, device="cuda") % 977).to(torch.float64 if i % 2 else torch.float32)
+          for i in range(700)]
+    torch.cuda.synchronize()
+    streams = c.compress_batch(xs)
+    outs = [torch.empty_like(x) for x in xs]
+    torch.cuda.synchronize()
+    plan = c.plan_decompress(streams, [x.numel() for x in xs], [x.dtype for x in xs], outs)
+    for _ in range(3):
+        for y in outs:
+            y.zero_()
+        torch.cuda.synchronize()
+        plan.run()
+        assert all(torch.equal(y, x) for x, y in zip(xs, outs))
+    plan.close()
+    c.close()
