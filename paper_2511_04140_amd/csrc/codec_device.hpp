@@ -167,6 +167,16 @@ struct TF64 {
     return (S)(u(t) - 0x4338000000000000ull);
   }
   static __device__ __forceinline__ F pow10(const LdsTables& s, int k) { return s.p64[k + POFF]; }
+  // hi and lo become the largest and smallest magnitude with theirs (quiet
+  // NaN values drop out); written out because the library maximum
+  // canonicalises every operand first
+  static __device__ __forceinline__ void range(const U (&v)[17], F& hi, F& lo) {
+#pragma unroll
+    for (int k = 0; k < 17; ++k) {
+      asm("v_max_f64 %0, |%1|, %0" : "+v"(hi) : "v"(f(v[k])));
+      asm("v_min_f64 %0, |%1|, %0" : "+v"(lo) : "v"(f(v[k])));
+    }
+  }
 };
 
 struct TF32 {
@@ -196,6 +206,15 @@ struct TF32 {
     return (S)(u(t) - 0x4B400000u);
   }
   static __device__ __forceinline__ F pow10(const LdsTables& s, int k) { return s.p32[k + POFF]; }
+  static __device__ __forceinline__ void range(const U (&v)[17], F& hi, F& lo) {
+#pragma unroll
+    for (int k = 0; k < 16; k += 2) {
+      asm("v_max3_f32 %0, |%1|, |%2|, %0" : "+v"(hi) : "v"(f(v[k])), "v"(f(v[k + 1])));
+      asm("v_min3_f32 %0, |%1|, |%2|, %0" : "+v"(lo) : "v"(f(v[k])), "v"(f(v[k + 1])));
+    }
+    asm("v_max_f32 %0, |%1|, %0" : "+v"(hi) : "v"(f(v[16])));
+    asm("v_min_f32 %0, |%1|, %0" : "+v"(lo) : "v"(f(v[16])));
+  }
 };
 
 // Per-wave LDS buffer of a one-dtype decoder, in 16-byte blocks: a chunk's
@@ -319,20 +338,27 @@ __device__ __forceinline__ uint32_t xor_lane(uint32_t v, int lane) {
 // bit L of lane p's word is bit p of lane L's word before.  Recursive block
 // swaps: lanes L and L ^ B exchange the off-diagonal B x B blocks, B = 32
 // (the two dwords), then 16, 8, 4, 2, 1 inside each dword.
+// A stage takes the partner's whole word, turned by B so that the block to
+// come lies where it goes, and merges it: per dword one cross-lane move, one
+// rotate, one bit-field insert (with the blocks cut out before the exchange it
+// was eight operations).
 __device__ __forceinline__ uint64_t wave_transpose64(uint64_t x, int lane) {
   uint32_t lo = (uint32_t)x, hi = (uint32_t)(x >> 32);
   {
-    const bool up = lane & 32;
-    const uint32_t r = xor_lane<32>(up ? lo : hi, lane);
-    if (up) lo = r;
-    else hi = r;
+    // B = 32: the upper lanes' low dwords change places with the lower
+    // lanes' high dwords
+    const auto r = __builtin_amdgcn_permlane32_swap(lo, hi, false, false);
+    lo = r[0];
+    hi = r[1];
   }
   auto stage = [&](auto b_tag, uint32_t m) {  // m: the bits whose index has bit B set
     constexpr int B = decltype(b_tag)::value;
     const bool up = lane & B;
+    const uint32_t keep = up ? m : ~m, turn = up ? B : 32 - B;
     auto one = [&](uint32_t& v) {
-      const uint32_t send = up ? (v & ~m) << B : (v & m) >> B;
-      v = (v & (up ? m : ~m)) | xor_lane<B>(send, lane);
+      const uint32_t r = xor_lane<B>(v, lane);
+      const uint32_t t = __builtin_amdgcn_alignbit(r, r, turn);
+      v = (v & keep) | (t & ~keep);
     };
     one(lo);
     one(hi);
