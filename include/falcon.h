@@ -315,7 +315,7 @@ typedef struct falcon_plan falcon_plan;
 
 typedef struct falcon_plan_info {
   int split;            /* 1: one launch per dtype; 0: one launch over both dtypes */
-  int waves_per_group;  /* wavefronts per workgroup */
+  int waves_per_group;  /* wavefronts per workgroup (8: 12 in a launch of float32 series alone) */
   int grid_percent;     /* grid as a percentage of the co-resident workgroups */
   int candidates;       /* geometries timed by the autotuner (0: not tuned) */
   float best_ms;        /* autotuner: time of the chosen geometry */

@@ -145,7 +145,7 @@ falcon_status enqueue_compress(falcon_ctx* ctx, Lane& l, const void* d_in, uint6
   if (timed) begin_timed(ctx);
   if (variant == 0) {
     if ((st = queue_prepare(l.q, nc ? nc : 1, s)) != FALCON_OK) return st;
-    const int nw = queue_waves(nc);
+    const int nw = queue_nw((int)dt, queue_waves(nc));
     a.qctr = l.q.ctr;
     a.qsize = l.q.size;
     a.qoff = l.q.off;
@@ -338,7 +338,7 @@ falcon_status falcon_create(int device, const falcon_opts* opts, falcon_ctx** ou
   for (int form_ = 1; form_ <= 3; ++form_) {
     ctx->grid_d[form_] = max_grid_decompress(device, form_);
     ctx->grid_q[form_][0] = max_grid_compress_queue(device, form_, 4);
-    ctx->grid_q[form_][1] = max_grid_compress_queue(device, form_, 8);
+    ctx->grid_q[form_][1] = max_grid_compress_queue(device, form_, queue_large(form_));
   }
   for (int f = 1; f <= 2; ++f)
     for (int v = 1; v <= 3; ++v)

@@ -181,7 +181,7 @@ falcon_status batch_enqueue(const falcon_ctx* ctx, BatchScratch& b, const BatchL
     for (int i = 0; i < np; ++i) {
       a.total_chunks = parts[i].chunks;
       a.t0 = parts[i].t0;
-      const int nw = g.nw ? g.nw : queue_waves(parts[i].chunks);
+      const int nw = queue_nw(parts[i].form, g.nw ? g.nw : queue_waves(parts[i].chunks));
       const int grid = grid_of(max_grid_q(ctx, parts[i].form, nw), g, parts[i].chunks + nw, nw);
       if ((st = dev_err(launch_compress_queue(a, parts[i].form, nw, grid, s))) != FALCON_OK) return st;
     }

@@ -1412,11 +1412,13 @@ __device__ __forceinline__ bool take_scan_role(const CompressArgs& a) {
 // a10 by one workgroup: sizes to offsets in chunk order, each series' offsets
 // starting at 0 (a size word carries its series' first-chunk mark).  It has
 // to keep up with the whole chip, some 500 chunks a microsecond, and nothing
-// else hides its latencies; a round reads 64 * kScanBlocks sizes per wave, and
+// else hides its latencies; a round reads 64 * scan_blocks sizes per wave, and
 // each wave scans its own part up to the first size still missing.  (One
 // wave alone moved 250 chunks a microsecond; with 1, 2, 4 and 8 blocks of 64 a
 // wave, 1 GiB of float32 took 1,134, 711, 544 and 560 us.)
-constexpr int kScanBlocks = 4;
+// In float32 12 waves of 2, 3, 4 and 6 blocks: 512 MiB 319, 271, 250, 248 us.
+template <int NW>
+constexpr int scan_blocks() { return NW > 8 ? 6 : 4; }
 struct ScanPart {   // one wave's part of a round
   uint32_t known;   // sizes up to the first gap
   uint32_t sum;     // their sum from the part's last first-chunk mark on
@@ -1426,7 +1428,9 @@ struct ScanPart {   // one wave's part of a round
 template <int NW, bool MANY>
 __device__ __forceinline__ void scan_group(const CompressArgs& a, ScanPart* parts, int lane, int wid,
                                            uint64_t t_start) {
+  constexpr int kScanBlocks = scan_blocks<NW>();
   constexpr uint32_t kPart = 64 * kScanBlocks;
+  static_assert(NW * kPart <= kQueueSlack && NW <= kQueueGroups, "a round's reads stay inside the size words");
   uint64_t t = 0, carry = 0, seen = 0;
   uint32_t idle = 0;
   __builtin_amdgcn_s_setprio(3);

@@ -211,7 +211,7 @@ falcon_status enqueue_decompress(falcon_ctx* ctx, Lane& l, const uint8_t* d_in, 
                                  falcon_dtype dt, uint64_t payload, void* d_out, hipStream_t s, bool timed);
 inline bool decompress_failed(const Lane& l) { return l.ctl->error == l.epoch; }
 
-inline int max_grid_q(const falcon_ctx* ctx, int form, int nw) { return ctx->grid_q[form][nw == 8 ? 1 : 0]; }
+inline int max_grid_q(const falcon_ctx* ctx, int form, int nw) { return ctx->grid_q[form][nw == 4 ? 0 : 1]; }
 inline int max_grid_d(const falcon_ctx* ctx, int form) { return ctx->grid_d[form]; }
 
 // Set-up of falcon_compress_noalloc on `device` (noalloc.hip): the device

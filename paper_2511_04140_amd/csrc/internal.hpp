@@ -21,7 +21,7 @@ struct Ctl {
 // its own (a counter is one word every kQueueStride): a launch in workgroups
 // of NW waves uses the first NW of kQueueGroups counters.  The lines after
 // them elect the scanning workgroup.
-constexpr int kQueueGroups = 8;
+constexpr int kQueueGroups = 12;
 constexpr int kRoleLines = 16;
 constexpr int kQueueStride = 16;
 // and those of decompression's draws, kDrawGroups lines from kDrawLine on,
@@ -32,7 +32,7 @@ constexpr int kDrawLine = kQueueGroups + 1 + kRoleLines;
 constexpr int kDrawGroups = 64;
 constexpr uint64_t kDrawFrom = 4;
 constexpr int kQueueWords = kQueueStride * (kDrawLine + kDrawGroups);
-constexpr int kQueueSlack = 4096;  // size and offset words past the chunks (the scan reads ahead)
+constexpr int kQueueSlack = 8192;  // size and offset words past the chunks (the scan reads ahead)
 
 // Time stamps of a timed launch, in ticks of the device's constant-rate
 // clock: words 0-2 the launch's start and, for compression, when the last
@@ -129,6 +129,17 @@ constexpr int kScanTile = 4096;  // chunk sizes per workgroup of the scans
 // CU); 16-wave workgroups would fit only one.
 constexpr int pass_waves(int dtype) { return dtype == 1 ? 8 : 16; }
 constexpr int kDecompressWaves = 4;   // wavefronts per decompression workgroup
+
+// Wavefronts per workgroup of a compression launch, which sets its ticket
+// counters and its scanning waves too: 4 up to 1,024 chunks (queue_waves),
+// beyond that 8, and 12 in float32 (two workgroups hold a CU's 24 waves).
+// float32 chunks are half as large, and one scanning workgroup of 8 waves
+// kept up with 490 of them a microsecond: 512 MiB of mixed float32, 8 against
+// 12 waves, 267 / 248 us, 256 MiB of decimals 143 / 125, 32 MiB 38.5 / 35.3;
+// 16 waves leave 4 a SIMD (286 / 141 / 33.3).  float64 in 16-wave
+// workgroups: 2 GiB of readings 781 / 827.
+constexpr int queue_large(int form) { return form == 1 ? 12 : 8; }
+constexpr int queue_nw(int form, int nw) { return nw == 4 ? 4 : queue_large(form); }
 
 // Kernel forms: one instantiation per dtype (1 = f32, 2 = f64) and a mixed
 // one (3) that takes either dtype per series.

@@ -56,15 +56,15 @@ static void launch_queue(const CompressArgs& a, int grid, hipStream_t s) {
 }
 
 hipError_t launch_compress_queue_f32(const CompressArgs& a, int nw, int grid, hipStream_t s) {
-  if (nw == 8) launch_queue<8>(a, grid, s);
+  if (nw == queue_large(1)) launch_queue<queue_large(1)>(a, grid, s);
   else launch_queue<4>(a, grid, s);
   return hipGetLastError();
 }
 
 // for the occupancy; launches of one series hold as many workgroups per CU
 const void* compress_queue_kernel_f32(int nw) {
-  return nw == 8 ? reinterpret_cast<const void*>(&k_compress_queue<TF32, 8, true>)
-                 : reinterpret_cast<const void*>(&k_compress_queue<TF32, 4, true>);
+  return nw == queue_large(1) ? reinterpret_cast<const void*>(&k_compress_queue<TF32, queue_large(1), true>)
+                              : reinterpret_cast<const void*>(&k_compress_queue<TF32, 4, true>);
 }
 
 }  // namespace falcon_dev

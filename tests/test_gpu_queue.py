@@ -157,3 +157,18 @@ def test_streams_in_turn(orc):
             assert np.array_equal(buf[: ln.value].cpu().numpy(), want)
         torch.cuda.synchronize()
     c.close()
+
+
+@pytest.mark.parametrize("chunks", [4607, 4608, 4609, 9217])
+def test_scan_rounds_of_float32(orc, chunks):
+    """float32 launches past 1,024 chunks run in workgroups of 12 waves, whose
+    scanning one takes 4,608 sizes a round."""
+    from paper_2511_04140_amd import codec as C
+    c = C.Codec(0)
+    x = _data(1025 * chunks - 9, "f32", chunks)
+    xd = torch.from_numpy(x).cuda()
+    want = np.frombuffer(orc.compress(x), np.uint8)
+    torch.cuda.synchronize()
+    for _ in range(2):
+        assert np.array_equal(c.compress(xd).cpu().numpy(), want)
+    c.close()
