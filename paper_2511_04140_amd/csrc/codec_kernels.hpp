@@ -3,8 +3,8 @@
 //
 // Compression runs in one launch with a work queue (k_compress_queue); where
 // nothing may be kept between calls, and for the ablation variants, in two
-// passes (k_compress_pass) around a scan of the sizes.  Decompression follows
-// a scan of the size array.
+// passes (k_compress_pass) around a scan of the sizes.  Decompression is one
+// launch that adds the sizes up itself, or follows one that does.
 #pragma once
 
 #include <type_traits>
@@ -1324,13 +1324,14 @@ __attribute__((amdgpu_waves_per_eu((T::W == 32 && WB == wave_blocks<T>()) ? 6 : 
 // wave waits between taking a chunk and publishing its size.  Both matter: an
 // offset needs the size of every earlier chunk, of which some 4,000 are under
 // way, so the slowest of them sets the wait.  Waiting right after the
-// assembly cost 500 us of 1,350 on 2 GiB of float64 readings; here it costs
-// nothing measurable.
-// Bound by instruction issue on decimal data and float32 (VALU at 60-70 % of
-// its rate), by memory on float64 readings.  Against a size pass, three scan
-// launches and a write pass, which read the input twice: 2 GiB of float64
-// readings 1,200 -> 810 us, of two-place decimals 1,075 -> 680 us, 1 GiB of
-// float32 645 -> 530 us, 8 MiB of decimals 47 -> 19 us, 16 KB 40 -> 15 us.
+// assembly cost 500 us of 1,350 on 2 GiB of float64 readings; here a chunk
+// waits 1.1 us of 14.6 there, 0.75 of 10.9 on decimals, 2.3 of 11.6 in float32.
+// Bound by memory on float64 readings, by the scanning workgroup on float32
+// (528 chunks a microsecond), by instruction issue on float64 decimals.
+// Against a size pass, three scan launches and a write pass, which read the
+// input twice: 2 GiB of float64 readings 1,208 -> 787 us, 512 MiB of
+// two-place decimals 300 -> 171, 512 MiB of mixed float32 353 -> 253, 8 MiB of
+// decimals 47 -> 15.5, 16 KB 38 -> 10.6 (per call in a row of calls).
 // Sizes and offsets travel through device-scope words that are zero between
 // launches: the scanning workgroup clears a size when it has read it, a wave
 // an offset, and the last to draw from a counter that counter, so a launch
@@ -1407,6 +1408,15 @@ __device__ __forceinline__ bool take_scan_role(const CompressArgs& a) {
   const uint64_t first = __hip_atomic_fetch_add(role, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (first == lines - 1) qstore(role, (uint64_t)0);
   return first == 0;
+}
+
+// The number of workgroups that came before this one (called by one thread);
+// the last clears the word.
+__device__ __forceinline__ uint32_t take_number(const CompressArgs& a) {
+  uint64_t* const role = a.qctr + (size_t)kQueueStride * kQueueGroups;
+  const uint64_t k = __hip_atomic_fetch_add(role, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (k == gridDim.x - 1) qstore(role, (uint64_t)0);
+  return (uint32_t)k;
 }
 
 // a10 by one workgroup: sizes to offsets in chunk order, each series' offsets
@@ -1670,16 +1680,28 @@ __device__ __forceinline__ void empty_launch(const CompressArgs& a, int lane, in
 
 // Tables, the headers of empty series, and the workgroup's role: true if it
 // is the scanning one (or the launch has no chunk).
+//
+// Where every chunk has a wave of its own (fits), nothing is drawn: the
+// workgroups count themselves at one word, the first scans, and workgroup
+// 1 + k takes the chunks NW * k to NW * k + NW - 1.  Numbered as they come, a
+// wave waits only for workgroups that came before its own, all resident.
+// Saves the wait for a ticket: 1,000 float64 values 10.9 -> 10.1 us a call,
+// 100,003 12.1 -> 11.2, 1 Mi 16.2 -> 15.4, 1 Mi float32 14.8 -> 14.1.
+template <int NW>
+__device__ __forceinline__ bool chunks_fit(const CompressArgs& a) {
+  return a.total_chunks <= (uint64_t)(gridDim.x - 1) * NW;
+}
 template <bool MANY, int NW, int WB>
-__device__ __forceinline__ bool queue_prologue(BlockLdsT<NW, WB>& sm, const CompressArgs& a) {
+__device__ __forceinline__ bool queue_prologue(BlockLdsT<NW, WB>& sm, const CompressArgs& a, uint64_t& first) {
   uint32_t* const role = reinterpret_cast<uint32_t*>(&sm.wave[0][0]);
-  if (threadIdx.x == 0) *role = a.total_chunks == 0 || take_scan_role(a) ? 1u : 0u;
+  if (threadIdx.x == 0) *role = a.total_chunks == 0 ? 0u : chunks_fit<NW>(a) ? take_number(a) : take_scan_role(a) ? 0u : 1u;
   load_tables(sm.tab);
   if (MANY) empty_series_headers(a);
   __syncthreads();
-  const bool scan = uniform(*role) != 0;
+  const uint32_t r = uniform(*role);
   __syncthreads();  // before the buffer is used
-  return scan;
+  first = (uint64_t)(r - 1) * NW + uniform(threadIdx.x >> 6);
+  return r == 0;
 }
 
 // One dtype per launch.  MANY: a batch launch; one of a single series keeps
@@ -1692,7 +1714,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(T::W ==
   const uint64_t t_start = now_ticks();
   const int lane = lane_id();
   const int wid = (int)uniform(threadIdx.x >> 6);
-  if (queue_prologue<MANY>(sm, a)) {
+  uint64_t first;
+  if (queue_prologue<MANY>(sm, a, first)) {
     if (a.total_chunks == 0) empty_launch<MANY>(a, lane, wid, t_start);
     else scan_group<NW, MANY>(a, reinterpret_cast<ScanPart*>(&sm.wave[0][1]), lane, wid, t_start);
     return;
@@ -1701,8 +1724,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(T::W ==
   int hint = -1;
   bool pending = false;
   Waiting p{0, 0, 0};
-  for (;;) {
-    const uint64_t t = take_chunk<NW>(a, (uint32_t)wid, lane);
+  const bool fits = chunks_fit<NW>(a);
+  for (bool more = true; more; more = !fits) {
+    const uint64_t t = fits ? first : take_chunk<NW>(a, (uint32_t)wid, lane);
     if (t >= a.total_chunks) break;
     const Waiting cur{t, MANY ? find_index(a.many, a.nseries, t + a.t0) : 0u, 0};
     const CompressSeries sd = get_series<MANY>(a.one, a.many, cur.series);
@@ -1724,7 +1748,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
   const uint64_t t_start = now_ticks();
   const int lane = lane_id();
   const int wid = (int)uniform(threadIdx.x >> 6);
-  if (queue_prologue<true>(sm, a)) {
+  uint64_t first;
+  if (queue_prologue<true>(sm, a, first)) {
     if (a.total_chunks == 0) empty_launch<true>(a, lane, wid, t_start);
     else scan_group<NW, true>(a, reinterpret_cast<ScanPart*>(&sm.wave[0][1]), lane, wid, t_start);
     return;
@@ -1733,8 +1758,9 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
   int hint = -1;
   bool pending = false, pending64 = false;
   Waiting p{0, 0, 0};
-  for (;;) {
-    const uint64_t t = take_chunk<NW>(a, (uint32_t)wid, lane);
+  const bool fits = chunks_fit<NW>(a);
+  for (bool more = true; more; more = !fits) {
+    const uint64_t t = fits ? first : take_chunk<NW>(a, (uint32_t)wid, lane);
     if (t >= a.total_chunks) break;
     const Waiting cur{t, find_index(a.many, a.nseries, t + a.t0), 0};
     const CompressSeries sd = get_series<true>(a.one, a.many, cur.series);

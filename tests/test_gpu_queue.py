@@ -172,3 +172,22 @@ def test_scan_rounds_of_float32(orc, chunks):
     for _ in range(2):
         assert np.array_equal(c.compress(xd).cpu().numpy(), want)
     c.close()
+
+
+@pytest.mark.parametrize("dt,chunks", [("f64", 4087), ("f64", 4088), ("f64", 4089), ("f32", 6131), ("f32", 6132),
+                                       ("f32", 6133)])
+def test_a_wave_per_chunk(orc, dt, chunks):
+    """Launches whose chunks all have a wave of their own (511 workgroups of 8
+    waves in float64, of 12 in float32, beside the scanning one) draw nothing;
+    one chunk more and they do.  In turn, on the same words."""
+    from paper_2511_04140_amd import codec as C
+    c = C.Codec(0)
+    x = _data(1025 * chunks - 1000, dt, chunks)
+    xd = torch.from_numpy(x).cuda()
+    small = xd[: 1025 * 30 + 1].clone()
+    want, want_small = (np.frombuffer(orc.compress(v.cpu().numpy()), np.uint8) for v in (xd, small))
+    torch.cuda.synchronize()
+    for _ in range(2):
+        assert np.array_equal(c.compress(xd).cpu().numpy(), want)
+        assert np.array_equal(c.compress(small).cpu().numpy(), want_small)
+    c.close()
