@@ -90,7 +90,11 @@ falcon_status batch_layout(BatchScratch& b, int op, const falcon_series* s, size
   L.op = op;
   L.count = count;
   const size_t dsz = op == FALCON_OP_COMPRESS ? sizeof(CompressSeries) : sizeof(DecompressSeries);
-  L.desc_bytes = count * dsz;
+  uint64_t total = 0;
+  for (size_t i = 0; i < count; ++i) total += chunks_of(s[i].n);
+  const uint64_t nindex = (total >> kIndexShift) + 2;
+  L.index_at = count * dsz;
+  L.desc_bytes = L.index_at + 4 * nindex;
   falcon_status r = grow(&b.h_desc, &b.h_desc_cap, L.desc_bytes, 1, true, st);
   if (r != FALCON_OK) return r;
   uint64_t t = 0;
@@ -135,6 +139,19 @@ falcon_status batch_layout(BatchScratch& b, int op, const falcon_series* s, size
     }
   }
   L.total = t;
+  // the index: the last series with chunk0 <= 64 k
+  uint32_t* const index = reinterpret_cast<uint32_t*>(b.h_desc + L.index_at);
+  uint64_t c = 0, filled = 0;
+  k = 0;
+  for (int pass = 0; pass < 2; ++pass) {
+    for (size_t i = 0; i < count; ++i) {
+      if ((s[i].dtype == FALCON_FLOAT64) != (pass == 0)) continue;
+      c += chunks_of(s[i].n);
+      for (; filled < nindex && filled << kIndexShift < c; ++filled) index[filled] = (uint32_t)k;
+      ++k;
+    }
+  }
+  for (; filled < nindex; ++filled) index[filled] = (uint32_t)(count - 1);
   if ((r = grow(&b.many, &b.many_cap, L.desc_bytes, 1, false, st)) != FALCON_OK ||
       (r = grow(&b.lens, &b.lens_cap, count, 8, true, st)) != FALCON_OK)
     return r;
@@ -171,6 +188,7 @@ falcon_status batch_enqueue(const falcon_ctx* ctx, BatchScratch& b, const BatchL
     a.one = L.one_c;
     a.many = static_cast<const CompressSeries*>(b.many);
     a.nseries = (uint32_t)L.count;
+    a.index = reinterpret_cast<const uint32_t*>(static_cast<const uint8_t*>(b.many) + L.index_at);
     a.lens = b.lens;
     a.qctr = b.q.ctr;
     a.qsize = b.q.size;
@@ -192,6 +210,7 @@ falcon_status batch_enqueue(const falcon_ctx* ctx, BatchScratch& b, const BatchL
   a.one = L.one_d;
   a.many = static_cast<const DecompressSeries*>(b.many);
   a.nseries = (uint32_t)L.count;
+  a.index = reinterpret_cast<const uint32_t*>(static_cast<const uint8_t*>(b.many) + L.index_at);
   a.ctl = b.ctl;
   a.epoch = kBatchEpoch;
   a.qctr = b.q.ctr;

@@ -1146,17 +1146,28 @@ __device__ __forceinline__ void decompress_chunk(const LdsTables& sm, uint8_t* b
 // ---------------------------------------------------------------------------
 // Kernels
 // ---------------------------------------------------------------------------
-// The series of launch chunk t: the last one of the sorted descriptors with
-// chunk0 <= t.
+// The last of the sorted descriptors lo .. hi with chunk0 <= t (many[lo] is
+// one).
 template <class Series>
-__device__ __forceinline__ uint32_t find_index(const Series* many, uint32_t ns, uint64_t t) {
-  uint32_t lo = 0, hi = ns - 1;
+__device__ __forceinline__ uint32_t find_between(const Series* many, uint32_t lo, uint32_t hi, uint64_t t) {
   while (lo < hi) {
     const uint32_t mid = (lo + hi + 1) >> 1;
     if (cst(many)[mid].chunk0 <= t) lo = mid;
     else hi = mid - 1;
   }
   return lo;
+}
+// The series of launch chunk t: the last one of the sorted descriptors with
+// chunk0 <= t.
+template <class Series>
+__device__ __forceinline__ uint32_t find_index(const Series* many, uint32_t ns, uint64_t t) {
+  return find_between(many, 0, ns - 1, t);
+}
+// The same by the batch's index (see kIndexShift).
+template <class Series>
+__device__ __forceinline__ uint32_t find_series(const Series* many, const uint32_t* index, uint64_t t) {
+  const const_ptr<uint32_t> at = cst(index + (t >> kIndexShift));
+  return find_between(many, at[0], at[1], t);
 }
 // Series i of a launch: of one series (MANY unset) its descriptor travels in
 // the arguments; else it is read as 8-byte scalar loads (a struct copy
@@ -1728,7 +1739,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(T::W ==
   for (bool more = true; more; more = !fits) {
     const uint64_t t = fits ? first : take_chunk<NW>(a, (uint32_t)wid, lane);
     if (t >= a.total_chunks) break;
-    const Waiting cur{t, MANY ? find_index(a.many, a.nseries, t + a.t0) : 0u, 0};
+    const Waiting cur{t, MANY ? find_series(a.many, a.index, t + a.t0) : 0u, 0};
     const CompressSeries sd = get_series<MANY>(a.one, a.many, cur.series);
     typename T::U vb[17];
     load_chunk<T>(sd, t + a.t0 - sd.chunk0, lane, vb);
@@ -1762,7 +1773,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(4))) vo
   for (bool more = true; more; more = !fits) {
     const uint64_t t = fits ? first : take_chunk<NW>(a, (uint32_t)wid, lane);
     if (t >= a.total_chunks) break;
-    const Waiting cur{t, find_index(a.many, a.nseries, t + a.t0), 0};
+    const Waiting cur{t, find_series(a.many, a.index, t + a.t0), 0};
     const CompressSeries sd = get_series<true>(a.one, a.many, cur.series);
     const bool is64 = uniform(sd.dtype) == 2;
     // float64 chunks come first, so a wave changes its dtype once at most
@@ -1833,7 +1844,7 @@ __device__ __forceinline__ void decompress_loop(const DecompressArgs& a, const u
     if (l == 0) ticket = __hip_atomic_fetch_add(ctr, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   };
   auto series = [&](uint64_t x) {
-    DecompressSeries sd = get_series<MANY>(a.one, a.many, MANY ? find_index(a.many, a.nseries, x + a.t0) : 0u);
+    DecompressSeries sd = get_series<MANY>(a.one, a.many, MANY ? find_series(a.many, a.index, x + a.t0) : 0u);
     if (sd.payload_bytes == kFromHeader) {
       bool ok;
       sd.payload_bytes = header_payload(sd, ok);

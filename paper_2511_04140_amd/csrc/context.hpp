@@ -96,7 +96,8 @@ struct BatchLayout {
   bool has64 = false, has32 = false;
   falcon_dev::CompressSeries one_c{};
   falcon_dev::DecompressSeries one_d{};
-  size_t desc_bytes = 0;
+  size_t desc_bytes = 0;  // descriptors and the index behind them
+  size_t index_at = 0;
 };
 
 // Device and pinned scratch of batch launches; grows on demand.  Scratch

@@ -191,3 +191,22 @@ def test_a_wave_per_chunk(orc, dt, chunks):
         assert np.array_equal(c.compress(xd).cpu().numpy(), want)
         assert np.array_equal(c.compress(small).cpu().numpy(), want_small)
     c.close()
+
+
+@pytest.mark.parametrize("tail", [0, 1, 64])
+def test_series_of_a_batch_by_index(orc, tail):
+    """Batches whose series begin and end around every 64th launch chunk, empty
+    ones between them, at the front and at the end."""
+    from paper_2511_04140_amd import codec as C
+    c = C.Codec(0)
+    chunks = [0, 1, 64, 0, 62, 1, 0, 128, 1, 0, 0, 63, 5, 64] * 4 + [1] * 130 + [tail]
+    xs = [_data(max(0, 1025 * k - (i % 3)) if k else 0, "f64" if i % 2 else "f32", i) for i, k in enumerate(chunks)]
+    xd = [torch.from_numpy(x).cuda() for x in xs]
+    torch.cuda.synchronize()
+    got = c.compress_batch(xd)
+    for x, s in zip(xs, got):
+        assert s.cpu().numpy().tobytes() == orc.compress(x)
+    ys = c.decompress_batch(got, [x.size for x in xs], [x.dtype for x in xd])
+    for x, y in zip(xs, ys):
+        assert y.cpu().numpy().tobytes() == x.tobytes()
+    c.close()
