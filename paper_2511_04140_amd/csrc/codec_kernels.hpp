@@ -905,8 +905,7 @@ __device__ __forceinline__ Staged stage_issue(const DecompressArgs& a, const uin
   const uint32_t* sizes = reinterpret_cast<const uint32_t*>(sd.in + kHdrBytes);
   st.S = uniform(cst(sizes)[c]);
   const uint64_t off = chunk_offset<DIRECT>(a, tiles, sizes, c, t, lane);
-  st.bad = st.S > hi || st.S < lo || off + st.S > sd.payload_bytes ||
-           (c == nc - 1 && off + st.S != sd.payload_bytes);
+  st.bad = st.S > hi || st.S < lo || !payload_inside(off, st.S, sd.payload_bytes, c == nc - 1);
   st.pad = 0;
   st.total = 0;
   st.sal = payload;

@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "offsets.hpp"
+
 namespace falcon_dev {
 
 // Control block of a launch queue, in pinned host memory so that the host
@@ -130,7 +132,6 @@ struct DecompressArgs {
 // chunks 12.2 / 16.7, 2,047 chunks 14.9 / 18.8, 4,093 chunks 28.0 / 27.6.
 // Plans of series of 1-360 chunks: 200 of them 57 / 67 us, 2,000 309 / 323.
 constexpr uint64_t kDirectChunks = 4096;
-constexpr int kScanTile = 4096;  // chunk sizes per workgroup of the scans
 
 // Wavefronts per workgroup of the two compression passes.  The float32
 // passes run 6 waves per SIMD (their LDS buffer is half the float64 one and

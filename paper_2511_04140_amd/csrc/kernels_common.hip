@@ -104,7 +104,7 @@ __global__ __launch_bounds__(256) void k_scan_local(DecompressSeries one, const 
           ++i;
           enter();
         }
-        v[k] = reinterpret_cast<const uint32_t*>(sd.in + kHdrBytes)[t - sd.chunk0];
+        v[k] = scan_size(reinterpret_cast<const uint32_t*>(sd.in + kHdrBytes)[t - sd.chunk0]);
         sum += v[k];
       }
     }
