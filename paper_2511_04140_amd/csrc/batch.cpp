@@ -13,7 +13,7 @@
 // and its scanning workgroup starts every series' offsets at 0 (see
 // codec_kernels.hpp).  A run never depends on host state beyond its
 // descriptors: the queue's words are clear before and after every launch,
-// the error words are cleared on the host after each run, and the launch
+// the error words are cleared on the host before each run, and the launch
 // epoch is fixed, so a recorded graph can be replayed (no memset nodes).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -167,9 +167,20 @@ falcon_status batch_layout(BatchScratch& b, int op, const falcon_series* s, size
   return FALCON_OK;
 }
 
+// Nothing of an earlier run may reach this one's result, also where that
+// run's was never asked for (the tuner's runs, an enqueue or a wait that
+// failed): the error words are cleared, and the queue's words again if it
+// gave up.  The scratch never grows here.
+falcon_status batch_begin(BatchScratch& b, const BatchLayout& L, hipStream_t s) {
+  b.ctl->error = 0;
+  (void)queue_failed(b.ctl, b.q);
+  return queue_prepare(b.q, L.op == FALCON_OP_COMPRESS ? L.total : 0, s);
+}
+
 falcon_status batch_enqueue(const falcon_ctx* ctx, BatchScratch& b, const BatchLayout& L, const BatchGeom& g,
                             hipStream_t s, bool upload) {
-  falcon_status st;
+  falcon_status st = batch_begin(b, L, s);
+  if (st != FALCON_OK) return st;
   if (upload && (st = dev_err(hipMemcpyAsync(b.many, b.h_desc, L.desc_bytes, hipMemcpyHostToDevice, s))) !=
                     FALCON_OK)
     return st;
@@ -228,9 +239,7 @@ falcon_status batch_enqueue(const falcon_ctx* ctx, BatchScratch& b, const BatchL
 
 falcon_status batch_result(BatchScratch& b, const BatchLayout& L, const falcon_series* src,
                            falcon_series* dst) {
-  const uint32_t err = b.ctl->error;
-  b.ctl->error = 0;  // for the next run
-  if (L.op == FALCON_OP_DECOMPRESS && err == kBatchEpoch) return FALCON_ERR_CORRUPT_STREAM;
+  if (L.op == FALCON_OP_DECOMPRESS && b.ctl->error == kBatchEpoch) return FALCON_ERR_CORRUPT_STREAM;
   if (queue_failed(b.ctl, b.q)) return FALCON_ERR_DEVICE;
   if (dst)
     for (size_t i = 0; i < L.count; ++i) dst[i].out_len = L.op == FALCON_OP_COMPRESS ? b.lens[i] : src[i].n;
@@ -415,9 +424,9 @@ falcon_status falcon_plan_create(falcon_ctx* ctx, falcon_op op, const falcon_ser
   if (st == FALCON_OK) st = dev_err(hipStreamSynchronize(p->stream));
   if (st == FALCON_OK && (flags & FALCON_PLAN_TUNE)) st = autotune(p);
   if (st == FALCON_OK && (flags & FALCON_PLAN_GRAPH)) {
-    if (hipStreamBeginCapture(p->stream, hipStreamCaptureModeThreadLocal) != hipSuccess) {
-      st = FALCON_ERR_DEVICE;
-    } else {
+    st = batch_begin(p->scratch, p->layout, p->stream);  // what it may have to clear is not recorded
+    if (st == FALCON_OK) st = dev_err(hipStreamBeginCapture(p->stream, hipStreamCaptureModeThreadLocal));
+    if (st == FALCON_OK) {
       const falcon_status est = batch_enqueue(ctx, p->scratch, p->layout, p->geom, p->stream, false);
       const hipError_t ce = hipStreamEndCapture(p->stream, &p->graph);
       if (est != FALCON_OK) st = est;
@@ -437,13 +446,12 @@ falcon_status falcon_plan_run(falcon_plan* p, falcon_series* s, void* stream) {
   if (!p) return FALCON_ERR_INVALID_ARG;
   if (hipSetDevice(p->ctx->device) != hipSuccess) return FALCON_ERR_DEVICE;
   hipStream_t hs = stream ? static_cast<hipStream_t>(stream) : p->stream;
-  // clears the queue's words again if the last run gave up (never grows them)
-  falcon_status st = p->layout.op == FALCON_OP_COMPRESS
-                         ? queue_prepare(p->scratch.q, p->layout.total ? p->layout.total : 1, hs)
-                         : FALCON_OK;
-  if (st != FALCON_OK) return st;
-  st = p->exec ? dev_err(hipGraphLaunch(p->exec, hs))
-                             : batch_enqueue(p->ctx, p->scratch, p->layout, p->geom, hs, false);
+  falcon_status st = FALCON_OK;
+  if (p->exec) {
+    if ((st = batch_begin(p->scratch, p->layout, hs)) == FALCON_OK) st = dev_err(hipGraphLaunch(p->exec, hs));
+  } else {
+    st = batch_enqueue(p->ctx, p->scratch, p->layout, p->geom, hs, false);
+  }
   if (st != FALCON_OK) return st;
   if ((st = dev_err(hipStreamSynchronize(hs))) != FALCON_OK) return st;
   return batch_result(p->scratch, p->layout, p->series.data(), s);

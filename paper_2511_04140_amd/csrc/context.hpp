@@ -227,8 +227,12 @@ falcon_status batch_check(int op, const falcon_series& d);
 // grows the device scratch to fit (waiting for `s` first if it grows).
 falcon_status batch_layout(BatchScratch& b, int op, const falcon_series* s, size_t count, BatchLayout& L,
                            hipStream_t st);
-// Enqueues one run: descriptor upload (if upload), clearing fills, the
-// launches, and the copy of the lengths or the error word to pinned memory.
+// Makes ready for a run that is enqueued otherwise (a recorded graph); the
+// run before it has completed.
+falcon_status batch_begin(BatchScratch& b, const BatchLayout& L, hipStream_t s);
+// Enqueues one run, the one before it having completed: batch_begin,
+// descriptor upload (if upload) and the launches.  Lengths and error words
+// land in pinned memory.
 falcon_status batch_enqueue(const falcon_ctx* ctx, BatchScratch& b, const BatchLayout& L, const BatchGeom& g,
                             hipStream_t s, bool upload);
 // After the run has completed: the error status, and each dst[i].out_len

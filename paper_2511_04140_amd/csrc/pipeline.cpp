@@ -374,6 +374,7 @@ falcon_status falcon_compress_host(falcon_ctx* ctx, const void* h_in, size_t n, 
   j.out_pinned = is_pinned(h_out);
   falcon_status st = pipe_ensure(ctx, !(j.in_pinned && j.out_pinned));
   if (st != FALCON_OK) return st;
+  for (auto& p : ctx->pipe) (void)compress_failed(p.lane);  // of a call that returned before it asked
   uint64_t total = 0;
   if (ctx->pipe_scheduler == FALCON_SCHED_SYNC_BASED) st = compress_sync_based(ctx, j, &total);
   else if (ctx->pipe_scheduler == FALCON_SCHED_PRE_ALLOCATION) st = compress_pre_allocation(ctx, j, &total);
