@@ -77,8 +77,9 @@ typedef struct falcon_ctx falcon_ctx;
  * Waves take chunks from a work queue (ticket counters), publish each
  * chunk's size (Sec. 3.3), and write its payload when its offset has
  * arrived from the workgroup that does the launch's prefix sum (Sec. 3.4);
- * the input is read once.  The launch makes progress with any number of its
- * workgroups resident. */
+ * the input is read once.  The launch makes progress once two of its
+ * workgroups are resident (that one and any other), whatever else the device
+ * runs; until then it waits. */
 typedef enum falcon_compress_form {
   FALCON_FORM_TWO_PASS = 0,
   FALCON_FORM_SINGLE_PASS = 1

@@ -365,7 +365,12 @@ falcon_status falcon_sync(falcon_ctx* ctx) {
     // chunk failed: a launch since the last sync has a larger one
     const uint32_t err = l.ctl->error;
     if (err != 0 && err > ctx->sync_epoch && err <= l.epoch) st = FALCON_ERR_CORRUPT_STREAM;
-    if (compress_failed(l)) st = FALCON_ERR_DEVICE;
+    if (compress_failed(l)) {
+      // cleared here and not before the next call, which may be the replay of
+      // a recorded one
+      st = FALCON_ERR_DEVICE;
+      if (queue_prepare(l.q, 0, ctx->last_stream) == FALCON_OK) (void)hipStreamSynchronize(ctx->last_stream);
+    }
   }
   ctx->pending.clear();
   ctx->sync_epoch = l.epoch;

@@ -11,6 +11,7 @@
 
 #include "codec_device.hpp"
 #include "internal.hpp"
+#include "queue_wait.hpp"
 
 namespace falcon_dev {
 
@@ -1354,8 +1355,9 @@ __attribute__((amdgpu_waves_per_eu((T::W == 32 && WB == wave_blocks<T>()) ? 6 : 
 // it publishes; if not, every chunk its counter has handed out is smaller, so
 // the wave of that counter in any resident working workgroup comes to it (the
 // offset it may wait for first is smaller still, and delivered).  So the queue
-// drains with the scanning workgroup and any one other resident, whatever
-// else runs on the device.  The waits are bounded all the same: past their
+// drains with the scanning workgroup and any one other resident; until the
+// other has come, the scanning one waits for it (ScanWait), as any launch waits
+// for a place on the chip.  The waits of taken chunks are bounded: past their
 // limits (or once another wave has given up) a wave sets ctl->qerror and
 // leaves; no payload is written without its offset, and none past the nc
 // chunk bounds that the caller's buffer holds.
@@ -1365,7 +1367,6 @@ constexpr uint64_t kOffReady = 1ull << 63;   // offset word: delivered (0: not y
 constexpr uint32_t kSizeHead = 1u << 31;     // the first chunk of its series
 constexpr uint32_t kSizeMask = kSizeHead - 1;
 constexpr uint32_t kWaitLimit = 1u << 20;    // rereads of an offset, a microsecond or so each
-constexpr uint32_t kScanLimit = 1u << 22;    // rounds of the scanning wave without a new size
 
 template <class W>
 __device__ __forceinline__ W qload(const W* p) {
@@ -1429,6 +1430,13 @@ __device__ __forceinline__ uint32_t take_number(const CompressArgs& a) {
   return (uint32_t)k;
 }
 
+// Whether every chunk has a wave of its own, and nothing is drawn
+// (queue_prologue).
+template <int NW>
+__device__ __forceinline__ bool chunks_fit(const CompressArgs& a) {
+  return a.total_chunks <= (uint64_t)(gridDim.x - 1) * NW;
+}
+
 // a10 by one workgroup: sizes to offsets in chunk order, each series' offsets
 // starting at 0 (a size word carries its series' first-chunk mark).  It has
 // to keep up with the whole chip, some 500 chunks a microsecond, and nothing
@@ -1452,7 +1460,12 @@ __device__ __forceinline__ void scan_group(const CompressArgs& a, ScanPart* part
   constexpr uint32_t kPart = 64 * kScanBlocks;
   static_assert(NW * kPart <= kQueueSlack && NW <= kQueueGroups, "a round's reads stay inside the size words");
   uint64_t t = 0, carry = 0, seen = 0;
-  uint32_t idle = 0;
+  ScanWait wait;
+  auto taken = [&] {
+    const bool fits = chunks_fit<NW>(a);
+    const uint64_t* const word = a.qctr + (fits ? kQueueStride * kQueueGroups : 0);
+    return chunk_taken(fits, uniform((uint32_t)qload(word)), t, NW);
+  };
   __builtin_amdgcn_s_setprio(3);
   for (uint32_t round = 0; t < a.total_chunks; ++round) {
     const uint64_t at = t + kPart * (uint32_t)wid + (uint32_t)lane;
@@ -1489,7 +1502,7 @@ __device__ __forceinline__ void scan_group(const CompressArgs& a, ScanPart* part
       }
       p.known += m[r];
     }
-    if (wid == 0 && (idle > kScanLimit || ((idle & 255u) == 255u && queue_failed(a.ctl)))) p.failed = 1;
+    if (__builtin_expect(wait.look(), 0) && wid == 0) p.failed = wait.give_up(queue_failed(a.ctl), taken());
     ScanPart* const now = parts + NW * (round & 1u);  // two sets: one barrier a round
     if (lane == 0) now[wid] = p;
     __syncthreads();
@@ -1525,7 +1538,7 @@ __device__ __forceinline__ void scan_group(const CompressArgs& a, ScanPart* part
         }
       }
     }
-    idle = t_next == t ? idle + 1 : 0;
+    if (t_next != t) wait.progress();
     t = t_next;
   }
   __builtin_amdgcn_s_setprio(0);
@@ -1697,10 +1710,6 @@ __device__ __forceinline__ void empty_launch(const CompressArgs& a, int lane, in
 // wave waits only for workgroups that came before its own, all resident.
 // Saves the wait for a ticket: 1,000 float64 values 10.9 -> 10.1 us a call,
 // 100,003 12.1 -> 11.2, 1 Mi 16.2 -> 15.4, 1 Mi float32 14.8 -> 14.1.
-template <int NW>
-__device__ __forceinline__ bool chunks_fit(const CompressArgs& a) {
-  return a.total_chunks <= (uint64_t)(gridDim.x - 1) * NW;
-}
 template <bool MANY, int NW, int WB>
 __device__ __forceinline__ bool queue_prologue(BlockLdsT<NW, WB>& sm, const CompressArgs& a, uint64_t& first) {
   uint32_t* const role = reinterpret_cast<uint32_t*>(&sm.wave[0][0]);
