@@ -42,7 +42,10 @@
  *     call synchronises itself and reports its own errors.
  *   - Successive device calls on one context are ordered even when they use
  *     different streams (they share the context's scratch): a call on a new
- *     stream first waits for the previous call.
+ *     stream first waits for the previous call, not for what its stream holds
+ *     after it.  The stream of the last call stays valid until falcon_sync;
+ *     while it is being captured, calls on other streams are refused
+ *     (FALCON_ERR_DEVICE) unless they follow a falcon_sync.
  *   - The host <-> host calls, batch calls and plan runs are synchronous.
  *   - Errors are reported as status codes; nothing unwinds across the ABI.
  *     On any error the contents of output buffers are unspecified.

@@ -120,6 +120,8 @@ int queue_waves(uint64_t nchunks) { return nchunks <= 1024 ? 4 : 8; }
 static void begin_timed(falcon_ctx* ctx) {
   ctx->ev_slot = (ctx->ev_slot + 1) % FALCON_TIMED_CALLS;
   ctx->ev_kind[ctx->ev_slot] = falcon_ctx::kNotTimed;
+  ctx->done_recorded[ctx->ev_slot] = false;
+  ctx->call_slot = ctx->ev_slot;
 }
 
 // Compression: one launch in which waves take chunks from a work queue and
@@ -236,27 +238,30 @@ hipStream_t call_stream(falcon_ctx* ctx, void* stream) {
 
 falcon_status begin_call(falcon_ctx* ctx, hipStream_t s) {
   if (hipSetDevice(ctx->device) != hipSuccess) return FALCON_ERR_DEVICE;
-  if (ctx->unsynced && ctx->last_stream != s) {
-    // a stream that its owner has destroyed since takes no event: then
-    // everything on the device is waited for
-    if (hipEventRecord(ctx->ev_last, ctx->last_stream) == hipSuccess) {
-      if (hipStreamWaitEvent(s, ctx->ev_last, 0) != hipSuccess) return FALCON_ERR_DEVICE;
-    } else {
-      (void)hipGetLastError();
-      if (hipDeviceSynchronize() != hipSuccess) return FALCON_ERR_DEVICE;
-    }
+  ctx->call_slot = FALCON_TIMED_CALLS;
+  if (!ctx->unsynced || ctx->last_stream == s) return FALCON_OK;
+  if (!ctx->last_event) {  // the last call's stream is the context's own
+    ctx->last_event = ctx->done[FALCON_TIMED_CALLS];
+    if (hipEventRecord(ctx->last_event, ctx->last_stream) != hipSuccess) return FALCON_ERR_DEVICE;
   }
-  return FALCON_OK;
+  if (hipStreamWaitEvent(s, ctx->last_event, 0) == hipSuccess) return FALCON_OK;
+  (void)hipGetLastError();  // reported here, not to the program's next call
+  return FALCON_ERR_DEVICE;
 }
 
 falcon_status end_call(falcon_ctx* ctx, hipStream_t s, falcon_status st) {
   // also after an error, so that a later call or falcon_sync still orders
   // after the work enqueued so far
   ctx->last_stream = s;
+  ctx->last_event = nullptr;
   ctx->unsynced = true;
   if (ctx->opt_flags & FALCON_OPT_BLOCKING) {
     const falcon_status sy = falcon_sync(ctx);
     if (st == FALCON_OK) st = sy;
+  } else if (s != ctx->main.stream) {
+    ctx->last_event = ctx->done[ctx->call_slot];
+    ctx->done_recorded[ctx->call_slot] = hipEventRecord(ctx->last_event, s) == hipSuccess;
+    if (!ctx->done_recorded[ctx->call_slot] && st == FALCON_OK) st = FALCON_ERR_DEVICE;
   }
   return st;
 }
@@ -321,8 +326,9 @@ falcon_status falcon_create(int device, const falcon_opts* opts, falcon_ctx** ou
   if (!ctx) return FALCON_ERR_OUT_OF_MEMORY;
   ctx->device = device;
   ctx->opt_flags = flags;
-  bool ok = lane_init(ctx->main) == FALCON_OK &&
-            hipEventCreateWithFlags(&ctx->ev_last, hipEventDisableTiming) == hipSuccess;
+  bool ok = lane_init(ctx->main) == FALCON_OK;
+  for (int c = 0; ok && c <= FALCON_TIMED_CALLS; ++c)
+    ok = hipEventCreateWithFlags(&ctx->done[c], hipEventDisableTiming) == hipSuccess;
   for (int c = 0; ok && c < FALCON_TIMED_CALLS; ++c)
     for (int i = 0; ok && i < 4; ++i) ok = hipEventCreate(&ctx->ev[c][i]) == hipSuccess;
   constexpr size_t kTimeBytes = (size_t)kTimeWords * 8;
@@ -389,7 +395,8 @@ void falcon_destroy(falcon_ctx* ctx) {
   for (auto& call : ctx->ev)
     for (hipEvent_t e : call)
       if (e) (void)hipEventDestroy(e);
-  if (ctx->ev_last) (void)hipEventDestroy(ctx->ev_last);
+  for (hipEvent_t e : ctx->done)
+    if (e) (void)hipEventDestroy(e);
   for (uint64_t* b : ctx->len_blocks) (void)hipHostFree(b);
   if (ctx->times) (void)hipFree(ctx->times);
   if (ctx->times_host) (void)hipHostFree(ctx->times_host);
@@ -549,9 +556,10 @@ falcon_status falcon_call_stage_ms(falcon_ctx* ctx, unsigned back, float* ms) {
       if (hipEventElapsedTime(ms + i, ev[i], ev[i + 1]) != hipSuccess) return FALCON_ERR_DEVICE;
     return FALCON_OK;
   }
-  // the call's stream, unless a falcon_sync has waited for it already
+  // the call, unless a falcon_sync has waited for it already: its event, or
+  // the context's own stream
   if (hipSetDevice(ctx->device) != hipSuccess ||
-      (ctx->unsynced && hipStreamSynchronize(ctx->last_stream) != hipSuccess) ||
+      (ctx->unsynced && ctx->done_recorded[slot] && hipEventSynchronize(ctx->done[slot]) != hipSuccess) ||
       hipMemcpyAsync(ctx->times_host, ctx->times + (size_t)slot * kTimeWords, (size_t)kTimeWords * 8,
                      hipMemcpyDeviceToHost, ctx->main.stream) != hipSuccess ||
       hipStreamSynchronize(ctx->main.stream) != hipSuccess)

@@ -125,10 +125,18 @@ struct falcon_ctx {
   unsigned opt_flags = 0;   // FALCON_OPT_* of falcon_create
   falcon_host::Lane main;
   // asynchronous device calls: a call on another stream than the last one's
-  // waits for it on the device (ev_last, recorded only then: an event record
-  // costs a call about as much as its launch); falcon_sync waits for
-  // last_stream
-  hipEvent_t ev_last = nullptr;
+  // waits for it on the device (last_event); falcon_sync waits for
+  // last_stream.  After a call on a caller's stream its event is recorded at
+  // once: later the stream may be gone, hold other work or be captured.  On
+  // the context's own stream there is only its own work, so nothing is
+  // recorded until a call changes streams: a record costs 3 us of a call's 16
+  // (32 calls of 100,003 values, 515 us on the own stream, 608 on a caller's).
+  // A timed call has an event of its own (its ring slot),
+  // the others share the last.
+  hipEvent_t done[FALCON_TIMED_CALLS + 1] = {};
+  bool done_recorded[FALCON_TIMED_CALLS + 1] = {};
+  int call_slot = FALCON_TIMED_CALLS;  // of the call being made
+  hipEvent_t last_event = nullptr;     // null: not recorded
   hipStream_t last_stream = nullptr;
   bool unsynced = false;
   uint32_t sync_epoch = 0;  // main lane's launch epoch at the last falcon_sync
