@@ -85,13 +85,18 @@ falcon_status queue_prepare(Queue& q, uint64_t nchunks, hipStream_t s) {
   if (q.ctr && nchunks + kQueueSlack <= q.cap && !q.dirty) return FALCON_OK;
   q.dirty = true;  // until everything below has worked
   if (!q.ctr && hipMalloc(&q.ctr, 8 * kQueueWords) != hipSuccess) return FALCON_ERR_OUT_OF_MEMORY;
+  // room for as many chunks as the other scratch then has: the next power of two
+  uint64_t room = 1024;
+  while (room < nchunks) room *= 2;
+  room += kQueueSlack;
+  if (room < q.cap) room = q.cap;
   const size_t had = q.cap;
   size_t cap = had;
   q.cap = 0;
-  falcon_status st = grow_raw(&q.size, &cap, nchunks + kQueueSlack, s);
+  falcon_status st = grow_raw(&q.size, &cap, room, s);
   if (st != FALCON_OK) return st;
   cap = had;
-  if ((st = grow_raw(&q.off, &cap, nchunks + kQueueSlack, s)) != FALCON_OK) return st;
+  if ((st = grow_raw(&q.off, &cap, room, s)) != FALCON_OK) return st;
   if ((st = dev_err(launch_fill_u64(q.ctr, kQueueWords, 0, s))) != FALCON_OK ||
       (st = dev_err(launch_fill_u64(reinterpret_cast<uint64_t*>(q.size), cap / 2, 0, s))) != FALCON_OK ||
       (st = dev_err(launch_fill_u64(q.off, cap, 0, s))) != FALCON_OK)
@@ -124,6 +129,13 @@ static void begin_timed(falcon_ctx* ctx) {
   ctx->call_slot = ctx->ev_slot;
 }
 
+// The scratch of a decompression of nc chunks, but for its counters.
+static falcon_status grow_decompress(Lane& l, uint64_t nc, hipStream_t s) {
+  if (nc <= kDirectChunks) return FALCON_OK;
+  const falcon_status st = grow_raw(&l.local, &l.local_cap, nc, s);
+  return st != FALCON_OK ? st : grow_raw(&l.tiles, &l.tiles_cap, scan_tiles(nc) + 1, s);
+}
+
 // Compression: one launch in which waves take chunks from a work queue and
 // one workgroup turns their sizes into offsets (k_compress_queue).  The ablation
 // variants run in two passes: a size pass, a scan of the chunk sizes into
@@ -145,8 +157,12 @@ falcon_status enqueue_compress(falcon_ctx* ctx, Lane& l, const void* d_in, uint6
   a.total_chunks = nc;
   a.lens = d_len;
   if (timed) begin_timed(ctx);
+  // a decompression of this size is to find its scratch grown: it may be
+  // recorded into a graph, where nothing can be allocated
+  if ((st = queue_prepare(l.q, variant == 0 ? nc : 0, s)) != FALCON_OK ||
+      (st = grow_decompress(l, nc, s)) != FALCON_OK)
+    return st;
   if (variant == 0) {
-    if ((st = queue_prepare(l.q, nc ? nc : 1, s)) != FALCON_OK) return st;
     const int nw = queue_nw((int)dt, queue_waves(nc));
     a.qctr = l.q.ctr;
     a.qsize = l.q.size;
@@ -192,9 +208,7 @@ falcon_status enqueue_decompress(falcon_ctx* ctx, Lane& l, const uint8_t* d_in, 
   const uint64_t nc = chunks_of(n);
   falcon_status st = FALCON_OK;
   const bool direct = nc <= kDirectChunks;
-  if (!direct && ((st = grow_raw(&l.local, &l.local_cap, nc, s)) != FALCON_OK ||
-                  (st = grow_raw(&l.tiles, &l.tiles_cap, scan_tiles(nc), s)) != FALCON_OK))
-    return st;
+  if ((st = grow_decompress(l, nc, s)) != FALCON_OK) return st;
   // the value a failing launch leaves in the error word
   l.epoch += 1;
   if (l.epoch == 0) l.epoch = 1;
