@@ -97,10 +97,21 @@ falcon_status queue_prepare(Queue& q, uint64_t nchunks, hipStream_t s) {
   if (st != FALCON_OK) return st;
   cap = had;
   if ((st = grow_raw(&q.off, &cap, room, s)) != FALCON_OK) return st;
-  if ((st = dev_err(launch_fill_u64(q.ctr, kQueueWords, 0, s))) != FALCON_OK ||
-      (st = dev_err(launch_fill_u64(reinterpret_cast<uint64_t*>(q.size), cap / 2, 0, s))) != FALCON_OK ||
-      (st = dev_err(launch_fill_u64(q.off, cap, 0, s))) != FALCON_OK)
-    return st;
+  // Cleared now and not by a recorded fill, where s is being captured: calls
+  // that are not recorded use the words too, and may come before any replay.
+  hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+  if ((st = dev_err(hipStreamIsCapturing(s, &capture))) != FALCON_OK) return st;
+  const bool recording = capture != hipStreamCaptureStatusNone;
+  hipStream_t at = s;
+  if (recording && (st = dev_err(hipStreamCreateWithFlags(&at, hipStreamNonBlocking))) != FALCON_OK) return st;
+  if ((st = dev_err(launch_fill_u64(q.ctr, kQueueWords, 0, at))) == FALCON_OK &&
+      (st = dev_err(launch_fill_u64(reinterpret_cast<uint64_t*>(q.size), cap / 2, 0, at))) == FALCON_OK)
+    st = dev_err(launch_fill_u64(q.off, cap, 0, at));
+  if (recording) {
+    if (hipStreamSynchronize(at) != hipSuccess && st == FALCON_OK) st = FALCON_ERR_DEVICE;
+    (void)hipStreamDestroy(at);
+  }
+  if (st != FALCON_OK) return st;
   q.cap = cap;
   q.dirty = false;
   return FALCON_OK;

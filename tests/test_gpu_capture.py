@@ -1,7 +1,9 @@
 """Calls recorded into a graph after eager calls of the same size: the scratch
 is grown by then, and a decompression finds its own grown by the compression
 that made its stream."""
-import numpy as np
+import ctypes
+import re
+
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -74,4 +76,49 @@ def test_calls_up_to_the_next_power_of_two(warm, chunks):
         g.replay()
         torch.cuda.synchronize()
         assert torch.equal(y, x), rep
+    c.close()
+
+
+@pytest.mark.parametrize("chunks", [20, 5000])
+@pytest.mark.parametrize("first", ["replay", "eager"])
+def test_the_first_call_is_recorded(first, chunks):
+    """Where the capture lets memory be allocated, a context's first call can
+    be recorded.  The graph holds what a later capture of the call holds:
+    nothing that clears words which eager calls use as well."""
+    from paper_2511_04140_amd import codec as C
+    n = 1025 * chunks
+    c = C.Codec(0, blocking=False, device_lengths=True)
+    s = torch.cuda.Stream()
+    x = _values(n, 0, torch.float64)
+    buf = torch.empty(C.compress_bound(n, x.dtype), dtype=torch.uint8, device="cuda")
+    y = torch.empty_like(x)
+    ln = torch.zeros(1, dtype=torch.int64, device="cuda")
+    torch.cuda.synchronize()
+    hip = ctypes.CDLL(re.search(r"/\S*libamdhip64\S*", open("/proc/self/maps").read()).group(0))
+
+    def call():
+        c.compress_async(x, buf, out_len=ln, stream=s)
+        c.decompress_n_async(buf, n, x.dtype, y, stream=s)
+
+    def record():
+        g = torch.cuda.CUDAGraph(keep_graph=True)
+        with torch.cuda.graph(g, stream=s, capture_error_mode="relaxed"):
+            call()
+        nodes = ctypes.c_size_t()
+        assert hip.hipGraphGetNodes(ctypes.c_void_p(g.raw_cuda_graph()), None, ctypes.byref(nodes)) == 0
+        g.instantiate()
+        return g, nodes.value
+    g, nodes = record()
+    for rep, how in enumerate((first, "replay", "eager", "replay")):
+        x.copy_(_values(n, rep, x.dtype))
+        y.zero_()
+        torch.cuda.synchronize()
+        if how == "replay":
+            g.replay()
+        else:
+            call()
+            c.sync()
+        torch.cuda.synchronize()
+        assert torch.equal(y, x), rep
+    assert record()[1] == nodes
     c.close()
