@@ -7,6 +7,7 @@ import fails loudly: there is no CPU fallback.
 from __future__ import annotations
 
 import ctypes
+import operator
 import os
 import threading
 
@@ -476,7 +477,12 @@ class Codec:
         if count:
             col = np.frombuffer(descs, _SERIES)
             col["d_in"] = [s_.data_ptr() for s_ in streams]
-            col["n"] = [counts[i] for i in range(count)]
+            # as a ctypes field takes them: integers of any kind, modulo 2^64
+            ns = [operator.index(counts[i]) for i in range(count)]
+            try:
+                col["n"] = ns
+            except OverflowError:
+                col["n"] = [n & 0xFFFFFFFFFFFFFFFF for n in ns]
             col["in_len"] = [s_.numel() for s_ in streams]
             col["d_out"] = [v.data_ptr() for v in views]  # 0 for an empty tensor
             col["out_cap"] = [v.numel() * v.element_size() for v in views]
