@@ -354,14 +354,24 @@ falcon_status autotune(falcon_plan* p) {
         g.grid_pct = pct;
         cands.push_back(g);
       }
+  // the default geometry, which default_ms stands for, is the candidate with
+  // the workgroups that its launches take by themselves; where those of the
+  // two dtypes differ, it is one more
+  size_t def = 0;
+  if (comp) {
+    const int w64 = queue_waves(p->layout.t64), w32 = queue_waves(p->layout.total - p->layout.t64);
+    const int nw = !p->layout.has32 ? w64 : !p->layout.has64 || w32 == w64 ? w32 : 0;
+    while (def < cands.size() && cands[def].nw != nw) ++def;
+    if (def == cands.size()) cands.push_back(BatchGeom());
+  }
   float best = 1e30f;
-  BatchGeom pick = cands[0];
+  BatchGeom pick = cands[def];
   for (size_t i = 0; i < cands.size(); ++i) {
     p->geom = cands[i];
     float ms;
     falcon_status st = time_runs(p, 3, &ms);
     if (st != FALCON_OK) return st;
-    if (i == 0) p->default_ms = ms;
+    if (i == def) p->default_ms = ms;
     if (ms < best) {
       best = ms;
       pick = cands[i];
