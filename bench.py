@@ -40,7 +40,7 @@ def kernel_source_digest():
     h = hashlib.sha256()
     csrc = os.path.join(ROOT, "paper_2511_04140_amd", "csrc")
     for name in sorted(os.listdir(csrc)):
-        if name.endswith(".hip") or name in ("codec_device.hpp", "codec_kernels.hpp"):
+        if name.endswith(".hip") or name in ("codec_device.hpp", "codec_kernels.hpp", "offsets.hpp", "queue_wait.hpp"):
             with open(os.path.join(csrc, name), "rb") as f:
                 h.update(name.encode() + b"\0" + f.read())
     with open(os.path.join(ROOT, "paper_2511_04140_amd", "build.py"), "rb") as f:
@@ -630,8 +630,7 @@ def _kernel_short(name):
     for key, label in (("k_compress_queue<", "k_compress_queue"), ("k_compress_queue_mixed<", "k_compress_queue_mixed"),
                        ("k_decompress_mixed", "k_decompress_mixed"), ("k_decompress<", "k_decompress"),
                        ("k_scan_local", "k_scan_local"), ("k_scan_tiles", "k_scan_tiles"), ("k_scan_tile_sums", "k_scan_tile_sums"),
-                       ("k_scan_apply", "k_scan_apply"), ("k_fill_u64", "k_fill_u64"),
-                       ("k_batch_headers", "k_batch_headers"), ("k_gather_sizes", "k_gather_sizes")):
+                       ("k_scan_apply", "k_scan_apply"), ("k_fill_u64", "k_fill_u64")):
         if key in name:
             return label
     return name[:60]
@@ -927,7 +926,7 @@ def main():
     # and the algorithmic bytes one launch moves
     kernels = {
         "k_compress_queue": (kc_ms, nbytes + clen),  # one launch; its stages overlap
-        "k_scan (decompress)": (float(np.mean([v[1] for v in sd_])), 4 * nc + 8 * nc),
+        "k_scan (decompress)": (float(np.mean([v[1] for v in sd_])), 4 * nc + 4 * nc),
         "k_decompress": (float(np.mean([v[2] for v in sd_])), clen + nbytes),
     }
     dominant = max(kernels, key=lambda k: kernels[k][0])
@@ -963,7 +962,7 @@ def main():
         "dtype": "f32" if f32 else "f64",
         "data": "synthetic",
         "config": {"workload": workload, "n": int(x.size), "bytes": int(nbytes),
-                   "chunk": 1025, "resident": "HBM", "compression_form": args.form,
+                   "chunk": 1025, "resident": "HBM", "compression_form": "one_launch",
                    "calls": "asynchronous falcon_compress + falcon_decompress_n per step, one wait per timed region"},
         "compress_gbps": round(nbytes / (kc_ms * 1e-3) / 1e9, 3),
         "decompress_gbps": round(nbytes / (kd_ms * 1e-3) / 1e9, 3),

@@ -25,7 +25,6 @@
 namespace falcon_dev {
 
 constexpr int kChunk = 1025;      // values per chunk (Sec. 5.1.4, n = 64k + 1)
-constexpr int kWavesC = 16;       // wavefronts per compression workgroup
 constexpr int kWavesD = 4;        // wavefronts per decompression workgroup
 constexpr int kGSlots = kChunk + 65;         // skewed slots: one pad every 16
 constexpr int kWaveLds = kGSlots * 8;        // 8720 bytes per wave
@@ -145,9 +144,6 @@ struct TF64 {
   static constexpr int W = 64, ZB = 8, AMAX = 22, BMAX = 15, MANT = 52;
   static constexpr int MARKSTEIN_MAX = 21;  // decoder's division-free quotient up to 5^alpha < 2^51
   static constexpr int EXPMAX = 0x7FF, BIAS = 1023;
-  // |v| >= 2^50 > 10^15 means FL10 >= 15 (beta > 15 at alpha = 0);
-  // |v| < 2^-74 < fl(10^-22) means FL10 <= -23 (decimal place > 22).
-  static constexpr int E2_HI = 50, E2_LO = -75;
   static constexpr int BOUND = 3 + ZB + 8 + 64 * 128;  // 8211
   static constexpr int POFF = 22;
   static __device__ __forceinline__ F f(U b) { return __longlong_as_double((long long)b); }
@@ -186,9 +182,6 @@ struct TF32 {
   static constexpr int W = 32, ZB = 4, AMAX = 10, BMAX = 6, MANT = 23;
   static constexpr int MARKSTEIN_MAX = 10;  // decoder's division-free quotient (every alpha)
   static constexpr int EXPMAX = 0xFF, BIAS = 127;
-  // |v| >= 2^20 > 10^6 means FL10 >= 6; |v| < 2^-34 < fl(10^-10) means
-  // FL10 <= -11.
-  static constexpr int E2_HI = 20, E2_LO = -35;
   static constexpr int BOUND = 3 + ZB + 4 + 32 * 128;  // 4107
   static constexpr int POFF = 10;
   static __device__ __forceinline__ F f(U b) { return __uint_as_float(b); }
@@ -303,22 +296,6 @@ __device__ __forceinline__ uint32_t wave_sum32(uint32_t v) {
   v += dpp<kDppHalfMirror>(v);
   v += dpp<kDppMirror>(v);
   return rl(v, 0) + rl(v, 16) + rl(v, 32) + rl(v, 48);
-}
-
-// Wave-wide sum of 64-bit values (uniform result), modulo 2^64.
-__device__ __forceinline__ uint64_t wave_sum64(uint64_t v) {
-  auto step = [&](auto ctrl_tag) {
-    constexpr int C = decltype(ctrl_tag)::value;
-    v += ((uint64_t)dpp<C>((uint32_t)(v >> 32)) << 32) | dpp<C>((uint32_t)v);
-  };
-  step(std::integral_constant<int, kDppXor1>{});
-  step(std::integral_constant<int, kDppXor2>{});
-  step(std::integral_constant<int, kDppHalfMirror>{});
-  step(std::integral_constant<int, kDppMirror>{});
-  uint64_t m = 0;
-#pragma unroll
-  for (int r = 0; r < 4; ++r) m += ((uint64_t)rl((uint32_t)(v >> 32), 16 * r) << 32) | rl((uint32_t)v, 16 * r);
-  return m;
 }
 
 // Lane L receives v from lane L ^ B: quad permutes for 1 and 2, a row

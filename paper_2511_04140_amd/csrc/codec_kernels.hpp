@@ -176,7 +176,7 @@ __device__ __forceinline__ bool alg2_literal(const LdsTables& sm, const typename
 // When no value is an exception both bisections are exact and the recover
 // checks pass; so a failed recover check means some value is one, and the
 // chunk gets the exception header, as Alg. 2 would give it.
-template <class T, bool HINT = true>
+template <class T>
 __device__ __forceinline__ void decide_case(const LdsTables& sm, const typename T::U (&vb)[17], int& A, int& B,
                             bool& case1, int& hint) {
   using U = typename T::U;
@@ -234,7 +234,7 @@ __device__ __forceinline__ void decide_case(const LdsTables& sm, const typename 
     // value, and the scale below it fails one, it is the largest place
     // without a bisection
     bool known = false;
-    if (HINT && hint >= 0 && hint <= lstar) {
+    if (hint >= 0 && hint <= lstar) {
       F r;
       const bool pass = eps_test<T>(vb[0], T::pow10(sm, hint), r);
       const bool below = hint != 0 && eps_test<T>(vb[0], T::pow10(sm, hint - 1), r);
@@ -297,17 +297,17 @@ __device__ __forceinline__ void decide_case(const LdsTables& sm, const typename 
   // chunk; -1: it did not)
   // the sample comes first and, when every value passes there, settles the
   // chunk without the test at L*.  Either order gives the same header.
-  bool all_pass = (HINT && hint >= 0) || all_pass_at_lstar();
+  bool all_pass = hint >= 0 || all_pass_at_lstar();
   if (all_pass) {
     sample();
     if (!s_bad && !s_rec_bad) {
       A = as;
       B = as + maxfl + 1;
       case1 = true;
-      if (HINT) hint = as;
+      hint = as;
       return;
     }
-    if (HINT && hint >= 0) {
+    if (hint >= 0) {
       hint = -1;
       all_pass = all_pass_at_lstar();
     }
