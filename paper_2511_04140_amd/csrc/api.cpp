@@ -2,9 +2,9 @@
 // context life cycle and the device-resident compress / decompress calls.
 //
 // A context owns a main lane (a HIP stream, a small pinned staging buffer
-// for the few bytes read back per call, the chunk offsets and size-pass
-// results of its launches, and the control block) and, once the host
-// pipeline is used, one lane per pipeline stream.
+// for the few bytes read back per call, the scratch of its launches, and the
+// control block) and, once the host pipeline is used, one lane per pipeline
+// stream.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include <string.h>
@@ -89,14 +89,18 @@ falcon_status queue_prepare(Queue& q, uint64_t nchunks, hipStream_t s) {
   uint64_t room = 1024;
   while (room < nchunks) room *= 2;
   room += kQueueSlack;
-  if (room < q.cap) room = q.cap;
-  const size_t had = q.cap;
-  size_t cap = had;
-  q.cap = 0;
-  falcon_status st = grow_raw(&q.size, &cap, room, s);
-  if (st != FALCON_OK) return st;
-  cap = had;
-  if ((st = grow_raw(&q.off, &cap, room, s)) != FALCON_OK) return st;
+  const size_t had = q.cap, cap = had > room ? had : room;
+  falcon_status st = FALCON_OK;
+  if (cap > had) {
+    q.cap = 0;
+    if ((q.size || q.off) && hipStreamSynchronize(s) != hipSuccess) return FALCON_ERR_DEVICE;
+    if (q.size) (void)hipFree(q.size);
+    if (q.off) (void)hipFree(q.off);
+    q.size = nullptr;
+    q.off = nullptr;
+    if (hipMalloc(&q.size, cap * sizeof(*q.size)) != hipSuccess || hipMalloc(&q.off, cap * sizeof(*q.off)) != hipSuccess)
+      return FALCON_ERR_OUT_OF_MEMORY;
+  }
   // Cleared now and not by a recorded fill, where s is being captured: calls
   // that are not recorded use the words too, and may come before any replay.
   hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
@@ -125,10 +129,11 @@ void queue_free(Queue& q) {
 }
 
 // Up to one 4-wave workgroup per CU (1,024 chunks), small workgroups spread
-// the chunks over more CUs; beyond that, 8-wave ones draw from 8 ticket
-// counters and scan twice as many sizes a round.  Decimal float64 data, 4
-// against 8 waves: 98 chunks 15.7 / 17.3 us, 1,024 chunks 20.2 / 20.6, 2,047
-// chunks 26.5 / 25.0, 16,369 chunks 87 / 70.
+// the chunks over more CUs; beyond that, larger ones (queue_large) draw from
+// as many ticket counters and scan more sizes a round.  Decimals, us a call:
+// float64, 4 against 8 waves, 98 chunks 10.8 / 12.5, 1,024 15.3 / 15.7, 1,200 16.9
+// / 16.3, 2,047 20.9 / 19.5, 16,369 76 / 56; float32, 4 against 12, 98 10.2 / 13.1,
+// 1,024 13.9 / 15.8, 2,047 18.7 / 17.1, 16,369 82 / 46.
 int queue_waves(uint64_t nchunks) { return nchunks <= 1024 ? 4 : 8; }
 
 // Moves the timing ring to a fresh slot for a timed call; the slot counts
@@ -525,7 +530,7 @@ falcon_status falcon_decompress(falcon_ctx* ctx, const void* d_in, size_t in_len
 }
 
 // The one-series-per-launch path over many series: one asynchronous call per
-// series, lengths written by the kernels to a device array, one wait.
+// series, lengths written by the kernels to pinned memory, one wait.
 falcon_status falcon_compress_each(falcon_ctx* ctx, falcon_series* ss, size_t count, void* stream) {
   if (!ctx || (count && !ss)) return FALCON_ERR_INVALID_ARG;
   for (size_t i = 0; i < count; ++i) {
