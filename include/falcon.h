@@ -105,9 +105,9 @@ enum {
 };
 
 /* Creates a context on HIP device `device` with options opts (NULL: the
- * defaults): a stream, pinned staging and device scratch (per-chunk
- * metadata, sizes and offsets for the prefix sum, work-queue counters and
- * status words, an error word), grown on demand.  Returns
+ * defaults): a stream, pinned memory (staging, stream lengths, error words)
+ * and device scratch (work-queue counters, a size and an offset word per
+ * chunk; metadata per chunk for the variants), grown on demand.  Returns
  * FALCON_ERR_INVALID_ARG for unknown option bits or form, FALCON_ERR_DEVICE
  * if the device cannot be used. */
 falcon_status falcon_create(int device, const falcon_opts* opts, falcon_ctx** out);
@@ -253,8 +253,10 @@ falcon_status falcon_decompress_host(falcon_ctx* ctx, const void* h_in, size_t i
 
 /* Sets the pipeline geometry used by the two calls above: n_streams HIP
  * streams (1..64; N_s of Alg. 1) and batch_chunks chunks of 1025 values per
- * batch (1..2^20).  Defaults: 4 streams, 2048 chunks (measured fastest on
- * MI355X; the paper's Sec. 5.1.4 setting is 16 streams, 4096 chunks).
+ * batch (1..2^20).  Defaults: 4 streams, 2048 chunks, for both directions.  On
+ * MI355X (2 GiB, pinned) that decompresses fastest, 46 GB/s; compression
+ * reaches 43 GB/s there and 50 on 2 streams.  The paper's Sec. 5.1.4 setting
+ * is 16 streams, 4096 chunks.
  * Device and pinned buffers (about 2 x 16.8 MB per stream at the default
  * batch, twice that when pageable buffers are staged) are allocated on
  * first use and kept until the geometry changes or the context is
@@ -319,7 +321,8 @@ typedef struct falcon_plan falcon_plan;
 
 typedef struct falcon_plan_info {
   int split;            /* 1: one launch per dtype; 0: one launch over both dtypes */
-  int waves_per_group;  /* wavefronts per workgroup (8: 12 in a launch of float32 series alone) */
+  int waves_per_group;  /* wavefronts per workgroup (8: 12 in a launch of float32 series alone); where an
+                           untuned plan's launches differ, what one launch of all chunks would take */
   int grid_percent;     /* grid as a percentage of the co-resident workgroups */
   int candidates;       /* geometries timed by the autotuner (0: not tuned) */
   float best_ms;        /* autotuner: time of the chosen geometry */
@@ -334,8 +337,8 @@ typedef struct falcon_plan_info {
 /* The one-series-per-launch path over count series, as a C loop: one
  * asynchronous falcon_compress (falcon_decompress_each: falcon_decompress_n)
  * per series, in order, on `stream`, each with its own launches; the stream
- * lengths are written by the kernels to device memory and read back once,
- * after a single wait at the end (s[i].out_len; decompression: s[i].n).
+ * lengths are written by the kernels to pinned memory and handed on after a
+ * single wait at the end (s[i].out_len; decompression: s[i].n).
  * Descriptors as for the batch calls below, checked on the host before any
  * launch.  It is the baseline that batch calls and plans are measured
  * against. */
@@ -386,10 +389,11 @@ void falcon_plan_destroy(falcon_plan* p);
  * one-request-per-launch FIFO. */
 typedef struct falcon_server falcon_server;
 
-/* Each lane also keeps the scratch of its batch launches (descriptors, chunk
- * sizes, offsets and metadata: about 36 bytes per chunk) outside the pool; a
- * batch takes requests only up to 2^22 chunks (at least one request), so this
- * stays below about 150 MB per lane. */
+/* Each lane also keeps the scratch of its batch launches (descriptors, a size
+ * and an offset word per chunk, 12 bytes, 4 more for decompression's scan;
+ * rounded up to powers of two) outside the pool; a batch takes requests only up
+ * to 2^22 chunks (at least one request), so this stays below about 100 MB per
+ * lane. */
 typedef struct falcon_server_opts {
   size_t hbm_budget;  /* bytes of the output pool (0: 64 GiB) */
   void* pool;         /* optional caller-owned device memory of hbm_budget bytes to use as the pool

@@ -1335,14 +1335,13 @@ __attribute__((amdgpu_waves_per_eu((T::W == 32 && WB == wave_blocks<T>()) ? 6 : 
 // wave waits between taking a chunk and publishing its size.  Both matter: an
 // offset needs the size of every earlier chunk, of which some 4,000 are under
 // way, so the slowest of them sets the wait.  Waiting right after the
-// assembly cost 500 us of 1,350 on 2 GiB of float64 readings; here a chunk
-// waits 1.1 us of 14.6 there, 0.75 of 10.9 on decimals, 2.3 of 11.6 in float32.
+// assembly cost 500 us of 1,350 on 2 GiB of float64 readings.
 // Bound by memory on float64 readings, by the scanning workgroup on float32
-// (528 chunks a microsecond), by instruction issue on float64 decimals.
+// (530 chunks a microsecond), by instruction issue on float64 decimals.
 // Against a size pass, three scan launches and a write pass, which read the
-// input twice: 2 GiB of float64 readings 1,208 -> 787 us, 512 MiB of
-// two-place decimals 300 -> 171, 512 MiB of mixed float32 353 -> 253, 8 MiB of
-// decimals 47 -> 15.5, 16 KB 38 -> 10.6 (per call in a row of calls).
+// input twice: 2 GiB of float64 readings 1,197 -> 754 us, 512 MiB of
+// two-place decimals 293 -> 169, 512 MiB of mixed float32 338 -> 247, 8 MiB of
+// decimals 47.5 -> 15.4, 16 KB 37.8 -> 10.3 (per call in a row of calls).
 // Sizes and offsets travel through device-scope words that are zero between
 // launches: the scanning workgroup clears a size when it has read it, a wave
 // an offset, and the last to draw from a counter that counter, so a launch
@@ -1442,9 +1441,9 @@ __device__ __forceinline__ bool chunks_fit(const CompressArgs& a) {
 // to keep up with the whole chip, some 500 chunks a microsecond, and nothing
 // else hides its latencies; a round reads 64 * scan_blocks sizes per wave, and
 // each wave scans its own part up to the first size still missing.  (One
-// wave alone moved 250 chunks a microsecond; with 1, 2, 4 and 8 blocks of 64 a
-// wave, 1 GiB of float32 took 1,134, 711, 544 and 560 us.)
-// In float32 12 waves of 2, 3, 4 and 6 blocks: 512 MiB 319, 271, 250, 248 us.
+// wave alone moved 250 chunks a microsecond.)  8 waves of 2, 4 and 8 blocks:
+// 512 MiB of float64 decimals 192, 169, 172 us, 2 GiB of readings 798, 766, 767;
+// 12 waves of 2, 3, 4 and 6 blocks: 512 MiB of mixed float32 309, 271, 252, 250.
 template <int NW>
 constexpr int scan_blocks() { return NW > 8 ? 6 : 4; }
 struct ScanPart {   // one wave's part of a round
@@ -1708,8 +1707,9 @@ __device__ __forceinline__ void empty_launch(const CompressArgs& a, int lane, in
 // workgroups count themselves at one word, the first scans, and workgroup
 // 1 + k takes the chunks NW * k to NW * k + NW - 1.  Numbered as they come, a
 // wave waits only for workgroups that came before its own, all resident.
-// Saves the wait for a ticket: 1,000 float64 values 10.9 -> 10.1 us a call,
-// 100,003 12.1 -> 11.2, 1 Mi 16.2 -> 15.4, 1 Mi float32 14.8 -> 14.1.
+// Saves the wait for a ticket: 1,000 float64 values 11.3 -> 10.1 us a call, 98
+// chunks 11.8 -> 10.8, 1,024 chunks 16.0 -> 15.3, in float32 9.9 -> 9.1, 10.7 ->
+// 10.2, 14.5 -> 14.0.
 template <bool MANY, int NW, int WB>
 __device__ __forceinline__ bool queue_prologue(BlockLdsT<NW, WB>& sm, const CompressArgs& a, uint64_t& first) {
   uint32_t* const role = reinterpret_cast<uint32_t*>(&sm.wave[0][0]);
@@ -1725,7 +1725,7 @@ __device__ __forceinline__ bool queue_prologue(BlockLdsT<NW, WB>& sm, const Comp
 
 // One dtype per launch.  MANY: a batch launch; one of a single series keeps
 // its descriptor in scalar registers (1 GiB of float32 549 -> 530 us, 8 MiB of
-// float64 21 -> 19 us).
+// float64 21 -> 19 us, in launches of 8 waves that all drew tickets).
 template <class T, int NW, bool MANY>
 __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(T::W == 32 ? 6 : 4))) void k_compress_queue(
     CompressArgs a) {
@@ -1823,8 +1823,8 @@ __device__ __forceinline__ void empty_series_checks(const DecompressArgs& a) {
 // that started together don't advance alike: a SIMD issues from its oldest
 // wave first, so with a fixed share each the oldest were done at 80 of 160 us
 // (128 Mi float32) and the youngest ran on alone.  Drawn, 2 GiB of
-// float64 readings take 672 us instead of 785, 512 MiB of decimals 132
-// instead of 147, 512 MiB of mixed float32 165 instead of 177.
+// float64 readings take 670 us instead of 785, 512 MiB of decimals 125
+// instead of 128, 512 MiB of mixed float32 150 instead of 164.
 // Counter g serves the workgroups g, g + kDrawGroups, ...: some of every age,
 // on one XCD, and the chunks 2 * total_waves + g + k * kDrawGroups.  A ticket is drawn a
 // whole chunk before its use, hence two fixed chunks.  Each wave draws one ticket past its
@@ -1834,8 +1834,8 @@ __device__ __forceinline__ void empty_series_checks(const DecompressArgs& a) {
 // just staged into LDS.
 // MANY: a batch launch, whose series each wave looks up per chunk.  A launch
 // of one series keeps its descriptor in scalar registers throughout: bound by
-// instruction issue, 1 GiB of float32 decodes in 343 us instead of 400 (with
-// the masks gone from stage_store).
+// instruction issue, 1 GiB of float32 took 343 us instead of 400 in fixed
+// shares (with the masks gone from stage_store); 254 now.
 template <bool DIRECT, bool MANY, class Dispatch>
 __device__ __forceinline__ void decompress_loop(const DecompressArgs& a, const uint64_t* tiles, uint8_t* buf,
                                                 uint32_t bufsize, int lane, int wid, uint64_t t_start, Dispatch&& dispatch) {

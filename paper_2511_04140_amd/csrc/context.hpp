@@ -131,8 +131,8 @@ struct falcon_ctx {
   // the context's own stream there is only its own work, so nothing is
   // recorded until a call changes streams: a record costs 3 us of a call's 16
   // (32 calls of 100,003 values, 515 us on the own stream, 608 on a caller's).
-  // A timed call has an event of its own (its ring slot),
-  // the others share the last.
+  // A timed call has an event of its own (its ring slot), the others share
+  // the last.
   hipEvent_t done[FALCON_TIMED_CALLS + 1] = {};
   bool done_recorded[FALCON_TIMED_CALLS + 1] = {};
   int call_slot = FALCON_TIMED_CALLS;  // of the call being made
@@ -150,8 +150,8 @@ struct falcon_ctx {
   };
   std::vector<PendingLen> pending;
   // co-resident workgroups of each kernel, by form (1 = f32, 2 = f64,
-  // 3 = mixed): decompression, and compression by workgroup size (4 or 8
-  // waves)
+  // 3 = mixed): decompression, and compression by workgroup size (4 waves, or
+  // queue_large: 8, 12 in float32)
   int grid_d[4] = {};
   int grid_q[4][2] = {};
   // the same for the ablation-variant compression kernels: [form][variant][pass]
@@ -168,9 +168,8 @@ struct falcon_ctx {
   uint64_t* times_host = nullptr;  // pinned, one slot
   int tick_khz = 100000;         // rate of the stamps' clock
   // host <-> device pipeline
-  // defaults measured on MI355X (4 hardware queues per process): 4 streams
-  // of 2048-chunk batches beat the 16 x 4096 setting of Sec. 5.1.4 in both
-  // directions
+  // defaults measured on MI355X (4 hardware queues per process): see
+  // falcon_set_pipeline
   int pipe_streams = 4;
   uint64_t pipe_batch_chunks = 2048;
   size_t pipe_buf_bytes = 0;     // bytes of each g_in / g_out / p_in / p_out
@@ -189,9 +188,10 @@ namespace falcon_host {
 
 // Enqueues the compression of n values at d_in into the stream buffer d_out
 // on lane l (stream s).  Nothing is waited for; the stream's payload byte
-// count lands in the stream header at d_out + 24.  With timed, events
-// around the kernel feed falcon_last_kernel_ms.  variant != 0 selects an
-// ablation variant's kernels (falcon_variant).  compress_failed() afterwards
+// count lands in the stream header at d_out + 24.  With timed, the
+// call feeds falcon_last_kernel_ms.  variant != 0 selects an ablation
+// variant's kernels (falcon_variant).  It also grows the lane's scratch for a
+// decompression of n values.  compress_failed() afterwards
 // (once the stream has passed the launch) tells whether it gave up.
 falcon_status enqueue_compress(falcon_ctx* ctx, Lane& l, const void* d_in, uint64_t n, falcon_dtype dt, void* d_out,
                                hipStream_t s, bool timed, int variant = 0, uint64_t* d_len = nullptr);

@@ -1,5 +1,5 @@
 // internal.hpp -- launch interface between the C ABI (api.cpp) and the
-// kernels (kernels.hip).  Not part of the public ABI.
+// kernels (kernels_*.hip).  Not part of the public ABI.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -28,8 +28,9 @@ constexpr int kRoleLines = 16;
 constexpr int kQueueStride = 16;
 // and those of decompression's draws, kDrawGroups lines from kDrawLine on,
 // used by launches of more than kDrawFrom chunks a wave: shorter ones gain
-// nothing (walks of float64, fixed against drawn: 4 chunks a wave 46.3 / 47.6
-// us, 5 54.5 / 53.7, 6 63.0 / 61.1, 8 79.7 / 76.0).
+// nothing.  Walks, fixed against drawn, us a call: float64 3 chunks a wave 46.8
+// / 46.8, 4 56.6 / 56.5, 5 66.3 / 63.0, 6 76.4 / 73.4, 8 95.5 / 91.5; float32 3
+// 35.8 / 37.6, 4 42.2 / 40.4, 5 47.8 / 48.0, 6 55.0 / 52.5, 8 68.5 / 65.1.
 constexpr int kDrawLine = kQueueGroups + 1 + kRoleLines;
 constexpr int kDrawGroups = 64;
 constexpr uint64_t kDrawFrom = 4;
@@ -128,9 +129,14 @@ struct DecompressArgs {
 
 // A decompression launch adds up its chunks' offsets itself (direct) when no
 // series is longer than this many chunks; else k_scan_local runs before it.
-// One float64 series, direct against scanned: 1 chunk 9.6 / 14.3 us, 1,024
-// chunks 12.2 / 16.7, 2,047 chunks 14.9 / 18.8, 4,093 chunks 28.0 / 27.6.
-// Plans of series of 1-360 chunks: 200 of them 57 / 67 us, 2,000 309 / 323.
+// One series, direct against scanned, us a call: float64 1 chunk 9.9 / 13.3,
+// 1,024 11.7 / 17.1, 4,093 17.8 / 22.3, 6,000 26.5 / 26.7, 8,000 36.2 / 37.5, 12,000
+// 52 / 47; float32 6.6 / 9.9, 8.5 / 13.8, 14.2 / 17.7, 18.9 / 20.8, 22.3 / 21.7,
+// 35.5 / 27.0.  So one series gains up to some 6,000 chunks; the line is lower
+// for what a batch of many long series loses, whose adding up is hidden by
+// nothing.  Plans: 200 series of 1-360 chunks 57 / 67 us, 2,000 309 / 323;
+// float64 1,024 series of 256 chunks 887 / 895, 128 of 2,048 915 / 860, 64 of 4,096
+// 953 / 862, float32 500 / 503, 489 / 460, 544 / 466.
 constexpr uint64_t kDirectChunks = 4096;
 
 // Wavefronts per workgroup of the two compression passes.  The float32
@@ -145,7 +151,7 @@ constexpr int kDecompressWaves = 4;   // wavefronts per decompression workgroup
 // beyond that 8, and 12 in float32 (two workgroups hold a CU's 24 waves).
 // float32 chunks are half as large, and one scanning workgroup of 8 waves
 // kept up with 490 of them a microsecond: 512 MiB of mixed float32, 8 against
-// 12 waves, 267 / 248 us, 256 MiB of decimals 143 / 125, 32 MiB 38.5 / 35.3;
+// 12 waves, 271 / 250 us, 256 MiB of decimals 143 / 124, 32 MiB 36.2 / 33.2;
 // 16 waves leave 4 a SIMD (286 / 141 / 33.3).  float64 in 16-wave
 // workgroups: 2 GiB of readings 781 / 827.
 constexpr int queue_large(int form) { return form == 1 ? 12 : 8; }
@@ -163,8 +169,8 @@ hipError_t launch_compress(const CompressArgs& a, int form, int pass, int grid, 
 // a.local and a.tiles are not used.
 hipError_t launch_decompress(const DecompressArgs& a, int form, bool direct, int grid, hipStream_t s);
 // One-launch compression (work queue over chunks, a scanning workgroup for the
-// offsets, so at least two workgroups), nw = 4 or 8 wavefronts per workgroup: a.qctr, a.qsize, a.qoff,
-// a.ctl set.
+// offsets, so at least two workgroups), nw = 4 or queue_large(form) wavefronts
+// per workgroup: a.qctr, a.qsize, a.qoff, a.ctl set.
 hipError_t launch_compress_queue(const CompressArgs& a, int form, int nw, int grid, hipStream_t s);
 hipError_t launch_compress_queue_f64(const CompressArgs& a, int nw, int grid, hipStream_t s);
 hipError_t launch_compress_queue_f32(const CompressArgs& a, int nw, int grid, hipStream_t s);

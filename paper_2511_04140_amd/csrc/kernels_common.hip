@@ -1,5 +1,5 @@
-// kernels_common.hip -- prefix scan of chunk sizes, batch preparation,
-// fill, and the dispatch of launches to the per-form translation units.
+// kernels_common.hip -- prefix scans of chunk sizes (two-pass compression,
+// decompression), fill, and the dispatch of launches to the per-form translation units.
 #include "codec_kernels.hpp"
 
 namespace falcon_dev {

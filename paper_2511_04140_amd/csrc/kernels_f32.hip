@@ -46,7 +46,7 @@ const void* compress_variant_kernel_f32(int variant, int pass) {
 }
 
 // For the occupancy.  A launch of one series would fit 7 waves a SIMD instead
-// of 6, and is slower for it (1 GiB: 354 against 343 us).
+// of 6, and is slower for it (1 GiB in fixed shares: 354 against 343 us).
 const void* decompress_kernel_f32() { return reinterpret_cast<const void*>(&k_decompress<TF32, false, true>); }
 
 template <int NW>

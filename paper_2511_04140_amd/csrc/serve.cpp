@@ -150,7 +150,7 @@ size_t output_bytes(const falcon_request& r) {
 }
 
 // A batch holds at most this many chunks, so that a lane's batch scratch
-// (about 36 bytes per chunk, outside the pool) stays below about 150 MB.
+// (16 bytes per chunk, outside the pool) stays below about 100 MB.
 constexpr uint64_t kLaneChunkCap = 1ull << 22;
 
 void complete(falcon_server* S, const Req& q, falcon_status st, size_t out_len, int lane = -1,
