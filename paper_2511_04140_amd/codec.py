@@ -478,7 +478,7 @@ class Codec:
             col = np.frombuffer(descs, _SERIES)
             col["d_in"] = [s_.data_ptr() for s_ in streams]
             # as a ctypes field takes them: integers of any kind, modulo 2^64
-            ns = [operator.index(counts[i]) for i in range(count)]
+            ns = list(map(operator.index, [counts[i] for i in range(count)]))
             try:
                 col["n"] = ns
             except OverflowError:
