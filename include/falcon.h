@@ -254,9 +254,9 @@ falcon_status falcon_decompress_host(falcon_ctx* ctx, const void* h_in, size_t i
 /* Sets the pipeline geometry used by the two calls above: n_streams HIP
  * streams (1..64; N_s of Alg. 1) and batch_chunks chunks of 1025 values per
  * batch (1..2^20).  Defaults: 4 streams, 2048 chunks, for both directions.  On
- * MI355X (2 GiB, pinned) that decompresses fastest, 46 GB/s; compression
- * reaches 43 GB/s there and 50 on 2 streams.  The paper's Sec. 5.1.4 setting
- * is 16 streams, 4096 chunks.
+ * MI355X (2 GiB, pinned) that compresses at 37-46 GB/s (2 streams: 50) and
+ * decompresses at 32-49 from run to run (1024 chunks: 36-46).  The paper's
+ * Sec. 5.1.4 setting is 16 streams, 4096 chunks.
  * Device and pinned buffers (about 2 x 16.8 MB per stream at the default
  * batch, twice that when pageable buffers are staged) are allocated on
  * first use and kept until the geometry changes or the context is
